@@ -795,7 +795,7 @@ __device__ __forceinline__ void ring_body(const double* __restrict__ G, S* __res
   } else {
     Sym<double> a = sym_get<D>(v + F::F1, kf);
     if (MODEL == M_HRR) a = hrr_mix(a, sym_get<D>(v + F::S, 0.5), sig, tau_f, rho);
-    N::eval(N::coef(rho, rho, u, om_f, a), f);
+    N::regular(rho, rho, u, om_f, a, f);
   }
   int x, y, z;
   fdecode(g, itf.rnode[r], x, y, z);
@@ -974,7 +974,7 @@ __device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __
                            2.0 * (0.5 * (gr[1][2] + gr[2][1]))};
       a = hrr_mix(a, Sc, sig, tau_c, rc);
     }
-    N::eval(N::coef(rc, rc, uc, om_c, a), f);
+    N::regular(rc, rc, uc, om_c, a, f);
   }
   int cx, cy, cz;
   cdecode(g, itf.tnc[t3], cx, cy, cz);

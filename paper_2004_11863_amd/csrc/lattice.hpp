@@ -80,10 +80,6 @@ struct Sym {
   T xx, yy, zz, xy, xz, yz;
 };
 
-// Third-order Hermite polynomial H_abc(xi) - the c_s^2 = 1/3 terms - for the
-// mixed components the lattices use: H_aab = xi_a^2 xi_b - xi_b / 3.
-__host__ __device__ constexpr double h3aab(int a, int b) { return (double)(a * a * b) - b / 3.0; }
-
 // ---------------------------------------------------------------------------
 // Per-node physics in moment space.
 //
@@ -92,15 +88,22 @@ __host__ __device__ constexpr double h3aab(int a, int b) { return (double)(a * a
 //   s_i = w_i [ A + xi_i.J + xi_i xi_i : M + sum_P H_P(xi_i) K_P ],
 // where the H_P are the third-order Hermite polynomials the lattice carries
 // (D2Q9: H_xxy, H_xyy; D3Q19: the sums and differences of the pairs
-// (H_xxy, H_yzz), (H_xzz, H_xyy), (H_yyz, H_xxz)).  The node computes the
-// coefficients (A, J, M, K) once and evaluates opposite velocities together:
-// the even part A + xi xi : M is shared, the odd part flips sign.
+// (H_xxy, H_yzz), (H_xzz, H_xyy), (H_yyz, H_xxz)).  The node computes a few
+// coefficients once and evaluates opposite velocities together: the even part
+// A + xi xi : M is shared, the odd part flips sign (build()).
+//
+// The bulk kernels issue as much arithmetic as they move bytes (k_fine2 keeps
+// the vector ALU 65-76 % busy), so the collision is written for few
+// operations: the momentum j is used as summed (never rho times u again), the
+// products t_ab = j_a u_b serve the equilibrium, the non-equilibrium moment
+// and the third order, the weights are folded into the coefficients, and the
+// third-order terms are taken per plane (on a diagonal of plane (a, b) only
+// K_aab and K_abb remain of the sums and differences).
 template <int LAT, bool DEV, typename T>
 struct Node {
   using L = Lattice<LAT>;
   static constexpr int Q = L::Q;
   static constexpr int D = L::D;
-  static constexpr int NP = D == 2 ? 2 : 6;
 
   // index of the opposite velocity
   __host__ __device__ static constexpr int opp(int i) {
@@ -108,29 +111,11 @@ struct Node {
       if (L::cx(j) == -L::cx(i) && L::cy(j) == -L::cy(i) && L::cz(j) == -L::cz(i)) return j;
     return i;
   }
-  // value of third-order basis polynomial p at velocity i
-  __host__ __device__ static constexpr double hp(int p, int i) {
-    const int x = L::cx(i), y = L::cy(i), z = L::cz(i);
-    if (D == 2) return p == 0 ? h3aab(x, y) : h3aab(y, x);
-    const double pa[3] = {h3aab(x, y), h3aab(z, x), h3aab(y, z)};  // xxy, xzz, yyz
-    const double pb[3] = {h3aab(z, y), h3aab(y, x), h3aab(x, z)};  // yzz, xyy, xxz
-    return p < 3 ? pa[p] + pb[p] : pa[p - 3] - pb[p - 3];
-  }
-  // 1 / (lattice norm of H_P), i.e. 1/(2 c_s^6) or 1/(6 c_s^6)
-  __host__ __device__ static constexpr double cp(int p) { return (D == 2 || p < 3) ? 13.5 : 4.5; }
-
-  struct Coef {
-    T A;
-    T J[3];
-    Sym<T> M;
-    T K[6];
-  };
-
   // eqs moment_rho, moment_rhoU.  r0: sum of stored values (rho for DEV = 0,
   // rho - 1 for DEV = 1).  Opposite velocities enter as the pair sum (even
   // moments) and the pair difference (odd moments); sums start from -0, which
   // the compiler folds away (x + -0 = x exactly).
-  __device__ __host__ static __forceinline__ void moments(const T* s, T& rho, T& r0, T* u) {
+  __device__ __host__ static __forceinline__ void moments(const T* s, T& rho, T& r0, T* j, T* u) {
     T m = s[0], jx = T(-0.0), jy = T(-0.0), jz = T(-0.0);
     static_for<Q>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
@@ -149,9 +134,16 @@ struct Node {
     r0 = m;
     rho = DEV ? T(1) + m : m;
     const T ir = T(1) / rho;
+    j[0] = jx;
+    j[1] = jy;
+    j[2] = (D == 3) ? jz : T(0);
     u[0] = jx * ir;
     u[1] = jy * ir;
     u[2] = (D == 3) ? jz * ir : T(0);
+  }
+  __device__ __host__ static __forceinline__ void moments(const T* s, T& rho, T& r0, T* u) {
+    T j[3];
+    moments(s, rho, r0, j, u);
   }
 
   // Second moments Pi_ab = sum_i xi_a xi_b s_i, from the pair sums (xi_a xi_b
@@ -179,105 +171,108 @@ struct Node {
     return Sym<T>{pxx, pyy, pzz, pxy, pxz, pyz};
   }
 
-  // Third-order coefficient combinations of a fully symmetric tensor given
-  // by its components (xxy, xyy, yzz, xzz, yyz, xxz), in basis order.
-  __device__ __host__ static __forceinline__ void third_combo(T xxy, T xyy, T yzz, T xzz, T yyz, T xxz, T* out) {
-    if (D == 2) {
-      out[0] = xxy;
-      out[1] = xyy;
+  // j_a u_b = rho u_a u_b.
+  __device__ __host__ static __forceinline__ Sym<T> flux(const T* j, const T* u) {
+    Sym<T> t;
+    t.xx = j[0] * u[0];
+    t.yy = j[1] * u[1];
+    t.xy = j[0] * u[1];
+    t.zz = D == 3 ? j[2] * u[2] : T(0);
+    t.xz = D == 3 ? j[0] * u[2] : T(0);
+    t.yz = D == 3 ? j[1] * u[2] : T(0);
+    return t;
+  }
+
+  // All Q stored values of f0 + om f1^RR (eqs fEqO3, f1RR, a13RR) from r0, the
+  // momentum j, the velocity u, t = flux(j, u) and m = t + om a1^(2):
+  //   A = r0 - 3/2 tr m,  J = 3 j,  M = 9/2 m,
+  //   third order rho u_a u_a u_b + om a1^(3)_aab = 2 u_a m_ab + u_b (m_aa - 2 t_aa)
+  // (eq a13RR: a1^(3)_aab = 2 u_a a1_ab + u_b a1_aa).  EQ: the equilibrium
+  // alone, m = t, where the third order is u_b t_aa.
+  // With w = 1/36 on every two-axis velocity the value there is
+  //   A/36 + (M_aa + M_bb)/36 +- m_ab/4 +- (g_a +- g_b),  g_a = j_a/12 + K_abb/4,
+  // M_aa/36 = m_aa/8; the even part of the one-axis velocities is 4 (D2Q9) or
+  // 2 (D3Q19) times (A + M_aa)/36.  The rest population and the odd part of
+  // the one-axis velocities are taken as what is left of r0 and j: the
+  // factors 1/36 and 1/12 are not exact in binary, and with a rounded factor
+  // on every velocity the same relative error would enter the mass and the
+  // momentum at every collision.
+  template <bool EQ>
+  __device__ __host__ static __forceinline__ void build(T r0, const T* j, const T* u, const Sym<T>& t,
+                                                        const Sym<T>& m, T* out) {
+    const T B = r0 - T(1.5) * (D == 3 ? m.xx + m.yy + m.zz : m.xx + m.yy);
+    const T A = B * T(1.0 / 36.0);
+    const T nx = T(0.125) * m.xx, ny = T(0.125) * m.yy, nz = T(0.125) * m.zz;
+    const T jx = T(1.0 / 12.0) * j[0], jy = T(1.0 / 12.0) * j[1], jz = T(1.0 / 12.0) * j[2];
+    // K_aab = 2 u_a m_ab + u_b q_aa
+    const T qx = EQ ? t.xx : m.xx - T(2) * t.xx, qy = EQ ? t.yy : m.yy - T(2) * t.yy;
+    const T qz = EQ ? t.zz : m.zz - T(2) * t.zz;
+    const T vx = T(2) * u[0], vy = T(2) * u[1], vz = T(2) * u[2];
+    auto third = [](T va, T mab, T ub, T qa) __attribute__((always_inline)) { return EQ ? ub * qa : va * mab + ub * qa; };
+    // g_a of plane (a, b) from K_abb
+    auto odd = [](T ja, T kabb) __attribute__((always_inline)) { return ja + T(0.25) * kabb; };
+    // one-axis velocities along a (i, its opposite o): r times the even part
+    // e, the odd part o
+    auto axis = [&](T r, T e, T o, int i, int io) __attribute__((always_inline)) {
+      out[i] = r * e + o;
+      out[io] = r * e - o;
+    };
+    // two-axis velocities of plane (a, b): p (+,+), its opposite, q (+,-),
+    // its opposite
+    auto plane = [&](T na, T nb, T mab, T ga, T gb, int p, int po, int q, int qo) __attribute__((always_inline)) {
+      const T e = A + na + nb;
+      const T ep = e + T(0.25) * mab, eq = e - T(0.25) * mab;
+      const T op = ga + gb, oq = ga - gb;
+      out[p] = ep + op;
+      out[po] = ep - op;
+      out[q] = eq + oq;
+      out[qo] = eq - oq;
+    };
+    if constexpr (D == 2) {
+      const T gx = odd(jx, third(vy, m.xy, u[0], qy)), gy = odd(jy, third(vx, m.xy, u[1], qx));
+      out[0] = B - T(20) * A;
+      axis(T(4), A + nx, T(0.5) * j[0] - T(2) * gx, 1, 3);
+      axis(T(4), A + ny, T(0.5) * j[1] - T(2) * gy, 2, 4);
+      plane(nx, ny, m.xy, gx, gy, 5, 7, 8, 6);
     } else {
-      out[0] = xxy + yzz;
-      out[1] = xzz + xyy;
-      out[2] = yyz + xxz;
-      out[3] = xxy - yzz;
-      out[4] = xzz - xyy;
-      out[5] = yyz - xxz;
+      const T gxy = odd(jx, third(vy, m.xy, u[0], qy)), gxz = odd(jx, third(vz, m.xz, u[0], qz));
+      const T gyx = odd(jy, third(vx, m.xy, u[1], qx)), gyz = odd(jy, third(vz, m.yz, u[1], qz));
+      const T gzx = odd(jz, third(vx, m.xz, u[2], qx)), gzy = odd(jz, third(vy, m.yz, u[2], qy));
+      out[0] = B - T(24) * A;
+      axis(T(2), A + nx, T(0.5) * j[0] - T(2) * (gxy + gxz), 1, 2);
+      axis(T(2), A + ny, T(0.5) * j[1] - T(2) * (gyx + gyz), 3, 4);
+      axis(T(2), A + nz, T(0.5) * j[2] - T(2) * (gzx + gzy), 5, 6);
+      plane(nx, ny, m.xy, gxy, gyx, 7, 8, 9, 10);
+      plane(nx, nz, m.xz, gxz, gzx, 11, 12, 13, 14);
+      plane(ny, nz, m.yz, gyz, gzy, 15, 16, 17, 18);
     }
   }
 
-  // Coefficients of om * f1^RR + f0 (eqs fEqO3, f1RR, a13RR), a = a1^(2):
-  //   A = r0 - 3/2 rho u^2 - 3/2 om tr(a),  J = 3 rho u,
-  //   M = 9/2 (rho u u + om a),            K_P = c_P (rho u^3 + om a1^(3))_P.
-  // om = 0 gives the equilibrium alone.
-  __device__ __host__ static __forceinline__ Coef coef(T rho, T r0, const T* u, T om, const Sym<T>& a) {
-    Coef c;
-    const T usq = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const T tra = a.xx + a.yy + a.zz;
-    c.A = r0 - T(1.5) * rho * usq - T(1.5) * om * tra;
-    c.J[0] = T(3) * rho * u[0];
-    c.J[1] = T(3) * rho * u[1];
-    c.J[2] = T(3) * rho * u[2];
-    c.M.xx = T(4.5) * (rho * u[0] * u[0] + om * a.xx);
-    c.M.yy = T(4.5) * (rho * u[1] * u[1] + om * a.yy);
-    c.M.zz = T(4.5) * (rho * u[2] * u[2] + om * a.zz);
-    c.M.xy = T(4.5) * (rho * u[0] * u[1] + om * a.xy);
-    c.M.xz = T(4.5) * (rho * u[0] * u[2] + om * a.xz);
-    c.M.yz = T(4.5) * (rho * u[1] * u[2] + om * a.yz);
-    // a1^(3)_abg = u_a a_bg + u_b a_ag + u_g a_ab (eq a13RR), mixed components
-    const T b_xxy = T(2) * u[0] * a.xy + u[1] * a.xx;
-    const T b_xyy = T(2) * u[1] * a.xy + u[0] * a.yy;
-    const T b_yzz = T(2) * u[2] * a.yz + u[1] * a.zz;
-    const T b_xzz = T(2) * u[2] * a.xz + u[0] * a.zz;
-    const T b_yyz = T(2) * u[1] * a.yz + u[2] * a.yy;
-    const T b_xxz = T(2) * u[0] * a.xz + u[2] * a.xx;
-    const T ru0 = rho * u[0], ru1 = rho * u[1];
-    T k[6];
-    third_combo(ru0 * u[0] * u[1] + om * b_xxy, ru0 * u[1] * u[1] + om * b_xyy, ru1 * u[2] * u[2] + om * b_yzz,
-                ru0 * u[2] * u[2] + om * b_xzz, ru1 * u[1] * u[2] + om * b_yyz, ru0 * u[0] * u[2] + om * b_xxz, k);
-#pragma unroll
-    for (int p = 0; p < NP; ++p) c.K[p] = T(cp(p)) * k[p];
-    return c;
+  // t + om a, componentwise.
+  __device__ __host__ static __forceinline__ Sym<T> relaxed(const Sym<T>& t, T om, const Sym<T>& a) {
+    Sym<T> m;
+    m.xx = t.xx + om * a.xx;
+    m.yy = t.yy + om * a.yy;
+    m.xy = t.xy + om * a.xy;
+    m.zz = D == 3 ? t.zz + om * a.zz : T(0);
+    m.xz = D == 3 ? t.xz + om * a.xz : T(0);
+    m.yz = D == 3 ? t.yz + om * a.yz : T(0);
+    return m;
   }
 
-  template <int i>
-  __device__ __host__ static __forceinline__ T even(const Coef& c) {
-    constexpr int x = L::cx(i), y = L::cy(i), z = L::cz(i);
-    T e = c.A;
-    if (x) e += c.M.xx;
-    if (y) e += c.M.yy;
-    if (D == 3 && z) e += c.M.zz;
-    if (x * y) e += T(2 * x * y) * c.M.xy;
-    if (D == 3 && x * z) e += T(2 * x * z) * c.M.xz;
-    if (D == 3 && y * z) e += T(2 * y * z) * c.M.yz;
-    return e;
-  }
-  template <int i>
-  __device__ __host__ static __forceinline__ T odd(const Coef& c) {
-    constexpr int x = L::cx(i), y = L::cy(i), z = L::cz(i);
-    T o = T(-0.0);  // folded away by the first term
-    if (x > 0) o += c.J[0];
-    if (x < 0) o -= c.J[0];
-    if (y > 0) o += c.J[1];
-    if (y < 0) o -= c.J[1];
-    if (D == 3 && z > 0) o += c.J[2];
-    if (D == 3 && z < 0) o -= c.J[2];
-    static_for<NP>([&](auto pc) {
-      constexpr int p = decltype(pc)::value;
-      constexpr double h = hp(p, i);
-      if (h != 0.0) o += T(h) * c.K[p];
-    });
-    return o;
-  }
-
-  // All Q stored values from coefficients.
-  __device__ __host__ static __forceinline__ void eval(const Coef& c, T* out) {
-    out[0] = T(L::w(0)) * even<0>(c);
-    static_for<Q>([&](auto ic) {
-      constexpr int i = decltype(ic)::value;
-      constexpr int j = opp(i);
-      if constexpr (i != 0 && i < j) {
-        const T e = even<i>(c), o = odd<i>(c);
-        out[i] = T(L::w(i)) * (e + o);
-        out[j] = T(L::w(j)) * (e - o);
-      }
-    });
+  // Stored values of f0(rho, u) + om f1^RR(a) from given rho, u and a1^(2) = a.
+  __device__ __host__ static __forceinline__ void regular(T rho, T r0, const T* u, T om, const Sym<T>& a, T* out) {
+    const T j[3] = {rho * u[0], rho * u[1], D == 3 ? rho * u[2] : T(0)};
+    const Sym<T> t = flux(j, u);
+    build<false>(r0, j, u, t, relaxed(t, om, a), out);
   }
 
   // Stored-form equilibrium s0_i = f0_i - DEV w_i (eq fEqO3 and its D3Q19
   // counterpart).
   __device__ __host__ static __forceinline__ void feq(T rho, T r0, const T* u, T* out) {
-    const Sym<T> z{T(0), T(0), T(0), T(0), T(0), T(0)};
-    eval(coef(rho, r0, u, T(0), z), out);
+    const T j[3] = {rho * u[0], rho * u[1], D == 3 ? rho * u[2] : T(0)};
+    const Sym<T> t = flux(j, u);
+    build<true>(r0, j, u, t, t, out);
   }
 
   // Collision of one node, in place on stored populations s[Q].
@@ -288,11 +283,12 @@ struct Node {
   // sum_i xi xi f0_i = rho (u u + c_s^2 I), so a1 = Pi - r0/3 I - rho u u
   // in stored form (the rest state carries Pi = I/3).
   __device__ __host__ static __forceinline__ void collide(T* s, int model, T om, T tau, T sig, const Sym<T>* S) {
-    T rho, r0, u[3];
-    moments(s, rho, r0, u);
+    T rho, r0, j[3], u[3];
+    moments(s, rho, r0, j, u);
+    const Sym<T> t = flux(j, u);
     if (model == 0) {
       T s0[Q];
-      feq(rho, r0, u, s0);
+      build<true>(r0, j, u, t, t, s0);
 #pragma unroll
       for (int i = 0; i < Q; ++i) s[i] = s0[i] + om * (s[i] - s0[i]);
       return;
@@ -300,12 +296,12 @@ struct Node {
     const Sym<T> P = second(s);
     const T tr0 = r0 * T(1.0 / 3.0);
     Sym<T> a;
-    a.xx = P.xx - tr0 - rho * u[0] * u[0];
-    a.yy = P.yy - tr0 - rho * u[1] * u[1];
-    a.zz = (D == 3) ? P.zz - tr0 - rho * u[2] * u[2] : T(0);
-    a.xy = P.xy - rho * u[0] * u[1];
-    a.xz = (D == 3) ? P.xz - rho * u[0] * u[2] : T(0);
-    a.yz = (D == 3) ? P.yz - rho * u[1] * u[2] : T(0);
+    a.xx = (P.xx - tr0) - t.xx;
+    a.yy = (P.yy - tr0) - t.yy;
+    a.zz = (D == 3) ? (P.zz - tr0) - t.zz : T(0);
+    a.xy = P.xy - t.xy;
+    a.xz = (D == 3) ? P.xz - t.xz : T(0);
+    a.yz = (D == 3) ? P.yz - t.yz : T(0);
     if (model == 2) {
       const T k = (T(1) - sig) * (T(-2.0 / 3.0) * tau * rho);
       a.xx = sig * a.xx + k * S->xx;
@@ -317,7 +313,7 @@ struct Node {
         a.yz = sig * a.yz + k * S->yz;
       }
     }
-    eval(coef(rho, r0, u, om, a), s);
+    build<false>(r0, j, u, t, relaxed(t, om, a), s);
   }
 };
 
