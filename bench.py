@@ -87,9 +87,7 @@ def kernel_label(D, collision, variants=None):
     if collision == "HRR" and D == 2:
         return "k_hrr2: one H-RR fine substep in one pass (pull, velocities of the tile in LDS, strain rate, collide)"
     if collision == "HRR":
-        if v[3] == 2:
-            return "k_hrr3: one H-RR fine substep in one marching pass (velocity planes in LDS, strain rate, collide)"
-        if v[3] == 3:
+        if v[3] >= 2:
             return ("k_hrr3s: one H-RR fine substep in one marching pass, one node per lane (velocity planes in "
                     "LDS, strain rate, collide)")
         return "k_collide_hrr: fine-level pull + H-RR collide (second pass)"

@@ -1503,6 +1503,15 @@ __global__ __launch_bounds__(HXV * HYR) void k_hrr2(const S* __restrict__ src, S
 // population), in the y- and z-bands into `half`; the t+1/2 ring
 // reconstruction fills both, and a ring column x = 0 / nx - 1 away from the
 // z faces reads the populations it sends inward from `xb`.
+//
+// Bound by the memory system and, next, by vector-ALU issue: a tile's rows
+// start and end inside 128-byte lines that the neighbouring tile completes.
+// The stores of the result are cached, so that the L2 joins the two parts
+// (non-temporal ones went out as partial lines: 3156 -> 2908 us per coarse
+// step on the 385^3 patch, FP32 RR, 64 x 16 tiles; 2234 -> 1774 us on a 257^3
+// patch in FP64), and rows are long (64 x 16 tiles 2908 us, 66 x 15 2988,
+// 98 x 10 2742, 130 x 7 2596: fewer lines per node outweigh the wider halo
+// in y, 7 rows for 5).
 template <int LAT>
 struct ZSets {
   using L = Lattice<LAT>;
@@ -1565,8 +1574,8 @@ struct Window {
   }
 };
 
-template <int LAT, bool DEV, typename S, int MODEL, bool NT, int TXH, int TYH, int MINW>
-__global__ __launch_bounds__(TXH * TYH, MINW) void k_fine3s(const S* __restrict__ src, S* __restrict__ dst,
+template <int LAT, bool DEV, typename S, int MODEL, int TXH, int TYH>
+__global__ __launch_bounds__(TXH * TYH) void k_fine3s(const S* __restrict__ src, S* __restrict__ dst,
                                                             S* __restrict__ half, S* __restrict__ xb, const Geo g,
                                                             const S om, int ntx, int nty, int nzc, int zlen,
                                                             int per_xcd) {
@@ -1809,36 +1818,48 @@ __global__ __launch_bounds__(TXH * TYH, MINW) void k_fine3s(const S* __restrict_
     }
     const uint32_t bo = Wn::boff(dl - pz) | minner;  // (x, y, z)
 #pragma unroll
-    for (int i = 0; i < Q; ++i) Wn::template store<NT>(rd, bo, i, f[i]);
+    for (int i = 0; i < Q; ++i) Wn::template store<false>(rd, bo, i, f[i]);
     buf ^= 1;
     shift(T);
   }
 }
 
 // ---------------------------------------------------------------------------
-// One H-RR fine substep in one pass with one node per lane (D3Q19, k_hrr3s).
-// A work group of TXH x TYH lanes holds the columns of a tile of (TXH - 2) x
-// (TYH - 2) middle nodes and its one-node halo and walks a run of zlen planes
-// along z.  The iteration for plane z takes the populations of plane z+1,
-// pulled two iterations earlier, computes their velocities (ring nodes: from
-// the velocity planes, where the ring macro step stored them) into one of
-// four LDS velocity planes and issues the pulls of plane z+3 into the
-// registers they leave (two planes of pulls in flight: two register sets,
-// the loop unrolled by two); after one barrier the inner lanes take the
-// strain rate of plane z by centred
-// differences from the planes of z-1, z and z+1 and collide the populations
-// of plane z they kept from the previous iteration.  Four velocity planes
-// rotate, so the plane written in one iteration is never one read in the
-// iteration before, and one barrier per plane suffices.  Every memory
-// operation is issued by every lane (masked lanes get offsets past the
-// window), so the loads of a plane stay in flight across the stores of the
-// one before.  Same arithmetic as the velocity pass followed by
-// k_collide_hrr, so bitwise the same.
-template <int LAT, bool DEV, typename S, bool NT, int TXH, int TYH, int MINW>
-__global__ __launch_bounds__(TXH * TYH, MINW) void k_hrr3s(const S* __restrict__ src, S* __restrict__ dst,
-                                                           const S* __restrict__ mac, const Geo g, const S om,
-                                                           const S tau, const S sig, int ntx, int nty, int nzc,
-                                                           int zlen, int per_xcd) {
+// One H-RR step of a level in one pass with one node per lane (D3Q19,
+// k_hrr3s): LEVEL 1 a fine substep, LEVEL 0 a coarse step.  A work group of
+// TXH x TYH lanes holds the columns of a tile of (TXH - 2) x (TYH - 2) nodes
+// and its one-node halo and walks a run of zlen planes along z.  The
+// iteration for plane z takes the populations of plane z+1, pulled two
+// iterations earlier, computes their velocities into one of four LDS velocity
+// planes and issues the pulls of plane z+3 into the registers they leave (two
+// planes of pulls in flight: two register sets, the loop unrolled by two);
+// after one barrier the inner lanes take the strain rate of plane z by
+// centred differences from the planes of z-1, z and z+1 and collide the
+// populations of plane z they kept from the previous iteration.  Four
+// velocity planes rotate, so the plane written in one iteration is never one
+// read in the iteration before, and one barrier per plane suffices.  Nodes
+// whose velocity another kernel provides take it from the velocity planes:
+// the fine ring (ring macro step), coarse TN nodes (fictitious propagation).
+// Coarse TN nodes are rebuilt by the transfer and covered ones are not
+// evolved: neither is pulled or stored (covered ones count as velocity 0 for
+// their TN neighbours).  Every memory operation is issued by every lane
+// (masked lanes get offsets past the window), so the loads of a plane stay in
+// flight across the stores of the one before.  Each plane is addressed
+// through a buffer resource of its own, whose base is a scalar: the periodic
+// wrap in z is a scalar select, and only one plane has to stay below 2^31
+// bytes.  Same arithmetic as the velocity pass followed by k_collide_hrr, so
+// bitwise the same.
+//
+// Bound by the memory system: a tile's rows start and end inside 128-byte
+// lines that a neighbouring tile completes.  Stores are cached, so that the
+// L2 joins the two parts (non-temporal ones went out as partial lines:
+// 945 -> 783 us for the 257^3 fine level of a 256^3 grid, FP32, 64 x 8
+// tiles), and rows are long (64 x 8 783 us, 34 x 15 659, 66 x 15 616,
+// 130 x 7 612).
+template <int LAT, bool DEV, typename S, int LEVEL, int TXH, int TYH>
+__global__ __launch_bounds__(TXH * TYH) void k_hrr3s(const S* __restrict__ src, S* __restrict__ dst,
+                                                     const S* __restrict__ mac, const Geo g, const S om, const S tau,
+                                                     const S sig, int ntx, int nty, int nzc, int zlen, int per_xcd) {
   using L = Lattice<LAT>;
   using N = Node<LAT, DEV, S>;
   constexpr int Q = L::Q, NL = TXH * TYH;
@@ -1851,78 +1872,117 @@ __global__ __launch_bounds__(TXH * TYH, MINW) void k_hrr3s(const S* __restrict__
   if (item >= ntile * nzc) return;  // whole work group, before any barrier
   const int zc = item / ntile, tile = item - zc * ntile;
   const int tx = tile % ntx, ty = tile / ntx;
-  const int nx = g.nf[0], ny = g.nf[1], nz = g.nf[2];
+  constexpr int O = LEVEL == 0 ? 1 : 0;  // the coarse tiles start at node 0, the fine ones at node 1
+  const int nx = LEVEL == 0 ? g.n[0] : g.nf[0], ny = LEVEL == 0 ? g.n[1] : g.nf[1];
+  const int nz = LEVEL == 0 ? g.n[2] : g.nf[2];
+  const int pitch = LEVEL == 0 ? g.pc : g.pf, xoff = LEVEL == 0 ? 0 : g.fxo;
+  const int64_t NP = LEVEL == 0 ? g.Ncp : g.Nfp;
+  const int zs = 1 - O + zc * zlen, ze = min(zs + zlen - 1, nz - 2 + O);
+  if (LEVEL == 0 && g.has_fine) {
+    // a run wholly inside the covered box is not evolved
+    const int xa = tx * (TXH - 2), xe = min(xa + TXH - 3, nx - 1), ya = ty * (TYH - 2), ye = min(ya + TYH - 3, ny - 1);
+    if (xa >= g.a[0] + 2 && xe <= g.a[0] + g.m[0] - 2 && ya >= g.a[1] + 2 && ye <= g.a[1] + g.m[1] - 2 &&
+        zs >= g.a[2] + 2 && ze <= g.a[2] + g.m[2] - 2)
+      return;  // whole work group
+  }
   const int t = threadIdx.x;
   const int hx = t % TXH, hy = t / TXH;
-  const int x = tx * (TXH - 2) + hx, y = ty * (TYH - 2) + hy;
-  const bool live = x <= nx - 1 && y <= ny - 1;
-  const bool inner = live && hx >= 1 && hx <= TXH - 2 && hy >= 1 && hy <= TYH - 2 && x <= nx - 2 && y <= ny - 2;
-  const bool xyring = live && (x == 0 || x == nx - 1 || y == 0 || y == ny - 1);
-  const int zs = 1 + zc * zlen, ze = min(zs + zlen - 1, nz - 2);
-  // storage window of the run (pulls reach planes zs - 2 .. ze + 2); the
-  // velocity planes are addressed from the same first position
-  using Wn = Window<S, Q>;
-  const Wn W(fpos(g, 0, 0, max(zs - 2, 0)));
-  const __amdgpu_buffer_rsrc_t rs = W.rsrc(src), rd = W.rsrc(dst);
-  const __amdgpu_buffer_rsrc_t rm =
-      __builtin_amdgcn_make_buffer_rsrc((void*)(mac + W.pb0), (short)0, (int)Wn::kOff, 0x00020000);
-  const int mplane = (int)(g.Nfp * (int64_t)sizeof(S));  // bytes between velocity planes
-  const uint32_t py = (uint32_t)g.pf, pz = (uint32_t)g.pf * (uint32_t)ny;
-  const uint32_t d0 = live ? (uint32_t)(fpos(g, x, y, zs - 1) - W.pb0) : 0u;  // node in plane zs - 1
-  const uint32_t mpull = (live && !xyring) ? 0u : Wn::kOff;
-  const uint32_t minner = inner ? 0u : Wn::kOff;
-  S H[Q], P0[Q], P1[Q], U0[3], U1[3];
-  // pulls of plane zp (window position d) into P; velocities of ring nodes
-  // (ring planes, columns and rows) from the velocity planes into UR
-  auto load = [&](int zp, uint32_t d, S (&P)[Q], S (&UR)[3]) __attribute__((always_inline)) {
-    const bool pring = zp == 0 || zp == nz - 1;
-#pragma unroll
-    for (int i = 0; i < Q; ++i)
-      P[i] = Wn::load(rs, Wn::boff(d - L::cx(i) - py * L::cy(i) - pz * L::cz(i)) | (pring ? Wn::kOff : mpull), i);
-    const uint32_t mo = (uint32_t)sizeof(S) * d | ((pring && live) || xyring ? 0u : Wn::kOff);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if constexpr (sizeof(S) == 4)
-        UR[k] = __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(rm, (int)mo, (1 + k) * mplane, 0));
-      else
-        UR[k] = __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(rm, (int)mo, (1 + k) * mplane, 0));
+  const int x = tx * (TXH - 2) + hx - O, y = ty * (TYH - 2) + hy - O;  // coarse: -1 .. n, periodic
+  const bool live = x <= nx - 1 + O && y <= ny - 1 + O;
+  const bool inner = live && hx >= 1 && hx <= TXH - 2 && hy >= 1 && hy <= TYH - 2 && x <= nx - 2 + O && y <= ny - 2 + O;
+  const int xw = LEVEL == 0 ? wrap(x, nx) : x, yw = LEVEL == 0 ? wrap(y, ny) : y;
+  // nodes not pulled: edge (fine ring column, or a column of the TN shell's
+  // sides) and, on the planes zin, the columns of the box
+  bool edge, box = false;
+  if constexpr (LEVEL == 0) {
+    const bool bx = xw >= g.a[0] + 1 && xw <= g.a[0] + g.m[0] - 1, by = yw >= g.a[1] + 1 && yw <= g.a[1] + g.m[1] - 1;
+    box = g.has_fine && bx && by;
+    edge = xw == g.a[0] + 1 || xw == g.a[0] + g.m[0] - 1 || yw == g.a[1] + 1 || yw == g.a[1] + g.m[1] - 1;
+  } else {
+    edge = live && (x == 0 || x == nx - 1 || y == 0 || y == ny - 1);
+  }
+  // given: the velocity comes from the velocity planes; gone: not evolved
+  auto given = [&](int z) __attribute__((always_inline)) {
+    if constexpr (LEVEL == 0) {
+      const bool in = z >= g.a[2] + 1 && z <= g.a[2] + g.m[2] - 1, on = z == g.a[2] + 1 || z == g.a[2] + g.m[2] - 1;
+      return live && box && in && (edge || on);
+    } else {
+      return live && (edge || z == 0 || z == nz - 1);
     }
   };
-  // velocity of the loaded plane zp into its LDS slot; its populations into H
-  auto put = [&](int zp, const S (&P)[Q], const S (&UR)[3]) __attribute__((always_inline)) {
-    const bool ring = xyring || zp == 0 || zp == nz - 1;
+  auto gone = [&](int z) __attribute__((always_inline)) {
+    if constexpr (LEVEL == 0) return live && box && z >= g.a[2] + 1 && z <= g.a[2] + g.m[2] - 1;
+    else return live && (edge || z == 0 || z == nz - 1);
+  };
+  // addressing inside a plane: the lane's position and the steps to its
+  // neighbours (periodic on the coarse level)
+  using Wn = Window<S, Q>;
+  const int64_t pz = (int64_t)pitch * ny;
+  const uint32_t q0 = live ? (uint32_t)(xw + xoff + pitch * yw) : 0u;
+  const int dxm = LEVEL == 0 ? wrap(xw - 1, nx) - xw : -1, dxp = LEVEL == 0 ? wrap(xw + 1, nx) - xw : 1;
+  const int dym = LEVEL == 0 ? pitch * (wrap(yw - 1, ny) - yw) : -pitch;
+  const int dyp = LEVEL == 0 ? pitch * (wrap(yw + 1, ny) - yw) : pitch;
+  const uint32_t mlive = live ? 0u : Wn::kOff;
+  const uint32_t minner = inner ? 0u : Wn::kOff;
+  auto zw = [&](int z) __attribute__((always_inline)) {
+    return LEVEL == 0 ? wrap(z, nz) : min(max(z, 0), nz - 1);
+  };
+  S H[Q], P0[Q], P1[Q], U0[3], U1[3];
+  // pulls of plane zq into P; given velocities from the velocity planes into UR
+  auto load = [&](int zq, S (&P)[Q], S (&UR)[3]) __attribute__((always_inline)) {
+    const int z0 = zw(zq);
+    const Wn W0(pz * z0), Wm(pz * zw(zq - 1)), Wp(pz * zw(zq + 1));
+    const __amdgpu_buffer_rsrc_t r0 = W0.rsrc(src), rm = Wm.rsrc(src), rp = Wp.rsrc(src);
+    const uint32_t d0 = q0 + (uint32_t)(pz * z0 - W0.pb0);
+    const uint32_t dm = q0 + (uint32_t)(pz * zw(zq - 1) - Wm.pb0), dp = q0 + (uint32_t)(pz * zw(zq + 1) - Wp.pb0);
+    const uint32_t mk = gone(z0) ? Wn::kOff : mlive;
+    static_for<Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      constexpr int cx = L::cx(i), cy = L::cy(i), cz = L::cz(i);
+      const uint32_t d = (cz == 0 ? d0 : (cz > 0 ? dm : dp)) + (uint32_t)(cx > 0 ? dxm : (cx < 0 ? dxp : 0)) +
+                         (uint32_t)(cy > 0 ? dym : (cy < 0 ? dyp : 0));
+      P[i] = Wn::load(cz == 0 ? r0 : (cz > 0 ? rm : rp), Wn::boff(d) | mk, i);
+    });
+    const uint32_t mo = (uint32_t)sizeof(S) * q0 | (given(z0) ? 0u : Wn::kOff);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(mac + (int64_t)(1 + k) * NP + pz * z0), (short)0, (int)Wn::kOff, 0x00020000);
+      if constexpr (sizeof(S) == 4)
+        UR[k] = __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(ru, (int)mo, 0, 0));
+      else
+        UR[k] = __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(ru, (int)mo, 0, 0));
+    }
+  };
+  // velocity of the loaded plane zq into its LDS slot; its populations into H
+  auto put = [&](int zq, const S (&P)[Q], const S (&UR)[3]) __attribute__((always_inline)) {
     S rho, r0, u[3];
     N::moments(P, rho, r0, u);
     using U = typename std::conditional<sizeof(S) == 4, uint32_t, uint64_t>::type;
-    const U mk = ring ? ~U(0) : U(0);
+    const U mk = gone(zw(zq)) ? ~U(0) : U(0);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       const S v = __builtin_bit_cast(S, (__builtin_bit_cast(U, UR[k]) & mk) | (__builtin_bit_cast(U, u[k]) & ~mk));
-      lu[zp & 3][k][t] = live ? v : S(0);
+      lu[zq & 3][k][t] = live ? v : S(0);
     }
 #pragma unroll
     for (int i = 0; i < Q; ++i) H[i] = P[i];
   };
   // planes zs - 1 (velocities) and zs (velocities and populations), the
   // pulls of planes zs + 1 and zs + 2 out (two planes in flight)
-  load(zs - 1, d0, P0, U0);
+  load(zs - 1, P0, U0);
   put(zs - 1, P0, U0);
-  load(zs, d0 + pz, P0, U0);
+  load(zs, P0, U0);
   put(zs, P0, U0);
-  load(zs + 1, d0 + 2 * pz, P0, U0);
-  {
-    const int zn = zs + 2 <= ze + 1 ? zs + 2 : ze + 1;
-    load(zn, d0 + (uint32_t)(zn - zs + 1) * pz, P1, U1);
-  }
+  load(zs + 1, P0, U0);
+  load(zs + 2 <= ze + 1 ? zs + 2 : ze + 1, P1, U1);
   auto iter = [&](int z, S (&Pu)[Q], S (&Uu)[3]) __attribute__((always_inline)) {
-    const uint32_t dz = d0 + (uint32_t)(z - zs + 1) * pz;  // window position of (x, y, z)
     S Hc[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) Hc[i] = H[i];
     put(z + 1, Pu, Uu);
     // pulls of plane z + 3 (plane ze + 1 again past the run's last plane)
-    const int zn = z + 3 <= ze + 1 ? z + 3 : ze + 1;
-    load(zn, d0 + (uint32_t)(zn - zs + 1) * pz, Pu, Uu);
+    load(z + 3 <= ze + 1 ? z + 3 : ze + 1, Pu, Uu);
     __syncthreads();
     if (inner) {
       const int sm = (z - 1) & 3, s0 = z & 3, sp = (z + 1) & 3;
@@ -1942,153 +2002,15 @@ __global__ __launch_bounds__(TXH * TYH, MINW) void k_hrr3s(const S* __restrict__
       Sr.yz = S(0.5) * (gr[1][2] + gr[2][1]);
       N::collide(Hc, M_HRR, om, tau, sig, &Sr);
     }
-    const uint32_t bo = Wn::boff(dz) | minner;
+    const Wn W(pz * z);
+    const __amdgpu_buffer_rsrc_t rd = W.rsrc(dst);
+    const uint32_t bo = Wn::boff(q0 + (uint32_t)(pz * z - W.pb0)) | (gone(z) ? Wn::kOff : minner);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) Wn::template store<NT>(rd, bo, i, Hc[i]);
+    for (int i = 0; i < Q; ++i) Wn::template store<false>(rd, bo, i, Hc[i]);
   };
   for (int z = zs; z <= ze; z += 2) {
     iter(z, P0, U0);
     if (z + 1 <= ze) iter(z + 1, P1, U1);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// One H-RR fine substep in one pass (D3Q19, k_hrr3): a work group owns TXV
-// vectors x TY rows of a run of zlen planes and walks it along z, one lane per
-// vector of the tile and its x/y halo.  The iteration for plane z pulls plane
-// z+1 into registers and writes its velocities into one of three LDS plane
-// slots (ring nodes: from the velocity planes, where the ring macro step
-// stored them); after the barrier the inner lanes take the strain rate of
-// plane z from the three slots and collide the populations they pulled one
-// iteration earlier.  Same arithmetic as the velocity pass followed by
-// k_collide_hrr.
-template <int LAT, bool DEV, typename S>
-__device__ __forceinline__ void hrr3_pull(const S* __restrict__ src, const S* __restrict__ mac, const Geo& g, int k,
-                                          int y, int z, int nv, typename VT<S, VecOf<S>::V>::a* P,
-                                          typename VT<S, VecOf<S>::V>::a* u) {
-  using L = Lattice<LAT>;
-  using N = Node<LAT, DEV, S>;
-  constexpr int V = VecOf<S>::V, Q = L::Q;
-  const int nx = g.nf[0], ny = g.nf[1], nz = g.nf[2];
-  const int64_t NP = g.Nfp;
-  const int x0 = 1 + V * k;
-  if (y == 0 || y == ny - 1 || z == 0 || z == nz - 1 || k == -1) {
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      const int x = x0 + j;
-      const bool in = x >= 0 && x <= nx - 1;
-      const int64_t p = fpos(g, in ? x : 0, y, z);
-#pragma unroll
-      for (int d = 0; d < 3; ++d) u[d][j] = in ? mac[(int64_t)(1 + d) * NP + p] : S(0);
-    }
-    return;
-  }
-  const Pull<S, Q, V, 1, 3> pl(g.pf, g.fxo, x0, y, z, nx, ny, nz);
-  pl.template load_all<L>(src, P);
-#pragma unroll
-  for (int j = 0; j < V; ++j) {
-    S f[Q], rho, r0, uu[3];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) f[i] = P[i][j];
-    N::moments(f, rho, r0, uu);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) u[d][j] = uu[d];
-  }
-  if (k == nv - 1) {
-    const int jr = nx - 1 - x0;
-    const int64_t p = fpos(g, nx - 1, y, z);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const S r = mac[(int64_t)(1 + d) * NP + p];
-#pragma unroll
-      for (int j = 0; j < V; ++j)
-        if (j == jr) u[d][j] = r;
-    }
-  }
-}
-
-template <int LAT, bool DEV, typename S, bool NT, int TXV, int TY, int MINW>
-__global__ __launch_bounds__(256, MINW) void k_hrr3(const S* __restrict__ src, S* __restrict__ dst,
-                                                    const S* __restrict__ mac, const Geo g, const S om, const S tau,
-                                                    const S sig, int ntx, int nty, int nzc, int zlen, int per_xcd) {
-  using L = Lattice<LAT>;
-  using N = Node<LAT, DEV, S>;
-  constexpr int V = VecOf<S>::V, Q = L::Q;
-  using VA = typename VT<S, V>::a;
-  constexpr int HX = TXV + 2, HY = TY + 2, RW = HX * V;
-  static_assert(L::D == 3, "the marching one-pass H-RR kernel is three-dimensional");
-  static_assert(HX * HY <= 256, "one lane per tile-and-halo vector");
-  __shared__ S lu[3][3][HY][RW];  // [plane slot][component][row][node]
-  const int b = blockIdx.x;
-  const int item = (b % kXCD) * per_xcd + b / kXCD;
-  const int ntile = ntx * nty;
-  if (item >= ntile * nzc) return;  // whole work group, before any barrier
-  const int zc = item / ntile, tile = item - zc * ntile;
-  const int tx = tile % ntx, ty = tile / ntx;
-  const int ny = g.nf[1], nz = g.nf[2];
-  const int nv = (g.nf[0] - 1 + V - 1) / V;
-  const int t = threadIdx.x;
-  const int hv = t % HX, hr = t / HX;
-  const int k = tx * TXV - 1 + hv, y = ty * TY + hr;
-  const bool lane = t < HX * HY;
-  const bool live = lane && y <= ny - 1 && k <= nv - 1;
-  const bool inner = live && hv >= 1 && hv <= TXV && hr >= 1 && hr <= TY && y <= ny - 2;
-  const int zs = 1 + zc * zlen, ze = min(zs + zlen - 1, nz - 2);
-  const VA zero = VA(S(0));
-  VA T[Q], P[Q], u[3];
-#pragma unroll
-  for (int i = 0; i < Q; ++i) T[i] = P[i] = zero;
-  auto put = [&](int zp) {
-    const int sl = zp % 3;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) *(VA*)&lu[sl][d][hr][hv * V] = u[d];
-  };
-  // planes zs - 1 (velocities) and zs (velocities and populations)
-  if (live) {
-    hrr3_pull<LAT, DEV, S>(src, mac, g, k, y, zs - 1, nv, P, u);
-    put(zs - 1);
-    hrr3_pull<LAT, DEV, S>(src, mac, g, k, y, zs, nv, T, u);
-    put(zs);
-  }
-  for (int z = zs; z <= ze; ++z) {
-    if (live) {
-      hrr3_pull<LAT, DEV, S>(src, mac, g, k, y, z + 1, nv, P, u);
-      put(z + 1);
-    }
-    __syncthreads();
-    if (inner) {
-      const int sm = (z + 2) % 3, s0 = z % 3, sp = (z + 1) % 3;
-      const int c = hv * V;
-#pragma unroll
-      for (int j = 0; j < V; ++j) {
-        S gr[3][3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          gr[0][d] = (lu[s0][d][hr][c + j + 1] - lu[s0][d][hr][c + j - 1]) * S(0.5);
-          gr[1][d] = (lu[s0][d][hr + 1][c + j] - lu[s0][d][hr - 1][c + j]) * S(0.5);
-          gr[2][d] = (lu[sp][d][hr][c + j] - lu[sm][d][hr][c + j]) * S(0.5);
-        }
-        Sym<S> Sr;
-        Sr.xx = gr[0][0];
-        Sr.yy = gr[1][1];
-        Sr.xy = S(0.5) * (gr[0][1] + gr[1][0]);
-        Sr.zz = gr[2][2];
-        Sr.xz = S(0.5) * (gr[0][2] + gr[2][0]);
-        Sr.yz = S(0.5) * (gr[1][2] + gr[2][1]);
-        S f[Q];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) f[i] = T[i][j];
-        N::collide(f, M_HRR, om, tau, sig, &Sr);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) T[i][j] = f[i];
-      }
-      const int64_t own = fpos(g, 1 + V * k, y, z);
-#pragma unroll
-      for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), T[i]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < Q; ++i) T[i] = P[i];
   }
 }
 

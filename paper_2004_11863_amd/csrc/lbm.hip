@@ -265,7 +265,7 @@ struct Grid final : GridBase {
   bool fused = false;
   int n_cu = 0;
   int f3_slots[kNVar] = {0, 0, 0, 0};  // resident k_fine3s work groups per device, per variant
-  int h3_slots[kNVar] = {0, 0, 0, 0};  // the same for k_hrr3 / k_hrr3s
+  int h3_slots[4] = {0, 0, 0, 0};      // the same for k_hrr3s, 2 * level + (variant & 1)
   int hs[3] = {0, 1, 2};
   Iface itf{};
   double tau_c = 0, tau_f = 0, sig = 0;
@@ -539,25 +539,20 @@ struct Grid final : GridBase {
                            (S)(1.0 - 1.0 / tau_f), ntx, nty, per, (double*)nullptr);
     }
   }
-  // Work decomposition of a marching fine kernel (k_hrr3) with TXV x TY
-  // tiles of vectors, for `slots` resident work groups on the device: a run
-  // of zlen planes costs zlen + 2 planes of work (its first step needs two
+  // Work decomposition of a marching kernel over ntx x nty tiles of columns
+  // of nzm planes, for `slots` resident work groups on the device: a run of
+  // zlen planes costs zlen + 2 planes of work (its first step needs two
   // more), and runs are at least kMinZRun planes long so that this overhead
   // stays small, while the work groups fill the device in few rounds.
+  // zcap: longest run allowed (k_fine3s addresses its run's storage window
+  // with 32-bit byte offsets).
   struct ZRuns {
     int ntx, nty, nzc, zlen, per;
   };
-  ZRuns zruns(int TXV, int TY, int slots) const {
-    const int nv = (g.nf[0] - 1 + V - 1) / V;
-    return zruns_tiles((nv + TXV - 1) / TXV, (g.nf[1] - 2 + TY - 1) / TY, slots);
-  }
-  // zcap: longest run allowed (runs of the one-node-per-lane kernels address
-  // their storage window with 32-bit byte offsets).
-  ZRuns zruns_tiles(int ntx, int nty, int slots, int zcap = 1 << 30) const {
+  ZRuns zruns_tiles(int ntx, int nty, int nzm, int slots, int zcap = 1 << 30) const {
     ZRuns r;
     r.ntx = ntx;
     r.nty = nty;
-    const int nzm = g.nf[2] - 2;
     const int64_t ntile = (int64_t)r.ntx * r.nty;
     r.zlen = std::min(nzm, zcap);
     double best = -1.0;
@@ -589,69 +584,66 @@ struct Grid final : GridBase {
   }
   // Both fine substeps in one marching kernel with one node per lane
   // (k_fine3s): tiles of (TXH - 2) x (TYH - 2) middle nodes.  The tile
-  // counts come from nodes, not vectors; the runs are cut as for k_hrr3.
-  // Longest run of a one-node-per-lane marching kernel: its storage window
-  // (zlen + 4 planes and one storage block) stays below 2^32 bytes.
+  // counts come from nodes, not vectors.  Longest run: its storage window
+  // (zlen + 4 planes and one storage block) stays below 2^31 bytes.
   int window_zcap() const {
     const double plane = (double)g.pf * g.nf[1] * Q * sizeof(S);
     const double room = 2147483648.0 - 2.0 * (double)PopBlock<S>::B * Q * sizeof(S);
     return std::max(0, (int)std::floor(room / plane) - 4);
   }
-  template <int MODEL, int TXH, int TYH, int MINW>
+  template <int MODEL, int TXH, int TYH>
   void go_fine3s(const S* src, S* dst, S* half, hipStream_t s, int v) {
     if constexpr (D == 3 && MODEL != M_HRR) {
-      auto kern = k_fine3s<LAT, DEV, S, MODEL, NT, TXH, TYH, MINW>;
+      auto kern = k_fine3s<LAT, DEV, S, MODEL, TXH, TYH>;
       const int ntx = (g.nf[0] - 2 + TXH - 3) / (TXH - 2), nty = (g.nf[1] - 2 + TYH - 3) / (TYH - 2);
       const int zcap = window_zcap();
       if (zcap < 1) throw LbmError(LBM_EUNSUPPORTED, "fine planes too large for the one-pass fused kernel");
       // the compact x-band copy is addressed with 32-bit byte offsets too
       if ((double)xband_elems(g, Q) * sizeof(S) >= 2147483648.0)
         throw LbmError(LBM_EUNSUPPORTED, "fine x-bands too large for the one-pass fused kernel");
-      const ZRuns r = zruns_tiles(ntx, nty, occupancy_slots(kern, f3_slots[v], TXH * TYH), zcap);
+      const ZRuns r = zruns_tiles(ntx, nty, g.nf[2] - 2, occupancy_slots(kern, f3_slots[v], TXH * TYH), zcap);
       hipLaunchKernelGGL(kern, dim3((unsigned)(r.per * kXCD)), dim3(TXH * TYH), 0, s, src, dst, half, xbuf.as<S>(),
                          g, (S)(1.0 - 1.0 / tau_f), r.ntx, r.nty, r.nzc, r.zlen, r.per);
     }
   }
-  // One H-RR fine substep in one pass (D3Q19): fine H-RR role variant 2 is
-  // k_hrr3 (30 x 6 tiles of vectors), variant 3 k_hrr3s (one node per lane,
-  // 64 x 8 lanes in FP32, 34 x 8 in FP64); variants 0 and 1 run the velocity
-  // pass and k_collide_hrr (capped at 2 / 3 resident work groups).  On the
-  // 385^3 patch in FP32, per substep: k_hrr3 2.78 ms, k_hrr3s 2.91 ms, the
-  // two-pass form 1.0 + 1.78 ms; the one-pass kernels save the velocity
-  // pass's traffic but re-read their tile halos from HBM.
-  bool hrr_one_pass3() const { return D == 3 && desc.collision == LBM_HRR && var[3] >= 2 && !dyn_on; }
-  int hrr_lds_var(int v) const { return (D == 3 && desc.collision == LBM_HRR) ? (v == 0 ? 2 : 1) : v; }
-  template <int TXV, int TY>
-  void go_hrr3(const S* src, S* dst, const S* mac, hipStream_t s, int v) {
-    if constexpr (D == 3) {
-      auto kern = k_hrr3<LAT, DEV, S, NT, TXV, TY, 2>;
-      const ZRuns r = zruns(TXV, TY, occupancy_slots(kern, h3_slots[v]));
-      hipLaunchKernelGGL(kern, dim3((unsigned)(r.per * kXCD)), dim3(256), 0, s, src, dst, mac, g,
-                         (S)(1.0 - 1.0 / tau_f), (S)tau_f, (S)sig, r.ntx, r.nty, r.nzc, r.zlen, r.per);
-    }
+  // One H-RR step of a level in one pass (D3Q19, k_hrr3s): H-RR role variants
+  // 2 and 3 are its tiles (130 x 7 and 66 x 15 lanes in FP32, 66 x 7 and
+  // 34 x 15 in FP64, whose columns need twice the registers); variants 0 and
+  // 1 run the velocity pass and k_collide_hrr (capped at 2 / 3 resident work
+  // groups).  257^3 fine level: FP32 612 / 616 us per substep against 304 +
+  // 533 us in two passes, FP64 1143 / 1171 against 560 + 968 us.  Taken only
+  // where a plane stays below 2^31 bytes (32-bit offsets inside a plane).
+  bool hrr3_fits(int level) const {
+    const double plane = level == 0 ? (double)g.pc * g.n[1] : (double)g.pf * g.nf[1];
+    return (plane + 2.0 * (double)PopBlock<S>::B) * Q * sizeof(S) < 2147483648.0;
   }
-  template <int TXH, int TYH>
+  bool hrr_one_pass3() const {
+    return D == 3 && desc.collision == LBM_HRR && var[3] >= 2 && !dyn_on && hrr3_fits(1);
+  }
+  int hrr_lds_var(int v) const { return (D == 3 && desc.collision == LBM_HRR) ? (v == 0 ? 2 : 1) : v; }
+  template <int LEVEL, int TXH, int TYH>
   void go_hrr3s(const S* src, S* dst, const S* mac, hipStream_t s, int v) {
     if constexpr (D == 3) {
-      auto kern = k_hrr3s<LAT, DEV, S, NT, TXH, TYH, 1>;
-      const int ntx = (g.nf[0] - 2 + TXH - 3) / (TXH - 2), nty = (g.nf[1] - 2 + TYH - 3) / (TYH - 2);
-      const int zcap = window_zcap();
-      // the velocity planes are read through a window of 2^31 bytes as well
-      if (zcap < 1 || (double)(1 + D) * g.Nfp * sizeof(S) >= 2147483648.0)
-        throw LbmError(LBM_EUNSUPPORTED, "fine level too large for the one-pass H-RR kernel");
-      const ZRuns r = zruns_tiles(ntx, nty, occupancy_slots(kern, h3_slots[v], TXH * TYH), zcap);
+      auto kern = k_hrr3s<LAT, DEV, S, LEVEL, TXH, TYH>;
+      // coarse: every node; fine: the middle nodes
+      const int ex = LEVEL == 0 ? g.n[0] : g.nf[0] - 2, ey = LEVEL == 0 ? g.n[1] : g.nf[1] - 2;
+      const int ez = LEVEL == 0 ? g.n[2] : g.nf[2] - 2;
+      const ZRuns r = zruns_tiles((ex + TXH - 3) / (TXH - 2), (ey + TYH - 3) / (TYH - 2), ez,
+                                  occupancy_slots(kern, h3_slots[2 * LEVEL + (v & 1)], TXH * TYH));
+      const double tau = LEVEL == 0 ? tau_c : tau_f;
       hipLaunchKernelGGL(kern, dim3((unsigned)(r.per * kXCD)), dim3(TXH * TYH), 0, s, src, dst, mac, g,
-                         (S)(1.0 - 1.0 / tau_f), (S)tau_f, (S)sig, r.ntx, r.nty, r.nzc, r.zlen, r.per);
+                         (S)(1.0 - 1.0 / tau), (S)tau, (S)sig, r.ntx, r.nty, r.nzc, r.zlen, r.per);
     }
   }
+  template <int LEVEL>
   void launch_hrr3(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1) {
-    if (v < 0) v = var[3];
+    if (v < 0) v = var[2 + LEVEL];
     if constexpr (sizeof(S) == 4) {
-      if (v == 2) go_hrr3<30, 6>(src, dst, mac, s, 2);
-      else go_hrr3s<64, 8>(src, dst, mac, s, 3);
+      if (v == 2) go_hrr3s<LEVEL, 130, 7>(src, dst, mac, s, v);
+      else go_hrr3s<LEVEL, 66, 15>(src, dst, mac, s, v);
     } else {
-      if (v == 2) go_hrr3<30, 6>(src, dst, mac, s, 2);
-      else go_hrr3s<34, 8>(src, dst, mac, s, 3);
+      if (v == 2) go_hrr3s<LEVEL, 66, 7>(src, dst, mac, s, v);
+      else go_hrr3s<LEVEL, 34, 15>(src, dst, mac, s, v);
     }
   }
   template <int MODEL>
@@ -665,11 +657,11 @@ struct Grid final : GridBase {
         default: go_fine2<MODEL, 32, 8>(src, dst, half, s, su); break;
       }
     } else if constexpr (sizeof(S) == 4) {
-      if (v == 2) go_fine3s<MODEL, 64, 16, 1>(src, dst, half, s, 2);
-      else go_fine3s<MODEL, 64, 8, 1>(src, dst, half, s, 3);
+      if (v == 2) go_fine3s<MODEL, 130, 7>(src, dst, half, s, 2);
+      else go_fine3s<MODEL, 66, 15>(src, dst, half, s, 3);
     } else {
-      if (v == 2) go_fine3s<MODEL, 34, 14, 1>(src, dst, half, s, 2);
-      else go_fine3s<MODEL, 34, 8, 1>(src, dst, half, s, 3);
+      if (v == 2) go_fine3s<MODEL, 34, 15>(src, dst, half, s, 2);
+      else go_fine3s<MODEL, 66, 7>(src, dst, half, s, 3);
     }
   }
 
@@ -736,7 +728,8 @@ struct Grid final : GridBase {
     } else if (D == 2) {
       launch_hrr2(fineA(), fineB(), mac_f.as<S>(), s, v);
     } else if (v >= 2) {
-      launch_hrr3(fineA(), fineB(), mac_f.as<S>(), s, v);
+      if (!hrr3_fits(1)) throw LbmError(LBM_EUNSUPPORTED, "plane too large for the one-pass H-RR kernel");
+      launch_hrr3<1>(fineA(), fineB(), mac_f.as<S>(), s, v);
     } else {
       // the two passes the one-pass variants replace
       launch_stream<M_HRR, 1>(fineA(), fineB(), mac_f.as<S>(), tau_f, s);
@@ -866,7 +859,7 @@ struct Grid final : GridBase {
         timed(s, [&] { launch_hrr2(fA, fB, mf, s, -1, true); });
       } else if (hrr_one_pass3()) {
         hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
-        timed(s, [&] { launch_hrr3(fA, fB, mf, s); });
+        timed(s, [&] { launch_hrr3<1>(fA, fB, mf, s); });
       } else {
         launch_stream<M_HRR, 1>(fA, fB, mf, tau_f, s);
         hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
@@ -894,7 +887,7 @@ struct Grid final : GridBase {
       if (fine_one_pass2()) {
         timed(s, [&] { launch_hrr2(fB, fA, mf, s, -1, true); });
       } else if (hrr_one_pass3()) {
-        timed(s, [&] { launch_hrr3(fB, fA, mf, s); });
+        timed(s, [&] { launch_hrr3<1>(fB, fA, mf, s); });
       } else {
         launch_stream<M_HRR, 1>(fB, fA, mf, tau_f, s);
         hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, s, Hm, H0, Hp, 0.0, 0.0, 1.0, mf, g, itf);
