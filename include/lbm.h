@@ -272,8 +272,8 @@ int lbm_kernel_time(lbm_handle h, int64_t* launches, double* mean_ms, int64_t* n
  * FP64).  For the H-RR roles of a D2Q9 grid, whose kernels run a coarse
  * step or a fine substep in one pass (velocities of the tile in LDS), the
  * variants are tiles of 64 x 8, 32 x 8, 32 x 16 and 128 x 4 lanes; for the
- * fine H-RR role of a D3Q19 grid, variants 0 and 1 run the velocity pass and
- * the collision (capped at 2 and 3 resident work groups per CU), 2 and 3 one
+ * H-RR roles of a D3Q19 grid, variants 0 and 1 run the velocity pass and the
+ * collision (capped at 2 and 3 resident work groups per CU), 2 and 3 one
  * pass walking tiles of columns along z (130 x 7 and 66 x 15 lanes in FP32,
  * 66 x 7 and 34 x 15 in FP64).  Every variant computes
  * bitwise the same result. */

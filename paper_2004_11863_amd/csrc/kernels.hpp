@@ -638,22 +638,27 @@ __global__ void k_hist_capture(const S* __restrict__ src, double* __restrict__ H
 // coarse state, computed here exactly as the velocity pass would (TN nodes:
 // the planes, where the fictitious propagation stored them).
 template <int LAT, bool DEV, typename T, bool PULL>
-__device__ __forceinline__ T hist_u(const T* __restrict__ src, const T* __restrict__ mac_c, const Geo& g, int x, int y,
-                                    int z, int b) {
+__device__ __forceinline__ void hist_u(const T* __restrict__ src, const T* __restrict__ mac_c, const Geo& g, int x, int y,
+                                       int z, T* u) {
   using L = Lattice<LAT>;
   using N = Node<LAT, DEV, T>;
   constexpr int Q = L::Q;
   const int64_t ip = cpos(g, x, y, z);
-  if (!PULL || coarse_class(g, x, y, z) == CC_TN) return mac_c[(1 + b) * g.Ncp + ip];
-  T f[Q], rho, r0, u[3];
+  if (!PULL || coarse_class(g, x, y, z) == CC_TN) {
+#pragma unroll
+    for (int b = 0; b < L::D; ++b) u[b] = mac_c[(1 + b) * g.Ncp + ip];
+    return;
+  }
+  T f[Q], rho, r0, v[3];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const int xs = wrap(x - L::cx(i), g.n[0]), ys = wrap(y - L::cy(i), g.n[1]);
     const int zs = L::D == 3 ? wrap(z - L::cz(i), g.n[2]) : 0;
     f[i] = src[pop_at<T, Q>(cpos(g, xs, ys, zs), i)];
   }
-  N::moments(f, rho, r0, u);
-  return u[b];
+  N::moments(f, rho, r0, v);
+#pragma unroll
+  for (int b = 0; b < L::D; ++b) u[b] = v[b];
 }
 template <int LAT, bool DEV, typename T, bool PULL>
 __device__ __forceinline__ void hist_strain_body(const T* __restrict__ src, const T* __restrict__ mac_c,
@@ -664,15 +669,15 @@ __device__ __forceinline__ void hist_strain_body(const T* __restrict__ src, cons
   if (h >= itf.NH) return;
   int x, y, z;
   cdecode(g, itf.hnode[h], x, y, z);
-  const int n3[3] = {g.n[0], g.n[1], g.n[2]};
   double gr[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll
   for (int a = 0; a < D; ++a) {
-    int cp[3] = {x, y, z}, cm[3] = {x, y, z};
-    cp[a] = wrap(cp[a] + 1, n3[a]);
-    cm[a] = wrap(cm[a] - 1, n3[a]);
-    for (int b = 0; b < D; ++b)
-      gr[a][b] = 0.5 * ((double)hist_u<LAT, DEV, T, PULL>(src, mac_c, g, cp[0], cp[1], cp[2], b) -
-                        (double)hist_u<LAT, DEV, T, PULL>(src, mac_c, g, cm[0], cm[1], cm[2], b));
+    T up[D], um[D];
+    const int ex = a == 0, ey = a == 1, ez = a == 2;
+    hist_u<LAT, DEV, T, PULL>(src, mac_c, g, wrap(x + ex, g.n[0]), wrap(y + ey, g.n[1]), wrap(z + ez, g.n[2]), up);
+    hist_u<LAT, DEV, T, PULL>(src, mac_c, g, wrap(x - ex, g.n[0]), wrap(y - ey, g.n[1]), wrap(z - ez, g.n[2]), um);
+#pragma unroll
+    for (int b = 0; b < D; ++b) gr[a][b] = 0.5 * ((double)up[b] - (double)um[b]);
   }
   const Sym<double> S{gr[0][0], gr[1][1], gr[2][2], 0.5 * (gr[0][1] + gr[1][0]), 0.5 * (gr[0][2] + gr[2][0]),
                       0.5 * (gr[1][2] + gr[2][1])};

@@ -311,8 +311,17 @@ struct Grid final : GridBase {
   void init() override {
     fused = desc.collision != LBM_HRR && g.has_fine && !child;
     HIPCHK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
-    if (fused) var[1] = 0;
-    if (D == 3 && desc.collision == LBM_HRR) var[3] = 0;
+    // D3Q19: the one-pass kernels by default in large levels (one work group
+    // a CU needs some planes of tiles to fill the device).  Fine, from 100 MB a
+    // level pair: 65^3 FP32 RR two launches 62 us a step, one 82, H-RR 122 and
+    // 137; 97^3 133 and 122, 229 and 195; 129^3 259 and 238, 444 and 422.  Coarse
+    // H-RR, from 2 GB: 200^3 FP32 1437 us a step in two passes, 1483 in one;
+    // 256^3 2481 and 2440; 384^3 7634 and 7320.  lbm_tune times them all.
+    if (fused) var[1] = D == 2 || level_bytes(1) < 1e8 ? 0 : (DEV && g.nf[0] <= 256 ? 3 : 2);
+    if (D == 3 && desc.collision == LBM_HRR) {
+      var[2] = level_bytes(0) < 2e9 ? 0 : 2;
+      var[3] = level_bytes(1) < 1e8 ? 0 : 2;
+    }
     timed_factor = fused_now() ? 2 : 1;
     // every state buffer starts at zero: the state is zero until
     // lbm_set_state, and values no step writes (the populations of covered
@@ -376,6 +385,10 @@ struct Grid final : GridBase {
     if (mac_f.p) HIPCHK(hipMemset(mac_f.p, 0, mac_f.bytes));
   }
 
+  // Bytes of a level's two population buffers.
+  double level_bytes(int level) const {
+    return level == 1 && !g.has_fine ? 0.0 : 2.0 * (double)pop_bytes(level == 0 ? g.Ncp : g.Nfp);
+  }
   static unsigned blocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
   // Grid of an interface-node kernel (xcd_block): a multiple of the XCD count.
   static unsigned xblocks(int64_t n, int bs) { return (blocks(n, bs) + kXCD - 1) / kXCD * kXCD; }
@@ -461,7 +474,7 @@ struct Grid final : GridBase {
   }
   // The coarse level in one pass (D2Q9 H-RR, rows a whole number of vectors:
   // coarse_one_pass()); same tile variants, role 2.
-  bool coarse_one_pass() const {
+  bool coarse_one_pass2() const {
     return D == 2 && desc.collision == LBM_HRR && g.n[0] % V == 0 && !nested_child;
   }
   // D2Q9 H-RR fine substeps in one pass (k_hrr2)
@@ -617,6 +630,12 @@ struct Grid final : GridBase {
     const double plane = level == 0 ? (double)g.pc * g.n[1] : (double)g.pf * g.nf[1];
     return (plane + 2.0 * (double)PopBlock<S>::B) * Q * sizeof(S) < 2147483648.0;
   }
+  // (a nested child's coarse level takes its ring's velocities from the
+  // planes of the velocity pass: two passes)
+  bool coarse_one_pass() const {
+    return coarse_one_pass2() || (D == 3 && desc.collision == LBM_HRR && var[2] >= 2 && !dyn_on && !nested_child &&
+                                  hrr3_fits(0));
+  }
   bool hrr_one_pass3() const {
     return D == 3 && desc.collision == LBM_HRR && var[3] >= 2 && !dyn_on && hrr3_fits(1);
   }
@@ -645,6 +664,13 @@ struct Grid final : GridBase {
       if (v == 2) go_hrr3s<LEVEL, 66, 7>(src, dst, mac, s, v);
       else go_hrr3s<LEVEL, 34, 15>(src, dst, mac, s, v);
     }
+  }
+  // The coarse H-RR step: in one pass, or the collision after the velocity
+  // pass (which the caller launched).
+  void launch_coarse_hrr(const S* src, S* dst, const S* mac, hipStream_t s) {
+    if (coarse_one_pass2()) launch_hrr2c(src, dst, mac, s, -1, true);
+    else if (coarse_one_pass()) launch_hrr3<0>(src, dst, mac, s);
+    else launch_collide_hrr<0>(src, dst, mac, tau_c, s, hrr_lds_var(var[2]), true);
   }
   template <int MODEL>
   void launch_fused(const S* src, S* dst, S* half, hipStream_t s, int v = -1, double* su = nullptr) {
@@ -721,10 +747,15 @@ struct Grid final : GridBase {
       if (model == M_BGK) launch_stream<M_BGK, 1>(fineA(), fineB(), nullptr, tau_f, s, v);
       else if (model == M_RR) launch_stream<M_RR, 1>(fineA(), fineB(), nullptr, tau_f, s, v);
       else launch_stream<M_HRR, 1>(fineA(), fineB(), mac_f.as<S>(), tau_f, s, v);
-    } else if (role == 2 && coarse_one_pass()) {
+    } else if (role == 2 && coarse_one_pass2()) {
       launch_hrr2c(c_cur, c_oth, mac_c.as<S>(), s, v);
+    } else if (role == 2 && D == 3 && v >= 2) {
+      if (!hrr3_fits(0)) throw LbmError(LBM_EUNSUPPORTED, "plane too large for the one-pass H-RR kernel");
+      launch_hrr3<0>(c_cur, c_oth, mac_c.as<S>(), s, v);
     } else if (role == 2) {
-      launch_collide_hrr<0>(c_cur, c_oth, mac_c.as<S>(), tau_c, s, v);
+      // (D3Q19: the two passes the one-pass variants replace)
+      if (D == 3) launch_stream<M_HRR, 0>(c_cur, c_oth, mac_c.as<S>(), tau_c, s);
+      launch_collide_hrr<0>(c_cur, c_oth, mac_c.as<S>(), tau_c, s, hrr_lds_var(v));
     } else if (D == 2) {
       launch_hrr2(fineA(), fineB(), mac_f.as<S>(), s, v);
     } else if (v >= 2) {
@@ -757,7 +788,7 @@ struct Grid final : GridBase {
       const bool hrr_role = role >= 2;
       if (!used || (hrr_role && desc.collision != LBM_HRR)) continue;
       if (role == 1 && D == 2 && desc.collision == LBM_HRR) continue;  // no fine velocity pass (k_hrr2)
-      if (role == 0 && coarse_one_pass()) continue;                    // no coarse velocity pass (k_hrr2c)
+      if (role == 0 && coarse_one_pass2()) continue;                   // no coarse velocity pass (k_hrr2c)
 
       float best = -1.f;
       for (int v = 0; v < NVAR; ++v) {
@@ -792,8 +823,8 @@ struct Grid final : GridBase {
     if (model == M_BGK) launch_stream<M_BGK, 0>(src, dst, nullptr, tau_c, s);
     else if (model == M_RR) launch_stream<M_RR, 0>(src, dst, nullptr, tau_c, s);
     else {
-      launch_stream<M_HRR, 0>(src, dst, mac_c.as<S>(), tau_c, s);
-      launch_collide_hrr<0>(src, dst, mac_c.as<S>(), tau_c, s, -1, true);
+      if (!coarse_one_pass()) launch_stream<M_HRR, 0>(src, dst, mac_c.as<S>(), tau_c, s);
+      launch_coarse_hrr(src, dst, mac_c.as<S>(), s);
     }
     cpar ^= 1;
   }
@@ -896,8 +927,7 @@ struct Grid final : GridBase {
       // coarse collision before the TN transfer: the vector kernel also
       // passes over TN nodes, which the transfer then overwrites; the t+1
       // ring (into fine A, independent of both) shares the transfer's launch
-      if (one_c) launch_hrr2c(csrc, cdst, mc, s, -1, true);
-      else launch_collide_hrr<0>(csrc, cdst, mc, tau_c, s, -1, true);
+      launch_coarse_hrr(csrc, cdst, mc, s);
       hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, M_HRR>), dim3(br2 + bc), dim3(256), 0, s, Hp, fA, fB, cdst, g,
                          itf, kf, omf, tau_f, kc, omc, tau_c, sig, (int)br2, (const S*)nullptr, (double*)nullptr);
     }
@@ -996,8 +1026,7 @@ struct Grid final : GridBase {
     };
     child->step(1, s);
     child->coarse_vel_hook = nullptr;
-    if (one_c) launch_hrr2c(csrc, cdst, mc, s);
-    else launch_collide_hrr<0>(csrc, cdst, mc, tau_c, s, -1, true);
+    launch_coarse_hrr(csrc, cdst, mc, s);
     hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, M_HRR>), dim3(br2 + bc), dim3(256), 0, s, Hp, fA, fB, cdst, g,
                        itf, kf, omf, tau_f, kc, omc, tau_c, sig, (int)br2, (const S*)nullptr, (double*)nullptr);
     HIPCHK(hipGetLastError());

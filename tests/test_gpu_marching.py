@@ -50,3 +50,18 @@ def test_fine_tile_edges(m, prec):
         for v in (2, 3):
             var[role] = v
             _same(_run(wl, model, p, var), ref, (model, v))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx", [12, 33, 64, 65, 128, 129])
+def test_coarse_one_pass_tile_edges(nx, prec):
+    """The coarse H-RR step in one marching pass (periodic in every axis, TN
+    nodes from the velocity planes, covered nodes skipped) against the velocity
+    pass and collision, with a patch and on a uniform grid."""
+    from paper_2004_11863_amd import lbm
+    p = lbm.LBM_FP32_DEV if prec == "fp32" else lbm.LBM_FP64
+    for lo, hi in (((3, 5, 2), (nx - 4, 14, 15)), ((0, 0, 0), (0, 0, 0))):
+        wl = _workload((nx, 19, 18), lo, hi)
+        ref = _run(wl, "HRR", p, [0, 0, 0, 0], steps=4)
+        for v in (2, 3):
+            _same(_run(wl, "HRR", p, [0, 0, v, 0], steps=4), ref, (lo, v))
