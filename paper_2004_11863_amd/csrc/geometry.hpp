@@ -22,7 +22,8 @@ enum CoarseClass : int { CC_MIDDLE = 0, CC_TF = 1, CC_TN = 2, CC_COVERED = 3 };
 enum FineClass : int { FC_MIDDLE = 0, FC_TF = 1, FC_IE = 2, FC_IEFACE = 3, FC_TN = 4 };
 
 // Device arrays use a padded row pitch (pc, pf: nodes per row rounded up to
-// a multiple of 4) so every row starts 16-byte aligned; Ncp, Nfp are the
+// a multiple of 4, or in large three-dimensional fine levels to whole
+// 128-byte lines, fine_pitch in lbm.hip) so every row starts aligned; Ncp, Nfp are the
 // padded node counts of a level (the positions of pop_at below, and the plane
 // size of the velocity planes).  Nc, Nf count logical nodes (the x-fastest
 // order of the C ABI and of the interface tables).  (A power-of-two fine
@@ -38,7 +39,7 @@ struct Geo {
   int64_t Nc, Nf;
   int pc, pf;        // row pitch of coarse / fine device arrays
   int fxo;           // offset of fine node x = 0 inside its row: the first
-                     // middle node (x = 1) starts a 16-byte boundary
+                     // middle node (x = 1) starts a 16-byte (or line) boundary
   int64_t Ncp, Nfp;  // padded plane sizes
 };
 

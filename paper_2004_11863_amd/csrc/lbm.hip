@@ -1365,6 +1365,37 @@ static GridBase* make_grid(const lbm_grid_desc& d) {
   return nullptr;
 }
 
+// Row pitch of a fine level of nf[3] nodes (of sb bytes) and the offset of
+// x = 0 in a row, so that the first middle node, x = 1, starts a 16-byte
+// vector or (below) a whole 128-byte line.
+//
+// Whole lines: the bulk kernels store rows from x = 1 on and leave a gap of
+// some nodes before the next row, so with 16-byte rows the first and the last
+// line of a row are written in part; in a level that does not fit the 256 MB
+// memory-side cache those reach HBM as partial lines.  385^3, FP32 RR:
+// k_stream 1675 -> 1492 us, k_fine3s 2590 -> 2344 us; 257^3, FP64: 1016 -> 893
+// and 1621 -> 1362 us.  Two-dimensional levels gain nothing (long rows:
+// 4097 x 2049 nodes, k_fine2 121 us either way), small ones lose (in cache,
+// padding only takes up room: a batch of eight 32^3 - 96^3 boxes 15.9 ->
+// 17.5 ms per 60 steps), as does padding of 14 % (201^3 FP32: no gain).  The
+// coarse level's rows have no gaps: wider ones only lose (200^3: +15 %).  So:
+// three dimensions, two buffers of 512 MB or more, padding of at most 12 %,
+// and not where memory or 32-bit offsets would be at stake: level pairs over
+// 64 GB and planes of 2^27 bytes or more keep the narrow rows.
+struct RowPitch {
+  int pitch, xo;
+};
+static RowPitch fine_pitch(const int* nf, int D, int64_t sb) {
+  const int xo = (int)(16 / sb) - 1, line = (int)(128 / sb);
+  const RowPitch narrow{pitch_of(nf[0] + xo), xo};
+  const RowPitch wide{(nf[0] + line - 1 + line - 1) / line * line, line - 1};
+  const int64_t node = 2 * 19 * sb, was = node * narrow.pitch * nf[1] * nf[2];
+  const bool take = D == 3 && was >= ((int64_t)512 << 20) && was <= ((int64_t)64 << 30) &&
+                    (int64_t)100 * wide.pitch <= (int64_t)112 * narrow.pitch &&
+                    node / 2 * wide.pitch * nf[1] < ((int64_t)1 << 27);
+  return take ? wide : narrow;
+}
+
 static Geo validate(const lbm_grid_desc& d) {
   if (d.lattice != LBM_D2Q9 && d.lattice != LBM_D3Q19) throw LbmError(LBM_EINVAL, "unknown lattice");
   if (d.collision < LBM_BGK || d.collision > LBM_HRR) throw LbmError(LBM_EINVAL, "unknown collision model");
@@ -1396,11 +1427,15 @@ static Geo validate(const lbm_grid_desc& d) {
     }
     g.Nf = (int64_t)g.nf[0] * g.nf[1] * g.nf[2];
   }
+  const int64_t sb = d.precision == LBM_FP32_DEV ? 4 : 8;
   g.pc = pitch_of(g.n[0]);
   g.Ncp = (int64_t)g.pc * g.n[1] * g.n[2];
-  g.fxo = d.precision == LBM_FP32_DEV ? 3 : 1;
-  g.pf = g.has_fine ? pitch_of(g.nf[0] + g.fxo) : 0;
-  g.Nfp = g.has_fine ? (int64_t)g.pf * g.nf[1] * g.nf[2] : 0;
+  if (g.has_fine) {
+    const RowPitch r = fine_pitch(g.nf, g.D, sb);
+    g.fxo = r.xo;
+    g.pf = r.pitch;
+    g.Nfp = (int64_t)g.pf * g.nf[1] * g.nf[2];
+  }
   // the bulk kernels number node positions and vectors in 32 bits
   if (g.Ncp >= ((int64_t)1 << 31) || g.Nfp >= ((int64_t)1 << 31)) throw LbmError(LBM_EINVAL, "grid too large");
   return g;
