@@ -198,18 +198,32 @@ __global__ __launch_bounds__(64) void kb_hist_time(const InstDev* __restrict__ i
   }
 }
 
-// Ring reconstruction of one 64-node item: SUB 0 (t+1/2, from G, into the
-// half-time buffer: fh when fused, else B), SUB 1 (t+1, from the t+1
-// history, into the buffer that holds t+1 after the step: B when fused, else
-// A); only the populations the stepping reads (the full ring of A is
-// completed before it is observed).
+// Ring reconstruction of one 64-node item: SUB 0 (t+1/2, from G, or in D2Q9
+// BGK / RR with the capture of ring_half_body, into the half-time buffer: fh
+// when fused, else B), SUB 1 (t+1, from the t+1 history, into the buffer that
+// holds t+1 after the step: B when fused, else A); only the populations the
+// stepping reads (the full ring of A is completed before it is observed).
 template <int LAT, bool DEV, typename S, int MODEL, int SUB>
 __device__ __forceinline__ void kb_ring_item(const InstDev& I, int idx, int lane) {
-  const double* G = glob(SUB == 0 ? I.G : I.hist[I.hs[2]]);
   S* dst = glob((S*)(SUB == 0 ? (I.fused ? I.fh : I.fbuf[I.fpar ^ 1]) : I.fbuf[I.fpar ^ I.fused]));
-  S* xb = (SUB == 0 && I.xb) ? glob((S*)I.xb) : nullptr;  // the t+1/2 ring fills the x-band copy
-  ring_body<LAT, DEV, S, MODEL, true>(G, dst, I.g, glob(I.itf), I.tau_f / (2.0 * I.tau_c), 1.0 - 1.0 / I.tau_f, I.tau_f, I.sig,
-                                      (int64_t)idx * 64 + lane, xb);
+  const double kf = I.tau_f / (2.0 * I.tau_c), om_f = 1.0 - 1.0 / I.tau_f;
+  const int64_t r = (int64_t)idx * 64 + lane;
+  if constexpr (SUB == 0 && Lattice<LAT>::D == 2 && MODEL != M_HRR) {
+    ring_half_body<LAT, DEV, S, MODEL>(glob((const S*)I.ccur), glob(I.hist[I.hs[0]]), glob(I.hist[I.hs[1]]), dst, I.g,
+                                       glob(I.itf), kf, om_f, I.tau_f, I.sig, r);
+  } else {
+    const double* G = glob(SUB == 0 ? I.G : I.hist[I.hs[2]]);
+    S* xb = (SUB == 0 && I.xb) ? glob((S*)I.xb) : nullptr;  // the t+1/2 ring fills the x-band copy
+    ring_body<LAT, DEV, S, MODEL, true>(G, dst, I.g, glob(I.itf), kf, om_f, I.tau_f, I.sig, r, xb);
+  }
+}
+// Item of this wave, or -1: block b of one part of a launch takes W
+// consecutive items, one per wave.
+template <int W>
+__device__ __forceinline__ int wave_item(int b, int n) {
+  const int grp = item_in(b, (n + W - 1) / W);
+  const int it = grp * W + __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  return grp < 0 || it >= n ? -1 : it;
 }
 template <int LAT, bool DEV, typename S, int MODEL, int SUB>
 __global__ __launch_bounds__(64) void kb_ring(const InstDev* __restrict__ inst, const Work* __restrict__ items,
@@ -222,21 +236,29 @@ __global__ __launch_bounds__(64) void kb_ring(const InstDev* __restrict__ inst, 
   }
 }
 
-// Coarse stream (BGK, RR) and the t+1/2 ring in one launch: blocks [0, nrb)
-// take ring items (64 lanes each), the rest coarse chunks.
+// Coarse stream (BGK, RR), the t+1/2 ring and, D2Q9, the history capture in
+// one launch: blocks [0, nrb) take ring items (one per wave), the next nhb
+// history items, the rest coarse chunks.
 template <int LAT, bool DEV, typename S, int MODEL, bool NT>
 __global__ __launch_bounds__(256) void kb_stream_ring(const InstDev* __restrict__ inst, const Work* __restrict__ ritems,
-                                                      const int* __restrict__ rcount, const Work* __restrict__ citems,
-                                                      const int* __restrict__ ccount, int nrb) {
-  const int b = blockIdx.x;
+                                                      const int* __restrict__ rcount, const Work* __restrict__ hitems,
+                                                      const int* __restrict__ hcount, const Work* __restrict__ citems,
+                                                      const int* __restrict__ ccount, int nrb, int nhb) {
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
   if (b < nrb) {
-    if (threadIdx.x >= 64) return;
-    const int it = item_in(b, *rcount);
+    const int it = wave_item<4>(b, *rcount);
     if (it < 0) return;
     const Work w = load_item(ritems, it);
-    kb_ring_item<LAT, DEV, S, MODEL, 0>(inst[w.inst], w.idx, threadIdx.x);
+    kb_ring_item<LAT, DEV, S, MODEL, 0>(inst[w.inst], w.idx, lane);
+  } else if (b < nrb + nhb) {
+    const int it = wave_item<4>(b - nrb, *hcount);
+    if (it < 0) return;
+    const Work w = load_item(hitems, it);
+    const InstDev& I = inst[w.inst];
+    hist_capture_body<LAT, DEV, S, MODEL>(glob((const S*)I.ccur), glob(I.hist[I.hs[2]]), I.g, glob(I.itf),
+                                          (int64_t)w.idx * 64 + lane);
   } else {
-    const int it = item_in(b - nrb, *ccount);
+    const int it = item_in(b - nrb - nhb, *ccount);
     if (it < 0) return;
     const Work w = load_item(citems, it);
     const InstDev& I = inst[w.inst];
@@ -245,17 +267,40 @@ __global__ __launch_bounds__(256) void kb_stream_ring(const InstDev* __restrict_
   }
 }
 
-// Both fine substeps of one tile (D2Q9 BGK / RR), A -> B with the t+1/2 ring
-// and band in fh.
+// Both fine substeps (D2Q9 BGK / RR), A -> B with the t+1/2 ring in fh, the
+// t+1 ring into B and the transfer to the TN nodes, as k_fine2: blocks
+// [0, ncb) take transfer segments, the next nrb ring items (one per wave), the
+// rest tiles.
 template <int LAT, bool DEV, typename S, int MODEL, bool NT, int HXV, int HYR>
-__global__ __launch_bounds__(HXV * HYR) void kb_fine2(const InstDev* __restrict__ inst, const Work* __restrict__ items,
-                                                      const int* __restrict__ count) {
-  const int it = item_of(*count);
+__global__ __launch_bounds__(HXV * HYR) void kb_fine2(const InstDev* __restrict__ inst, const Work* __restrict__ sitems,
+                                                      const int* __restrict__ scount, const Work* __restrict__ ritems,
+                                                      const int* __restrict__ rcount, const Work* __restrict__ items,
+                                                      const int* __restrict__ count, int ncb, int nrb) {
+  __shared__ __attribute__((aligned(16))) char raw[fine2_lds<S, MODEL, HXV, HYR>()];
+  const int b = blockIdx.x;
+  if (b < ncb) {
+    const int it = item_in(b, *scount);
+    if (it < 0) return;  // whole work group: the transfer synchronises its lanes
+    const Work w = load_item(sitems, it);
+    const InstDev& I = inst[w.inst];
+    coalesce2_segment<LAT, DEV, S, MODEL, fine2_nseg<HXV * HYR>()>(
+        glob((const S*)I.fbuf[I.fpar]), glob((const S*)I.fh), glob((S*)I.cnext), I.g, (S)(1.0 - 1.0 / I.tau_f),
+        2.0 * I.tau_c / I.tau_f, 1.0 - 1.0 / I.tau_c, I.tau_c, w.idx, raw, nullptr);
+    return;
+  }
+  if (b < ncb + nrb) {
+    const int it = wave_item<HXV * HYR / 64>(b - ncb, *rcount);
+    if (it < 0) return;
+    const Work w = load_item(ritems, it);
+    kb_ring_item<LAT, DEV, S, MODEL, 1>(inst[w.inst], w.idx, threadIdx.x & 63);
+    return;
+  }
+  const int it = item_in(b - ncb - nrb, *count);
   if (it < 0) return;
   const Work w = load_item(items, it);
   const InstDev& I = inst[w.inst];
-  fine2_tile<LAT, DEV, S, MODEL, NT, HXV, HYR>(glob((const S*)I.fbuf[I.fpar]),
-                                                             glob((S*)I.fbuf[I.fpar ^ 1]), glob((S*)I.fh), I.g, (S)(1.0 - 1.0 / I.tau_f), I.ntx, w.idx);
+  fine2_tile<LAT, DEV, S, MODEL, NT, HXV, HYR>(glob((const S*)I.fbuf[I.fpar]), glob((S*)I.fbuf[I.fpar ^ 1]),
+                                               glob((S*)I.fh), I.g, (S)(1.0 - 1.0 / I.tau_f), I.ntx, w.idx, raw);
 }
 
 // H-RR ring rho, u at t+1/2 (SUB 0) or t+1 (SUB 1).

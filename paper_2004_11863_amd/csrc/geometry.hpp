@@ -53,19 +53,17 @@ __host__ __device__ inline int64_t cpos(const Geo& g, int x, int y, int z) {
 __host__ __device__ inline int64_t fpos(const Geo& g, int x, int y, int z) {
   return (int64_t)(x + g.fxo) + (int64_t)g.pf * ((int64_t)y + (int64_t)g.nf[1] * z);
 }
-// Logical node index -> coordinates.
-__host__ __device__ inline void cdecode(const Geo& g, int64_t i, int& x, int& y, int& z) {
-  x = (int)(i % g.n[0]);
-  const int64_t r = i / g.n[0];
-  y = (int)(r % g.n[1]);
-  z = (int)(r / g.n[1]);
+// Logical node index -> coordinates (32-bit: levels of 2^31 or more positions
+// are rejected, and 64-bit divisions cost the interface kernels some hundred
+// instructions a node).
+__host__ __device__ inline void decode_in(const int* n, int64_t i, int& x, int& y, int& z) {
+  const uint32_t k = (uint32_t)i, r = k / (uint32_t)n[0];
+  x = (int)(k - r * (uint32_t)n[0]);
+  z = (int)(r / (uint32_t)n[1]);
+  y = (int)(r - (uint32_t)z * (uint32_t)n[1]);
 }
-__host__ __device__ inline void fdecode(const Geo& g, int64_t i, int& x, int& y, int& z) {
-  x = (int)(i % g.nf[0]);
-  const int64_t r = i / g.nf[0];
-  y = (int)(r % g.nf[1]);
-  z = (int)(r / g.nf[1]);
-}
+__host__ __device__ inline void cdecode(const Geo& g, int64_t i, int& x, int& y, int& z) { decode_in(g.n, i, x, y, z); }
+__host__ __device__ inline void fdecode(const Geo& g, int64_t i, int& x, int& y, int& z) { decode_in(g.nf, i, x, y, z); }
 
 __host__ __device__ inline int coarse_class(const Geo& g, int x, int y, int z) {
   if (!g.has_fine) return CC_MIDDLE;

@@ -576,22 +576,17 @@ __device__ __forceinline__ double time_half(double hm, double h0, double hp) {
   return -0.125 * hm + 0.75 * h0 + 0.375 * hp;
 }
 
-// Pre-collision state of coarse history nodes at t+1 (pulled from the
-// post-collision coarse state at t): rho, u and the non-equilibrium part.
-// With G set (BGK, RR: every field is known here) each value is also
-// interpolated to t+1/2 from the two older levels Hm, H0 into G.
+// Pre-collision state of a coarse history node at t+1 (pulled from the
+// post-collision coarse state at t): rho, u and the non-equilibrium part, the
+// first HF::S fields of v.
 template <int LAT, bool DEV, typename S, int MODEL>
-__device__ __forceinline__ void hist_capture_body(const S* __restrict__ src, double* __restrict__ H, const Geo& g,
-                                         const Iface& itf, int64_t h, double* __restrict__ G = nullptr,
-                                         const double* __restrict__ Hm = nullptr,
-                                         const double* __restrict__ H0 = nullptr) {
+__device__ __forceinline__ void hist_values(const S* __restrict__ src, const Geo& g, int64_t node, double* v) {
   using L = Lattice<LAT>;
   using F = HF<LAT, MODEL>;
   using N = Node<LAT, false, double>;
   constexpr int Q = L::Q;
-  if (h >= itf.NH) return;
   int x, y, z;
-  cdecode(g, itf.hnode[h], x, y, z);
+  cdecode(g, node, x, y, z);
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   double f[Q];
 #pragma unroll
@@ -602,25 +597,36 @@ __device__ __forceinline__ void hist_capture_body(const S* __restrict__ src, dou
   }
   double rho, r0, u[3];
   N::moments(f, rho, r0, u);
-  const int64_t NH = itf.NH;
-  auto put = [&](int field, double v) {
-    const int64_t k = (int64_t)field * NH + h;
-    H[k] = v;
-    if (G) G[k] = time_half(Hm[k], H0[k], v);
-  };
-  put(F::RHO, rho);
+  v[F::RHO] = rho;
 #pragma unroll
-  for (int d = 0; d < L::D; ++d) put(F::U + d, u[d]);
+  for (int d = 0; d < L::D; ++d) v[F::U + d] = u[d];
   if (MODEL == M_BGK) {
     double f0[Q];
     N::feq(rho, r0, u, f0);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) put(F::F1 + i, f[i] - f0[i]);
+    for (int i = 0; i < Q; ++i) v[F::F1 + i] = f[i] - f0[i];
   } else {
-    double a[NS<L::D>::value];
-    sym_put<L::D>(a1_of<LAT>(f, rho, u), a, 1.0);
+    sym_put<L::D>(a1_of<LAT>(f, rho, u), v + F::F1, 1.0);
+  }
+}
+
+// Captures history node h into H.  With G set (D3Q19 BGK, RR: every field is
+// known here) each value is also interpolated to t+1/2 from the two older
+// levels Hm, H0 into G.
+template <int LAT, bool DEV, typename S, int MODEL>
+__device__ __forceinline__ void hist_capture_body(const S* __restrict__ src, double* __restrict__ H, const Geo& g,
+                                         const Iface& itf, int64_t h, double* __restrict__ G = nullptr,
+                                         const double* __restrict__ Hm = nullptr,
+                                         const double* __restrict__ H0 = nullptr) {
+  using F = HF<LAT, MODEL>;
+  if (h >= itf.NH) return;
+  double v[F::S];
+  hist_values<LAT, DEV, S, MODEL>(src, g, itf.hnode[h], v);
 #pragma unroll
-    for (int k = 0; k < NS<L::D>::value; ++k) put(F::F1 + k, a[k]);
+  for (int f = 0; f < F::S; ++f) {
+    const int64_t k = (int64_t)f * itf.NH + h;
+    H[k] = v[f];
+    if (G) G[k] = time_half(Hm[k], H0[k], v[f]);
   }
 }
 template <int LAT, bool DEV, typename S, int MODEL>
@@ -769,26 +775,13 @@ __global__ void k_ring_macro(const double* __restrict__ Hm, const double* __rest
 // With xb set (the t+1/2 ring of the two-launch D3Q19 path) ring nodes in
 // the x-bands also store the same populations into the compact band copy.
 template <int LAT, bool DEV, typename S, int MODEL, bool PARTIAL>
-__device__ __forceinline__ void ring_body(const double* __restrict__ G, S* __restrict__ dst, const Geo& g, const Iface& itf,
-                                 double kf, double om_f, double tau_f, double sig, int64_t r,
-                                 S* __restrict__ xb = nullptr) {
+__device__ __forceinline__ void ring_store(const double* v, S* __restrict__ dst, const Geo& g, const Iface& itf,
+                                           double kf, double om_f, double tau_f, double sig, int64_t r,
+                                           S* __restrict__ xb) {
   using L = Lattice<LAT>;
   using F = HF<LAT, MODEL>;
   using N = Node<LAT, false, double>;
   constexpr int Q = L::Q, D = L::D;
-  if (r >= itf.NR) return;
-  const int np = itf.rnp[r];
-  const int32_t* pt = itf.rpt + 16 * r;
-  const int64_t NH = itf.NH;
-  double v[F::N];
-#pragma unroll
-  for (int k = 0; k < F::N; ++k) v[k] = 0.0;
-  for (int s = 0; s < np; ++s) {
-    const int64_t h = pt[s];
-    const double ws = ring_w(np, s);
-#pragma unroll
-    for (int k = 0; k < F::N; ++k) v[k] += ws * G[(int64_t)k * NH + h];
-  }
   const double rho = v[F::RHO];
   double u[3] = {v[F::U], v[F::U + 1], D == 3 ? v[F::U + 2] : 0.0};
   double f[Q];
@@ -820,6 +813,58 @@ __device__ __forceinline__ void ring_body(const double* __restrict__ G, S* __res
       if (x >= g.nf[0] - 5) xb[xband_at(g, Q, 1, i, y, z, x - (g.nf[0] - 5))] = sv;
     }
   }
+}
+template <int LAT, bool DEV, typename S, int MODEL, bool PARTIAL>
+__device__ __forceinline__ void ring_body(const double* __restrict__ G, S* __restrict__ dst, const Geo& g, const Iface& itf,
+                                 double kf, double om_f, double tau_f, double sig, int64_t r,
+                                 S* __restrict__ xb = nullptr) {
+  using F = HF<LAT, MODEL>;
+  if (r >= itf.NR) return;
+  const int np = itf.rnp[r];
+  const int32_t* pt = itf.rpt + 16 * r;
+  const int64_t NH = itf.NH;
+  double v[F::N];
+#pragma unroll
+  for (int k = 0; k < F::N; ++k) v[k] = 0.0;
+  for (int s = 0; s < np; ++s) {
+    const int64_t h = pt[s];
+    const double ws = ring_w(np, s);
+#pragma unroll
+    for (int k = 0; k < F::N; ++k) v[k] += ws * G[(int64_t)k * NH + h];
+  }
+  ring_store<LAT, DEV, S, MODEL, PARTIAL>(v, dst, g, itf, kf, om_f, tau_f, sig, r, xb);
+}
+// The t+1/2 ring of a D2Q9 BGK / RR level without the history capture before
+// it: the t+1 values of the node's (at most four) history points are captured
+// here as hist_capture_body captures them, and interpolated in time with the
+// two older levels -- the arithmetic of capture, G and ring_body in turn, so
+// the same bits, and one launch less in the chain of the step.
+template <int LAT, bool DEV, typename S, int MODEL>
+__device__ __forceinline__ void ring_half_body(const S* __restrict__ src, const double* __restrict__ Hm,
+                                               const double* __restrict__ H0, S* __restrict__ dst, const Geo& g,
+                                               const Iface& itf, double kf, double om_f, double tau_f, double sig,
+                                               int64_t r) {
+  using F = HF<LAT, MODEL>;
+  static_assert(Lattice<LAT>::D == 2 && MODEL != M_HRR, "stencils of at most four points, every field captured");
+  if (r >= itf.NR) return;
+  const int np = itf.rnp[r];
+  const int32_t* pt = itf.rpt + 16 * r;
+  double v[F::N];
+#pragma unroll
+  for (int k = 0; k < F::N; ++k) v[k] = 0.0;
+  for (int s = 0; s < np; ++s) {
+    const int64_t h = pt[s];
+    const double ws = ring_w(np, s);
+    double c[F::S];
+    hist_values<LAT, DEV, S, MODEL>(src, g, itf.hnode[h], c);
+#pragma unroll
+    for (int k = 0; k < F::N; ++k) {
+      const int64_t o = (int64_t)k * itf.NH + h;
+      const double gv = time_half(Hm[o], H0[o], c[k]);
+      v[k] += ws * gv;
+    }
+  }
+  ring_store<LAT, DEV, S, MODEL, true>(v, dst, g, itf, kf, om_f, tau_f, sig, r, nullptr);
 }
 template <int LAT, bool DEV, typename S, int MODEL, bool PARTIAL>
 __global__ void k_ring(const double* __restrict__ G, S* __restrict__ dst, const Geo g, const Iface itf,
@@ -895,36 +940,38 @@ __global__ void k_fict(const S* __restrict__ src_f, T* __restrict__ mac_c, const
 // (eq filterFneq), rescaled by 2 tau_c / tau_f (eq rescfc) and added to f0
 // of the co-located fine node; H-RR takes S^c = 2 S^f (eq PijResc) with S^f
 // by fine centred differences.  The coarse node is then collided with tau_c.
-// One work group handles PER TN nodes: lane (stencil point s, TN node t),
-// t fastest so neighbouring lanes read neighbouring nodes, computes the
-// weighted non-equilibrium part of one stencil node into LDS; lanes per
-// (TN node, component) sum the stencil in a fixed order; one lane per TN node
-// rebuilds and collides.  SENS: the node's record for the NH sensors, as in
-// stream_body.
-template <int LAT, bool DEV, typename S, int MODEL, bool SENS = false>
-__device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g, const Iface& itf,
-                                     double kc, double om_c, double tau_c, double sig, int64_t blk,
-                                     const S* __restrict__ xb = nullptr, double* __restrict__ su = nullptr) {
+// A work group handles up to PER TN nodes (cnt of them live): lane (stencil
+// point s, TN node t), t fastest so neighbouring lanes read neighbouring
+// nodes, computes the weighted non-equilibrium part of one stencil node into
+// LDS; lanes per (TN node, component) sum the stencil in a fixed order; one
+// lane per TN node rebuilds and collides.  pull(t, ox, oy, oz, f) gives the
+// populations that arrive at the stencil node, tnode(t, cx, cy, cz) the coarse
+// TN node; raw: LDS of coalesce_lds() bytes.  su: the node's record for the
+// NH sensors, as in stream_body, or null.
+template <int LAT, int MODEL, int PER>
+constexpr int coalesce_lds() {
+  constexpr int NST = Lattice<LAT>::D == 2 ? 9 : 27, NC = HF<LAT, MODEL>::NF1;
+  return (int)sizeof(double) * PER * (NST * (NC + 4) + NC);
+}
+template <int LAT, bool DEV, typename S, int MODEL, int PER, typename PullF, typename NodeF>
+__device__ __forceinline__ void coalesce_nodes(char* raw, int cnt, PullF&& pull, NodeF&& tnode, S* __restrict__ dst_c,
+                                               const Geo& g, double kc, double om_c, double tau_c, double sig,
+                                               double* __restrict__ su) {
   using L = Lattice<LAT>;
   using N = Node<LAT, false, double>;
   using F = HF<LAT, MODEL>;
   constexpr int Q = L::Q, D = L::D;
   constexpr int NST = (D == 2) ? 9 : 27;
-  constexpr int PER = 256 / NST;
   constexpr int CEN = (D == 2) ? 4 : 13;
   constexpr int NC = F::NF1;  // components filtered per stencil node
-  __shared__ double sf1[PER][NST][NC];
-  __shared__ double sm[PER][NST][4];
-  __shared__ double sacc[PER][NC];
-  __syncthreads();  // the LDS may still be read by a previous call in this work group
+  double(*sf1)[NST][NC] = reinterpret_cast<double(*)[NST][NC]>(raw);
+  double(*sm)[NST][4] = reinterpret_cast<double(*)[NST][4]>(raw + sizeof(double) * PER * NST * NC);
+  double(*sacc)[NC] = reinterpret_cast<double(*)[NC]>(raw + sizeof(double) * PER * NST * (NC + 4));
   const int lt = threadIdx.x % PER, s = threadIdx.x / PER;
-  const int64_t t = blk * PER + lt;
-  if (s < NST && t < itf.NT) {
-    int x, y, z;
-    fdecode(g, itf.tnf[t], x, y, z);
+  if (s < NST && lt < cnt) {
     const int ox = s % 3 - 1, oy = (s / 3) % 3 - 1, oz = (D == 3) ? s / 9 - 1 : 0;
     double f[Q], rho, r0, u[3];
-    pull_fine<LAT, DEV, S>(src_f, g, x + ox, y + oy, z + oz, f, xb);
+    pull(lt, ox, oy, oz, f);
     N::moments(f, rho, r0, u);
     const double w = (ox ? 0.25 : 0.5) * (oy ? 0.25 : 0.5) * (D == 3 ? (oz ? 0.25 : 0.5) : 1.0);
     if (MODEL == M_BGK) {
@@ -944,17 +991,15 @@ __device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __
     sm[lt][s][3] = u[2];
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < PER * NC; p += blockDim.x) {
+  for (int p = threadIdx.x; p < cnt * NC; p += blockDim.x) {
     const int l2 = p / NC, q = p % NC;
     double acc = 0.0;
     for (int k = 0; k < NST; ++k) acc += sf1[l2][k][q];
     sacc[l2][q] = acc;
   }
   __syncthreads();
-  if ((int)threadIdx.x >= PER) return;
   const int l3 = threadIdx.x;
-  const int64_t t3 = blk * PER + l3;
-  if (t3 >= itf.NT) return;
+  if (l3 >= cnt) return;
   const double rc = sm[l3][CEN][0];
   double uc[3] = {sm[l3][CEN][1], sm[l3][CEN][2], sm[l3][CEN][3]};
   double f[Q];
@@ -982,15 +1027,15 @@ __device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __
     N::regular(rc, rc, uc, om_c, a, f);
   }
   int cx, cy, cz;
-  cdecode(g, itf.tnc[t3], cx, cy, cz);
+  tnode(l3, cx, cy, cz);
   const int64_t ci = cpos(g, cx, cy, cz);
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const S st = store_pop<S, DEV, LAT>(f[i], i);
     dst_c[pop_at<S, Q>(ci, i)] = st;
-    if constexpr (SENS) f[i] = full_pop<S, DEV, LAT>(st, i);
+    f[i] = full_pop<S, DEV, LAT>(st, i);
   }
-  if constexpr (SENS) {
+  if (su) {
     double r, r0, u[3];
     N::moments(f, r, r0, u);
 #pragma unroll
@@ -998,26 +1043,147 @@ __device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __
   }
 }
 
+// The TN nodes [blk PER, (blk + 1) PER) of the table, from the fine state
+// src_f (and the compact copy xb of its x-bands); the whole work group of 256
+// lanes calls it.
+template <int LAT, bool DEV, typename S, int MODEL>
+__device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g, const Iface& itf,
+                                     double kc, double om_c, double tau_c, double sig, int64_t blk,
+                                     const S* __restrict__ xb = nullptr, double* __restrict__ su = nullptr) {
+  constexpr int PER = 256 / (Lattice<LAT>::D == 2 ? 9 : 27);
+  __shared__ __attribute__((aligned(16))) char raw[coalesce_lds<LAT, MODEL, PER>()];
+  const int64_t t0 = blk * PER;
+  const int cnt = (int)min((int64_t)PER, itf.NT - t0);
+  if (cnt <= 0) return;  // whole work group
+  coalesce_nodes<LAT, DEV, S, MODEL, PER>(
+      raw, cnt,
+      [&](int lt, int ox, int oy, int oz, double* f) __attribute__((always_inline)) {
+        int x, y, z;
+        fdecode(g, itf.tnf[t0 + lt], x, y, z);
+        pull_fine<LAT, DEV, S>(src_f, g, x + ox, y + oy, z + oz, f, xb);
+      },
+      [&](int lt, int& cx, int& cy, int& cz) __attribute__((always_inline)) { cdecode(g, itf.tnc[t0 + lt], cx, cy, cz); },
+      dst_c, g, kc, om_c, tau_c, sig, su);
+}
 
-// Coarse pull-stream + collide (BGK, RR) and the ring reconstruction at
-// t+1/2 (G -> the fine buffer of half times) in one launch: independent work,
-// the ring latency-bound and the stream bandwidth-bound, so the ring hides
-// inside the stream.  Blocks [0, nrb) take 256 ring nodes each (dispatched
-// first), the rest are the stream's chunks; both parts are XCD-contiguous.
+// ---------------------------------------------------------------------------
+// The fine-to-coarse transfer of a D2Q9 BGK / RR level beside the fused fine
+// substeps (k_fine2), which keep the t+1/2 state on chip: a work group takes a
+// run of up to NSEG TN nodes along one side of the TN square and computes the
+// t+1/2 state of the 2 NSEG + 3 by 5 fine nodes their stencils pull from
+// itself -- middle nodes pulled from the state at t and collided exactly as
+// fine2_s1 does, ring nodes from `half` -- into LDS.  It then depends on
+// nothing the tiles of the same launch write, which saves the launch after
+// them and the stores of the band the transfer used to read.
+struct Segs {  // sides: y = 2, y = ny - 3, x = 2, x = nx - 3 (without the corners)
+  int nx, ny;  // TN nodes of a horizontal / vertical side
+  int sx, sy;  // segments per side
+};
+__host__ __device__ inline Segs coalesce2_segs(const Geo& g, int nseg) {
+  Segs s;
+  s.nx = g.m[0] - 1;
+  s.ny = g.m[1] - 3;
+  s.sx = (s.nx + nseg - 1) / nseg;
+  s.sy = (s.ny + nseg - 1) / nseg;
+  return s;
+}
+__host__ __device__ inline int coalesce2_count(const Geo& g, int nseg) {
+  const Segs s = coalesce2_segs(g, nseg);
+  return 2 * (s.sx + s.sy);
+}
+template <int MODEL, typename S, int NSEG>
+constexpr int coalesce2_lds() {
+  return (9 * 5 * (2 * NSEG + 3) * (int)sizeof(S) + 15) / 16 * 16 + coalesce_lds<0, MODEL, NSEG>();
+}
+template <int LAT, bool DEV, typename S, int MODEL, int NSEG>
+__device__ __forceinline__ void coalesce2_segment(const S* __restrict__ src, const S* __restrict__ half,
+                                                  S* __restrict__ dst_c, const Geo& g, const S om_f, double kc,
+                                                  double om_c, double tau_c, int seg, char* raw,
+                                                  double* __restrict__ su) {
+  using L = Lattice<LAT>;
+  constexpr int Q = L::Q, NP = 5 * (2 * NSEG + 3);
+  static_assert(L::D == 2 && MODEL != M_HRR, "beside the fused D2Q9 kernel");
+  S(*st)[NP] = reinterpret_cast<S(*)[NP]>(raw);
+  char* rest = raw + (sizeof(S) * Q * NP + 15) / 16 * 16;
+  const Segs sg = coalesce2_segs(g, NSEG);
+  int side, i0, n;
+  if (seg < 2 * sg.sx) {
+    side = seg / sg.sx;
+    i0 = (seg - side * sg.sx) * NSEG;
+    n = sg.nx;
+  } else {
+    const int k = seg - 2 * sg.sx, v = k / sg.sy;
+    side = 2 + v;
+    i0 = (k - v * sg.sy) * NSEG;
+    n = sg.ny;
+  }
+  const int cnt = min(NSEG, n - i0);
+  const int nx = g.nf[0], ny = g.nf[1];
+  // first TN node of the run (fine coordinates) and the step to the next
+  const bool hor = side < 2;
+  const int tx0 = hor ? 2 + 2 * i0 : (side == 2 ? 2 : nx - 3), ty0 = hor ? (side == 0 ? 2 : ny - 3) : 4 + 2 * i0;
+  const int pw = hor ? 2 * cnt + 3 : 5, ph = hor ? 5 : 2 * cnt + 3;
+  const int p = threadIdx.x;
+  if (p < pw * ph) {
+    const int x = tx0 - 2 + p % pw, y = ty0 - 2 + p / pw;
+    S f[Q];
+    if (x == 0 || x == nx - 1 || y == 0 || y == ny - 1) {
+      const int64_t q = fpos(g, x, y, 0);
+#pragma unroll
+      for (int i = 0; i < Q; ++i) f[i] = half[pop_at<S, Q>(q, i)];
+    } else {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) f[i] = src[pop_at<S, Q>(fpos(g, x - L::cx(i), y - L::cy(i), 0), i)];
+      Node<LAT, DEV, S>::collide(f, MODEL, om_f, S(0), S(0), nullptr);
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) st[i][p] = f[i];
+  }
+  __syncthreads();
+  coalesce_nodes<LAT, DEV, S, MODEL, NSEG>(
+      rest, cnt,
+      [&](int lt, int ox, int oy, int, double* f) __attribute__((always_inline)) {
+        const int c = (2 + ox + (hor ? 2 * lt : 0)) + pw * (2 + oy + (hor ? 0 : 2 * lt));
+#pragma unroll
+        for (int i = 0; i < Q; ++i) f[i] = full_pop<S, DEV, LAT>(st[i][c - L::cx(i) - pw * L::cy(i)], i);
+      },
+      [&](int lt, int& cx, int& cy, int& cz) __attribute__((always_inline)) {
+        cx = g.a[0] + (tx0 + (hor ? 2 * lt : 0)) / 2;
+        cy = g.a[1] + (ty0 + (hor ? 0 : 2 * lt)) / 2;
+        cz = 0;
+      },
+      dst_c, g, kc, om_c, tau_c, 0.0, su);
+}
+
+// Coarse pull-stream + collide (BGK, RR), the ring reconstruction at t+1/2
+// (into the fine buffer of half times) and, D2Q9, the history capture in one
+// launch: independent work, the interface parts latency-bound and the stream
+// bandwidth-bound, so they hide inside the stream.  D2Q9 rings capture the
+// history values they need themselves (ring_half_body); D3Q19 rings read G,
+// which the capture filled.  Blocks [0, nrb) take lanes ring nodes each
+// (dispatched first), the next nhb as many history nodes, the rest are the
+// stream's chunks; every part is XCD-contiguous.
 // SENS: the stream also records the NH sensors' coarse velocities into su.
 template <int LAT, bool DEV, typename S, int MODEL, bool NT, bool SENS = false>
 __global__ __launch_bounds__(256) void k_stream_ring(const S* __restrict__ src, S* __restrict__ dst, const Geo g,
                                                      const Flat fl, const S om, const double* __restrict__ G,
-                                                     S* __restrict__ fdst, const Iface itf, double kf, double om_f,
-                                                     double tau_f, double sig, int nrb, S* __restrict__ xb,
-                                                     double* __restrict__ su) {
+                                                     const double* __restrict__ Hm, const double* __restrict__ H0,
+                                                     double* __restrict__ Hp, S* __restrict__ fdst, const Iface itf,
+                                                     double kf, double om_f, double tau_f, double sig, int lanes,
+                                                     int nrb, int nhb, S* __restrict__ xb, double* __restrict__ su) {
   const int b = blockIdx.x;
-  if (b < nrb) {
-    const int per = nrb / kXCD;
-    const int64_t blk = (int64_t)(b % kXCD) * per + b / kXCD;
-    ring_body<LAT, DEV, S, MODEL, true>(G, fdst, g, itf, kf, om_f, tau_f, sig, blk * 256 + threadIdx.x, xb);
+  if (b < nrb + nhb) {
+    if ((int)threadIdx.x >= lanes) return;
+    const int c = b < nrb ? b : b - nrb, per = (b < nrb ? nrb : nhb) / kXCD;
+    const int64_t k = ((int64_t)(c % kXCD) * per + c / kXCD) * lanes + threadIdx.x;
+    if constexpr (Lattice<LAT>::D == 2) {
+      if (b < nrb) ring_half_body<LAT, DEV, S, MODEL>(src, Hm, H0, fdst, g, itf, kf, om_f, tau_f, sig, k);
+      else hist_capture_body<LAT, DEV, S, MODEL>(src, Hp, g, itf, k);
+    } else {
+      ring_body<LAT, DEV, S, MODEL, true>(G, fdst, g, itf, kf, om_f, tau_f, sig, k, xb);
+    }
   } else {
-    const int b2 = b - nrb;
+    const int b2 = b - nrb - nhb;
     stream_body<LAT, DEV, S, MODEL, 0, NT, SENS>(src, dst, nullptr, g, fl, om, (b2 % kXCD) * fl.per_xcd + b2 / kXCD,
                                                  nullptr, su);
   }
@@ -1028,9 +1194,9 @@ __global__ __launch_bounds__(256) void k_stream_ring(const S* __restrict__ src, 
 // state at t+1/2 -> coarse TN) in one launch: they write disjoint buffers and
 // read none of each other's outputs.  Blocks [0, nrb) take 256 ring nodes
 // each, the rest PER TN nodes each; both parts are XCD-contiguous (nrb is a
-// multiple of 8).  SENS: the transfer records the NH sensors' velocities of
-// the TN nodes into su.
-template <int LAT, bool DEV, typename S, int MODEL, bool SENS = false>
+// multiple of 8).  su: the transfer records the NH sensors' velocities of the
+// TN nodes there (or null).
+template <int LAT, bool DEV, typename S, int MODEL>
 __global__ __launch_bounds__(256) void k_ring_coalesce(const double* __restrict__ Hp, S* __restrict__ fdst,
                                                        const S* __restrict__ src_f, S* __restrict__ dst_c,
                                                        const Geo g, const Iface itf, double kf, double om_f,
@@ -1043,7 +1209,7 @@ __global__ __launch_bounds__(256) void k_ring_coalesce(const double* __restrict_
     ring_body<LAT, DEV, S, MODEL, true>(Hp, fdst, g, itf, kf, om_f, tau_f, sig, blk * 256 + threadIdx.x);
   } else {
     const int b2 = b - nrb, per = ((int)gridDim.x - nrb) / kXCD;
-    coalesce_body<LAT, DEV, S, MODEL, SENS>(src_f, dst_c, g, itf, kc, om_c, tau_c, sig,
+    coalesce_body<LAT, DEV, S, MODEL>(src_f, dst_c, g, itf, kc, om_c, tau_c, sig,
                                             (int64_t)(b2 % kXCD) * per + b2 / kXCD, xb, su);
   }
 }
@@ -1058,21 +1224,18 @@ __global__ __launch_bounds__(256) void k_ring_coalesce(const double* __restrict_
 // (t+1/2 -> t+1) then pulls from LDS and collides the tile, writing dst.  HBM
 // sees one read and one write of the populations per fine node per coarse
 // step instead of two of each; the arithmetic per node is that of two
-// k_stream launches, so the results are bitwise the same.  The t+1/2 state of
-// the middle nodes within 2 nodes of the TN line (where the fine-to-coarse
-// transfer pulls) is also stored into `half`.
+// k_stream launches, so the results are bitwise the same.
 // Substep 1 of one vector (node x0 = 1 + V k of row y) into an LDS row
 // (`row[i]` points at population i of that row, c0 the vector's first
 // column).  Middle nodes pull from src and collide; ring nodes take their
-// t+1/2 values from `half`; `band` asks to store the result of middle nodes
-// within 2 nodes of the TN line into `half` as well.  SENS (the NH sensors'
-// record of this iteration, for the lane that owns the vector, `band`):
+// t+1/2 values from `half`.  SENS (the NH sensors' record of this iteration,
+// for the lane that owns the vector, `own`):
 // every middle node's result goes to `half` and the velocity of its pulled
 // (pre-collision) populations to the double planes su ([1 + D][padded
 // positions]), in the arithmetic of k_sens_vel.
 template <int LAT, bool DEV, typename S, int MODEL, bool SENS = false>
 __device__ __forceinline__ void fine2_s1(const S* __restrict__ src, S* __restrict__ half, const Geo& g, const S om,
-                                         int k, int y, int nv, S* const* row, int c0, bool band,
+                                         int k, int y, int nv, S* const* row, int c0, bool own,
                                          double* __restrict__ su = nullptr) {
   using L = Lattice<LAT>;
   using N = Node<LAT, DEV, S>;
@@ -1100,7 +1263,7 @@ __device__ __forceinline__ void fine2_s1(const S* __restrict__ src, S* __restric
   // multiples of V)
   const bool whole = x0 + V - 1 <= nx - 2;
   if constexpr (SENS) {
-    if (band) {
+    if (own) {
       typedef double DV __attribute__((ext_vector_type(V)));
       DV uv[2];
 #pragma unroll
@@ -1146,19 +1309,17 @@ __device__ __forceinline__ void fine2_s1(const S* __restrict__ src, S* __restric
 #pragma unroll
       for (int i = 0; i < Q; ++i) row[i][c0 + jr] = half[pop_at<S, Q>(p, i)];
   }
-  if (band) {
-    if (SENS && whole) {
-      const int64_t p0 = fpos(g, x0, y, 0);
+  if (SENS && own) {
+    const int64_t p0 = fpos(g, x0, y, 0);
+    if (whole) {
 #pragma unroll
       for (int i = 0; i < Q; ++i) vstore<false>((VA*)(half + pop_at<S, Q>(p0, i)), v[i]);
     } else {
 #pragma unroll
       for (int j = 0; j < V; ++j) {
-        const int x = x0 + j;
-        if (x > nx - 2 || (!SENS && !(x <= 4 || x >= nx - 5 || y <= 4 || y >= ny - 5))) continue;
-        const int64_t p = fpos(g, x, y, 0);
+        if (x0 + j > nx - 2) continue;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) half[pop_at<S, Q>(p, i)] = v[i][j];
+        for (int i = 0; i < Q; ++i) half[pop_at<S, Q>(p0 + j, i)] = v[i][j];
       }
     }
   }
@@ -1191,8 +1352,19 @@ __device__ __forceinline__ void fine2_s2(S* __restrict__ dst, const Geo& g, cons
     for (int i = 0; i < Q; ++i) v[i][j] = f[i];
   }
   const int64_t own = fpos(g, 1 + V * k, y, 0);
+  if (V * k + V <= g.nf[0] - 2) {
 #pragma unroll
-  for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), v[i]);
+    for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), v[i]);
+  } else {
+    // the last vector of a row holds ring node x = nx - 1, which the t+1 ring
+    // reconstruction writes in the same launch: middle nodes only
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      if (V * k + 1 + j > g.nf[0] - 2) continue;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) dst[pop_at<S, Q>(own + j, i)] = v[i][j];
+    }
+  }
 }
 
 // Tiles (k_fine2): a work group of HXV x HYR lanes owns the middle nodes of
@@ -1206,14 +1378,14 @@ __device__ __forceinline__ void fine2_s2(S* __restrict__ dst, const Geo& g, cons
 // calls it.
 template <int LAT, bool DEV, typename S, int MODEL, bool NT, int HXV, int HYR, bool SENS = false>
 __device__ __forceinline__ void fine2_tile(const S* __restrict__ src, S* __restrict__ dst, S* __restrict__ half,
-                                           const Geo& g, const S om, int ntx, int tile,
+                                           const Geo& g, const S om, int ntx, int tile, char* raw,
                                            double* __restrict__ su = nullptr) {
   using L = Lattice<LAT>;
   constexpr int V = VecOf<S>::V, Q = L::Q;
   constexpr int TXV = HXV - 2, TY = HYR - 2, RW = HXV * V;
   static_assert(L::D == 2, "fused fine substeps are two-dimensional");
   static_assert((HXV * HYR) % 64 == 0 && HXV * HYR <= 1024, "whole waves");
-  __shared__ S lds[Q][HYR][RW];
+  S(*lds)[HYR][RW] = reinterpret_cast<S(*)[HYR][RW]>(raw);
   const int tx = tile % ntx, ty = tile / ntx;
   const int ny = g.nf[1];
   const int nv = (g.nf[0] - 1 + V - 1) / V;
@@ -1247,15 +1419,60 @@ __host__ __device__ inline int fine2_ntx(const Geo& g, int HXV) {
 }
 __host__ __device__ inline int fine2_nty(const Geo& g, int HYR) { return (g.nf[1] - 2 + HYR - 3) / (HYR - 2); }
 
-// SENS: also the NH sensors' record of the t+1/2 iteration (fine2_s1) in su.
+// TN nodes per transfer segment of a launch of NL lanes, and its LDS: the
+// tile's t+1/2 state, which the segment's fits into.
+template <int NL>
+constexpr int fine2_nseg() {
+  return NL >= 512 ? 40 : (NL >= 256 ? 20 : 10);
+}
+template <typename S, int MODEL, int HXV, int HYR>
+constexpr int fine2_lds() {
+  constexpr int tile = 9 * HYR * HXV * 16, seg = coalesce2_lds<MODEL, S, fine2_nseg<HXV * HYR>()>();
+  constexpr int n = fine2_nseg<HXV * HYR>();
+  static_assert(5 * (2 * n + 3) <= HXV * HYR && 9 * n <= HXV * HYR, "one lane per node of a segment");
+  static_assert(seg <= tile, "a segment fits the tile's LDS");
+  return tile;
+}
+
+// Both fine substeps, the t+1 ring (Hp -> dst) and the fine-to-coarse transfer
+// in one launch: the ring and the transfer read the history, the state at t
+// and the t+1/2 ring only.  Blocks [0, ncb) take a transfer segment each (the
+// longest chains first), the next nrb `lanes` ring nodes each, the rest tiles;
+// every part is XCD-contiguous.  SENS: also the NH sensors' record of the
+// t+1/2 iteration (fine2_s1) in su; suc: that of the TN nodes (or null).
+struct Fine2Iface {
+  Iface itf;
+  const double* Hp;
+  double kf, om_f, tau_f, kc, om_c, tau_c;
+  int lanes, ncb, nrb;
+};
 template <int LAT, bool DEV, typename S, int MODEL, bool NT, int HXV, int HYR, int MINW, bool SENS = false>
 __global__ __launch_bounds__(HXV * HYR, MINW) void k_fine2(const S* __restrict__ src, S* __restrict__ dst,
-                                                         S* __restrict__ half, const Geo g, const S om, int ntx,
-                                                         int nty, int per_xcd, double* __restrict__ su) {
-  const int b = blockIdx.x;
+                                                         S* __restrict__ half, S* __restrict__ dst_c, const Geo g,
+                                                         const S om, const Fine2Iface fi, int ntx, int nty,
+                                                         int per_xcd, double* __restrict__ su,
+                                                         double* __restrict__ suc) {
+  __shared__ __attribute__((aligned(16))) char raw[fine2_lds<S, MODEL, HXV, HYR>()];
+  constexpr int NSEG = fine2_nseg<HXV * HYR>();
+  int b = blockIdx.x;
+  if (b < fi.ncb) {
+    const int seg = (b % kXCD) * (fi.ncb / kXCD) + b / kXCD;
+    if (seg >= coalesce2_count(g, NSEG)) return;  // whole work group, before any barrier
+    coalesce2_segment<LAT, DEV, S, MODEL, NSEG>(src, half, dst_c, g, om, fi.kc, fi.om_c, fi.tau_c, seg, raw, suc);
+    return;
+  }
+  b -= fi.ncb;
+  if (b < fi.nrb) {
+    if ((int)threadIdx.x >= fi.lanes) return;
+    const int64_t blk = (int64_t)(b % kXCD) * (fi.nrb / kXCD) + b / kXCD;
+    ring_body<LAT, DEV, S, MODEL, true>(fi.Hp, dst, g, fi.itf, fi.kf, fi.om_f, fi.tau_f, 0.0,
+                                        blk * fi.lanes + threadIdx.x);
+    return;
+  }
+  b -= fi.nrb;
   const int tile = (b % kXCD) * per_xcd + b / kXCD;
   if (tile >= ntx * nty) return;  // whole work group, before any barrier
-  fine2_tile<LAT, DEV, S, MODEL, NT, HXV, HYR, SENS>(src, dst, half, g, om, ntx, tile, su);
+  fine2_tile<LAT, DEV, S, MODEL, NT, HXV, HYR, SENS>(src, dst, half, g, om, ntx, tile, raw, su);
 }
 
 // The H-RR collision of one lane's vector in the D2Q9 one-pass kernels: the

@@ -432,23 +432,34 @@ struct Grid final : GridBase {
     hipLaunchKernelGGL((k_stream<LAT, DEV, S, MODEL, LEVEL, NT>), dim3((unsigned)(f.per_xcd * kXCD)), dim3(256),
                        (unsigned)kVarLds[v], s, src, dst, mac, g, f, (S)(1.0 - 1.0 / tau), xb);
   }
-  // Coarse stream (BGK, RR) and the t+1/2 ring reconstruction from G into
-  // fdst, one launch (k_stream_ring).
-  template <int MODEL>
+  // Interface nodes per work group of a launch shared with bulk work: one
+  // wave while that spreads them over the chip (each lane's chain of dependent
+  // loads and double-precision arithmetic is what such a part takes), whole
+  // work groups of `lanes` beyond.
+  static int iface_lanes(int64_t n, int lanes) { return n <= 64 * 256 ? 64 : lanes; }
+  // Coarse stream (BGK, RR), the t+1/2 ring reconstruction into fdst and, in
+  // D2Q9, the history capture, one launch (k_stream_ring).
   // su: the NH sensors' record of the coarse state it leaves (SENS), or null
+  template <int MODEL>
   void launch_stream_ring(const S* src, S* dst, S* fdst, double kf, double omf, hipStream_t s, S* xb = nullptr,
                           double* su = nullptr) {
-    const Flat f = flat(0);
-    const unsigned nrb = xblocks(itf.NR, 256);
-    const dim3 gr(nrb + (unsigned)(f.per_xcd * kXCD)), bl(256);
-    const unsigned lds = (unsigned)kVarLds[var[0]];
-    const S om = (S)(1.0 - 1.0 / tau_c);
-    if (su)
-      hipLaunchKernelGGL((k_stream_ring<LAT, DEV, S, MODEL, NT, true>), gr, bl, lds, s, src, dst, g, f, om,
-                         G.as<double>(), fdst, itf, kf, omf, tau_f, sig, (int)nrb, xb, su);
-    else
-      hipLaunchKernelGGL((k_stream_ring<LAT, DEV, S, MODEL, NT, false>), gr, bl, lds, s, src, dst, g, f, om,
-                         G.as<double>(), fdst, itf, kf, omf, tau_f, sig, (int)nrb, xb, (double*)nullptr);
+    if constexpr (MODEL != M_HRR) {
+      const Flat f = flat(0);
+      const int lanes = iface_lanes(itf.NR, 256);
+      const unsigned nrb = xblocks(itf.NR, lanes), nhb = D == 2 ? xblocks(itf.NH, lanes) : 0;
+      const dim3 gr(nrb + nhb + (unsigned)(f.per_xcd * kXCD)), bl(256);
+      const unsigned lds = (unsigned)kVarLds[var[0]];
+      const S om = (S)(1.0 - 1.0 / tau_c);
+      const double *Hm = hist[hs[0]].as<double>(), *H0 = hist[hs[1]].as<double>();
+      double* Hp = hist[hs[2]].as<double>();
+      if (su)
+        hipLaunchKernelGGL((k_stream_ring<LAT, DEV, S, MODEL, NT, true>), gr, bl, lds, s, src, dst, g, f, om,
+                           G.as<double>(), Hm, H0, Hp, fdst, itf, kf, omf, tau_f, sig, lanes, (int)nrb, (int)nhb, xb, su);
+      else
+        hipLaunchKernelGGL((k_stream_ring<LAT, DEV, S, MODEL, NT, false>), gr, bl, lds, s, src, dst, g, f, om,
+                           G.as<double>(), Hm, H0, Hp, fdst, itf, kf, omf, tau_f, sig, lanes, (int)nrb, (int)nhb, xb,
+                           (double*)nullptr);
+    }
   }
   // The t+1 ring (Hp -> fdst) and the fine-to-coarse transfer (src_f ->
   // the TN nodes of cdst), one launch (k_ring_coalesce); su as above.
@@ -459,12 +470,8 @@ struct Grid final : GridBase {
     const unsigned br2 = xblocks(itf.NR, 256), bc = xblocks(itf.NT, PER);
     const double kf = tau_f / (2.0 * tau_c), kc = 2.0 * tau_c / tau_f;
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
-    if (su)
-      hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, MODEL, true>), dim3(br2 + bc), dim3(256), 0, s, Hp, fdst, src_f,
-                         cdst, g, itf, kf, omf, tau_f, kc, omc, tau_c, sig, (int)br2, xb, su);
-    else
-      hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, MODEL, false>), dim3(br2 + bc), dim3(256), 0, s, Hp, fdst,
-                         src_f, cdst, g, itf, kf, omf, tau_f, kc, omc, tau_c, sig, (int)br2, xb, (double*)nullptr);
+    hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, MODEL>), dim3(br2 + bc), dim3(256), 0, s, Hp, fdst, src_f, cdst, g,
+                       itf, kf, omf, tau_f, kc, omc, tau_c, sig, (int)br2, xb, su);
   }
 
   // One H-RR fine substep in one pass (D2Q9, k_hrr2): variants of the fine
@@ -546,25 +553,34 @@ struct Grid final : GridBase {
                          mac, g, f, (S)(1.0 - 1.0 / tau), (S)tau, (S)sig, (S*)nullptr, (S)0, (S)0);
   }
 
-  // Both fine substeps (BGK / RR), src -> dst, t+1/2 ring and band in half.
+  // Both fine substeps (BGK / RR), src -> dst, the t+1/2 ring in half; with
+  // cdst set also the t+1 ring (into dst) and the transfer to the TN nodes of
+  // cdst (D2Q9, k_fine2).
   // D2Q9 variants of the fine role (halo-tile lanes, vectors x rows): 64 x 8,
   // 64 x 16, 32 x 16 and 32 x 8 (measured on the 4097 x 2049 patch, FP32:
   // 119, 134-147, 135 and 135 us; narrower or non-power-of-two widths and
   // 1024-lane tiles were slower still).
   // su: the NH sensors' velocity planes of the t+1/2 iteration (k_fine2
-  // SENS records them, and the whole t+1/2 state into half), or null.
+  // SENS records them, and the whole t+1/2 state into half), or null; suc:
+  // their record of the coarse TN nodes.
   template <int MODEL, int HXV, int HYR>
-  void go_fine2(const S* src, S* dst, S* half, hipStream_t s, double* su = nullptr) {
+  void go_fine2(const S* src, S* dst, S* half, S* cdst, hipStream_t s, double* su, double* suc) {
     if constexpr (D == 2 && MODEL != M_HRR) {
       const int ntx = fine2_ntx<S>(g, HXV), nty = fine2_nty(g, HYR);
       const int per = (ntx * nty + kXCD - 1) / kXCD;
-      const dim3 gr((unsigned)(per * kXCD)), bl(HXV * HYR);
+      Fine2Iface fi{itf, hist[hs[2]].as<double>(), tau_f / (2.0 * tau_c), 1.0 - 1.0 / tau_f, tau_f,
+                    2.0 * tau_c / tau_f, 1.0 - 1.0 / tau_c, tau_c, iface_lanes(itf.NR, HXV * HYR), 0, 0};
+      if (cdst) {
+        fi.ncb = (coalesce2_count(g, fine2_nseg<HXV * HYR>()) + kXCD - 1) / kXCD * kXCD;
+        fi.nrb = (int)xblocks(itf.NR, fi.lanes);
+      }
+      const dim3 gr((unsigned)(fi.ncb + fi.nrb + per * kXCD)), bl(HXV * HYR);
       if (su)
-        hipLaunchKernelGGL((k_fine2<LAT, DEV, S, MODEL, NT, HXV, HYR, 4, true>), gr, bl, 0, s, src, dst, half, g,
-                           (S)(1.0 - 1.0 / tau_f), ntx, nty, per, su);
+        hipLaunchKernelGGL((k_fine2<LAT, DEV, S, MODEL, NT, HXV, HYR, 4, true>), gr, bl, 0, s, src, dst, half, cdst, g,
+                           (S)(1.0 - 1.0 / tau_f), fi, ntx, nty, per, su, suc);
       else
-        hipLaunchKernelGGL((k_fine2<LAT, DEV, S, MODEL, NT, HXV, HYR, 4, false>), gr, bl, 0, s, src, dst, half, g,
-                           (S)(1.0 - 1.0 / tau_f), ntx, nty, per, (double*)nullptr);
+        hipLaunchKernelGGL((k_fine2<LAT, DEV, S, MODEL, NT, HXV, HYR, 4, false>), gr, bl, 0, s, src, dst, half, cdst,
+                           g, (S)(1.0 - 1.0 / tau_f), fi, ntx, nty, per, (double*)nullptr, suc);
     }
   }
   // Work decomposition of a marching kernel over ntx x nty tiles of columns
@@ -688,14 +704,15 @@ struct Grid final : GridBase {
     else launch_collide_hrr<0>(src, dst, mac, tau_c, s, hrr_lds_var(var[2]), true);
   }
   template <int MODEL>
-  void launch_fused(const S* src, S* dst, S* half, hipStream_t s, int v = -1, double* su = nullptr) {
+  void launch_fused(const S* src, S* dst, S* half, S* cdst, hipStream_t s, int v = -1, double* su = nullptr,
+                    double* suc = nullptr) {
     if (v < 0) v = var[1];
     if constexpr (D == 2) {
       switch (v) {
-        case 0: go_fine2<MODEL, 64, 8>(src, dst, half, s, su); break;
-        case 1: go_fine2<MODEL, 64, 16>(src, dst, half, s, su); break;
-        case 2: go_fine2<MODEL, 32, 16>(src, dst, half, s, su); break;
-        default: go_fine2<MODEL, 32, 8>(src, dst, half, s, su); break;
+        case 0: go_fine2<MODEL, 64, 8>(src, dst, half, cdst, s, su, suc); break;
+        case 1: go_fine2<MODEL, 64, 16>(src, dst, half, cdst, s, su, suc); break;
+        case 2: go_fine2<MODEL, 32, 16>(src, dst, half, cdst, s, su, suc); break;
+        default: go_fine2<MODEL, 32, 8>(src, dst, half, cdst, s, su, suc); break;
       }
     } else if constexpr (sizeof(S) == 4) {
       if (v == 2) go_fine3s<MODEL, 130, 7>(src, dst, half, s, 2);
@@ -754,10 +771,10 @@ struct Grid final : GridBase {
         else launch_stream<M_RR, 1>(fineA(), fineB(), nullptr, tau_f, s, fine_lds_var(v));
       }
     } else if (role == 1 && fused) {
-      // both substeps: writes the other buffer and the t+1/2 band, which the
-      // next step rewrites
-      if (model == M_BGK) launch_fused<M_BGK>(fineA(), fineB(), fbuf[2].as<S>(), s, v);
-      else launch_fused<M_RR>(fineA(), fineB(), fbuf[2].as<S>(), s, v);
+      // both substeps: writes the other buffer (D3Q19: and the t+1/2 band),
+      // which the next step rewrites
+      if (model == M_BGK) launch_fused<M_BGK>(fineA(), fineB(), fbuf[2].as<S>(), nullptr, s, v);
+      else launch_fused<M_RR>(fineA(), fineB(), fbuf[2].as<S>(), nullptr, s, v);
     } else if (role == 1) {
       if (model == M_BGK) launch_stream<M_BGK, 1>(fineA(), fineB(), nullptr, tau_f, s, v);
       else if (model == M_RR) launch_stream<M_RR, 1>(fineA(), fineB(), nullptr, tau_f, s, v);
@@ -864,10 +881,12 @@ struct Grid final : GridBase {
     constexpr int PER = 256 / (D == 2 ? 9 : 27);
     const unsigned bh = xblocks(NH, IB), br = xblocks(itf.NR, IB), bt = xblocks(itf.NT, IB);
     const unsigned bc = xblocks(itf.NT, PER), br2 = xblocks(itf.NR, 256);
-    // BGK / RR: the capture also interpolates every history value to t+1/2
-    // (G); H-RR fills its strain-rate fields later and interpolates then
-    hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
-                       MODEL == M_HRR ? nullptr : G.as<double>(), Hm, H0);
+    // D3Q19 BGK / RR: the capture also interpolates every history value to
+    // t+1/2 (G); H-RR fills its strain-rate fields later and interpolates
+    // then.  D2Q9 BGK / RR: it shares the coarse stream's launch.
+    if (D == 3 || MODEL == M_HRR)
+      hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
+                         MODEL == M_HRR ? nullptr : G.as<double>(), Hm, H0);
     timed_factor = fused_now() ? 2 : 1;
     sens_pre_half = MODEL != M_HRR && fused_now();
     // BGK / RR: the coarse record of the state this step leaves
@@ -879,8 +898,9 @@ struct Grid final : GridBase {
       // x-band copy, from which the transfer reads the x-bands
       S* xb = D == 3 ? xbuf.as<S>() : nullptr;
       launch_stream_ring<MODEL>(csrc, cdst, fH, kf, omf, s, xb, scn);
-      timed(s, [&] { launch_fused<MODEL>(fA, fB, fH, s, -1, rec_fine ? sUf.as<double>() : nullptr); });
-      launch_ring_coalesce<MODEL>(Hp, fB, fH, cdst, xb, scn, s);
+      // D2Q9: the t+1 ring and the transfer share the fused launch
+      timed(s, [&] { launch_fused<MODEL>(fA, fB, fH, cdst, s, -1, rec_fine ? sUf.as<double>() : nullptr, scn); });
+      if (D == 3) launch_ring_coalesce<MODEL>(Hp, fB, fH, cdst, xb, scn, s);
       fpar ^= 1;
     } else if (MODEL != M_HRR) {
       // substep 1 writes the ring column x = nx - 1 of B, so the t+1/2 ring
@@ -976,8 +996,9 @@ struct Grid final : GridBase {
     constexpr int IB = kIfaceBlock;
     constexpr int PER = 256 / (D == 2 ? 9 : 27);
     const unsigned bh = xblocks(NH, IB), bc = xblocks(itf.NT, PER), br2 = xblocks(itf.NR, 256);
-    hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
-                       G.as<double>(), Hm, H0);
+    if (D == 3)
+      hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
+                         G.as<double>(), Hm, H0);
     child->step(1, s);
     launch_stream_ring<MODEL>(csrc, cdst, fB, kf, omf, s, nullptr);
     child->step(1, s);
@@ -1621,7 +1642,10 @@ struct Batch final : BatchBase {
       for (int64_t c = 0; c < (nh * hfields + 63) / 64; ++c) lists[W_HTIME].push_back({sl, (int)c});
       for (int64_t c = 0; c < (nr + 63) / 64; ++c) lists[W_RING].push_back({sl, (int)c});
       for (int64_t c = 0; c < (nt + 63) / 64; ++c) lists[W_TN].push_back({sl, (int)c});
-      for (int64_t c = 0; c < (nt + PER - 1) / PER; ++c) lists[W_TNB].push_back({sl, (int)c});
+      const int64_t ntb =
+          I.fused ? coalesce2_count(I.g, tile_var == 0 ? fine2_nseg<kTileX[0] * kTileY[0]>() : fine2_nseg<kTileX[1] * kTileY[1]>())
+                  : (nt + PER - 1) / PER;
+      for (int64_t c = 0; c < ntb; ++c) lists[W_TNB].push_back({sl, (int)c});
       if (I.fused) {
         const int ntile = fine2_ntx<S>(I.g, kTileX[tile_var]) * fine2_nty(I.g, kTileY[tile_var]);
         for (int c = 0; c < ntile; ++c) lists[W_TILE].push_back({sl, c});
@@ -1884,17 +1908,26 @@ struct Batch final : BatchBase {
                        di(), items(LEVEL == 0 ? W_COARSE : W_FINE), cnt(LEVEL == 0 ? W_COARSE : W_FINE));
   }
 
-  // Fused fine phase (D2Q9 BGK / RR) in the current tile shape.
-  template <int MODEL>
-  void phase_fine2(hipStream_t s) {
+  // Work groups for list k at `per` items each (a multiple of 8).
+  unsigned groups_of(int k, int per) const {
+    return (unsigned)((item_cap[k] + (size_t)per * kXCD - 1) / ((size_t)per * kXCD) * kXCD);
+  }
+  // Fused fine phase (D2Q9 BGK / RR) in the current tile shape, with the t+1
+  // ring and the transfer unless alone is set (the tuner's trial launches).
+  template <int MODEL, int TV>
+  void go_fine2(hipStream_t s, bool alone) {
     if constexpr (D == 2 && MODEL != M_HRR) {
-      if (tile_var == 0)
-        hipLaunchKernelGGL((kb_fine2<LAT, DEV, S, MODEL, NT, kTileX[0], kTileY[0]>), grid_of(W_TILE),
-                           dim3(kTileX[0] * kTileY[0]), 0, s, di(), items(W_TILE), cnt(W_TILE));
-      else
-        hipLaunchKernelGGL((kb_fine2<LAT, DEV, S, MODEL, NT, kTileX[1], kTileY[1]>), grid_of(W_TILE),
-                           dim3(kTileX[1] * kTileY[1]), 0, s, di(), items(W_TILE), cnt(W_TILE));
+      constexpr int NL = kTileX[TV] * kTileY[TV];
+      const unsigned ncb = alone ? 0 : grid_of(W_TNB).x, nrb = alone ? 0 : groups_of(W_RING, NL / 64);
+      hipLaunchKernelGGL((kb_fine2<LAT, DEV, S, MODEL, NT, kTileX[TV], kTileY[TV]>), dim3(ncb + nrb + grid_of(W_TILE).x),
+                         dim3(NL), 0, s, di(), items(W_TNB), cnt(W_TNB), items(W_RING), cnt(W_RING), items(W_TILE),
+                         cnt(W_TILE), (int)ncb, (int)nrb);
     }
+  }
+  template <int MODEL>
+  void phase_fine2(hipStream_t s, bool alone = false) {
+    if (tile_var == 0) go_fine2<MODEL, 0>(s, alone);
+    else go_fine2<MODEL, 1>(s, alone);
   }
   // Sets the fused tile shape: every instance's tile count per row on the
   // device (that field only: the rest of a descriptor advances on the device)
@@ -1915,16 +1948,18 @@ struct Batch final : BatchBase {
   void launch_step_model(hipStream_t s) {
     using F = HF<LAT, MODEL>;
     const dim3 ib(64);
-    hipLaunchKernelGGL((kb_hist_capture<LAT, DEV, S, MODEL>), grid_of(W_HIST), ib, 0, s, di(), items(W_HIST),
-                       cnt(W_HIST));
-    if (MODEL != M_HRR) {
-      // as Grid::step_two_level: the capture interpolated G; the t+1/2 ring
-      // shares the coarse launch; the t+1 ring shares the transfer's launch
-      const unsigned nrb = grid_of(W_RING).x;
+    if (D == 3 || MODEL == M_HRR)
+      hipLaunchKernelGGL((kb_hist_capture<LAT, DEV, S, MODEL>), grid_of(W_HIST), ib, 0, s, di(), items(W_HIST),
+                         cnt(W_HIST));
+    if constexpr (MODEL != M_HRR) {
+      // as Grid::step_two_level: the t+1/2 ring shares the coarse launch (D2Q9:
+      // the history capture too; D3Q19: the capture interpolated G); the t+1
+      // ring and the transfer share a launch (D2Q9: the fused fine phase's)
       auto stream_ring = [&] {
-        hipLaunchKernelGGL((kb_stream_ring<LAT, DEV, S, MODEL, NT>), dim3(nrb + grid_of(W_COARSE).x), dim3(256),
-                           (unsigned)kVarLds[var_c], s, di(), items(W_RING), cnt(W_RING), items(W_COARSE),
-                           cnt(W_COARSE), (int)nrb);
+        const unsigned nrb = groups_of(W_RING, 4), nhb = D == 2 ? groups_of(W_HIST, 4) : 0;
+        hipLaunchKernelGGL((kb_stream_ring<LAT, DEV, S, MODEL, NT>), dim3(nrb + nhb + grid_of(W_COARSE).x), dim3(256),
+                           (unsigned)kVarLds[var_c], s, di(), items(W_RING), cnt(W_RING), items(W_HIST), cnt(W_HIST),
+                           items(W_COARSE), cnt(W_COARSE), (int)nrb, (int)nhb);
       };
       if constexpr (D == 2) {  // fused() for BGK / RR
         stream_ring();
@@ -1933,9 +1968,10 @@ struct Batch final : BatchBase {
         phase_stream<MODEL, 1, 0>(s, var_f);  // writes B's ring column: the t+1/2 ring follows
         stream_ring();
         phase_stream<MODEL, 1, 1>(s, var_f);
+        const unsigned nrb = grid_of(W_RING).x;
+        hipLaunchKernelGGL((kb_ring_coalesce<LAT, DEV, S, MODEL>), dim3(nrb + grid_of(W_TNB).x), dim3(256), 0, s, di(),
+                           items(W_RING), cnt(W_RING), items(W_TNB), cnt(W_TNB), (int)nrb);
       }
-      hipLaunchKernelGGL((kb_ring_coalesce<LAT, DEV, S, MODEL>), dim3(nrb + grid_of(W_TNB).x), dim3(256), 0, s, di(),
-                         items(W_RING), cnt(W_RING), items(W_TNB), cnt(W_TNB), (int)nrb);
     } else {
       phase_stream<M_HRR, 0, 0>(s, var_c);
       phase_stream<M_HRR, 1, 0>(s, var_f);
@@ -2009,15 +2045,15 @@ struct Batch final : BatchBase {
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     if (fused() && counts[W_FINE] > 0) {
-      // fused fine phase: one variant per tile shape (it rewrites B and the
-      // half-step buffer, which the next step rewrites)
+      // fused fine phase: one variant per tile shape (it rewrites B, which the
+      // next step rewrites)
       float best = -1.f;
       int bt = 0;
       for (int tv = 0; tv < kNTile; ++tv) {
         set_tile_var(tv);
         auto run = [&] {
-          if (collision == LBM_BGK) phase_fine2<M_BGK>(stream);
-          else phase_fine2<M_RR>(stream);
+          if (collision == LBM_BGK) phase_fine2<M_BGK>(stream, true);
+          else phase_fine2<M_RR>(stream, true);
         };
         run();
         HIPCHK(hipEventRecord(e0, stream));
