@@ -334,7 +334,8 @@ int lbm_batch_use_graph(lbm_batch_handle b, int on);
 /* Autotuner over the bulk-kernel variants of the whole batch; variants[2]
  * receives the chosen coarse and fine variant (for D2Q9 BGK / RR batches,
  * whose fine phase runs both substeps in one launch, the fine variant is its
- * tile shape: 0 = 64 x 8, 1 = 32 x 8 lanes).  Synchronous. */
+ * tile shape: 0 = 64 x 8, 1 = 32 x 8 lanes; for D2Q9 H-RR batches both are
+ * tile shapes, index modulo 2).  Synchronous. */
 int lbm_batch_tune(lbm_batch_handle b, int reps, int32_t variants[2]);
 /* Applies variants as lbm_batch_tune returns them (coarse, fine or tile
  * shape), e.g. from a stored tuning result; LBM_EINVAL when an index is out

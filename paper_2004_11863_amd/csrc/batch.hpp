@@ -41,7 +41,8 @@ struct InstDev {
   int active;
   int fpar;   // fine buffer holding the state at integer times
   int fused;  // both fine substeps in one phase (D2Q9 BGK / RR): fpar flips every step
-  int ntx;    // fused: fine tiles per row of tiles (of the batch's tile shape)
+  int ntx;    // D2Q9: fine tiles per row of tiles (of the batch's tile shape)
+  int ntxc;   // D2Q9 H-RR: coarse tiles per row of tiles
 };
 
 // Pointers read from the descriptor table are generic to the compiler, which
@@ -78,12 +79,14 @@ enum WorkKind : int {
   W_RING = 4,    // 64 ring nodes
   W_TN = 5,      // 64 TN nodes
   W_TNB = 6,     // PER TN nodes (one fine-to-coarse work group)
-  W_TILE = 7,    // fused fine tile (the batch's tile shape)
-  W_KINDS = 8
+  W_TILE = 7,    // D2Q9 fine tile (the batch's tile shape)
+  W_CTILE = 8,   // D2Q9 H-RR coarse tile
+  W_KINDS = 9
 };
 
-// Fused fine tile shapes of the batch (lanes, vectors x rows), chosen by its
-// autotuner: wide tiles suit long fine rows, narrow ones short rows.
+// D2Q9 tile shapes of the batch (lanes, vectors x rows; H-RR: of the coarse and
+// of the fine level), chosen by its autotuner: wide tiles suit long rows, narrow
+// ones short rows.
 constexpr int kNTile = 2;
 constexpr int kTileX[kNTile] = {64, 32}, kTileY[kNTile] = {8, 8};
 
@@ -317,6 +320,114 @@ __global__ __launch_bounds__(64) void kb_ring_macro(const InstDev* __restrict__ 
                             glob((S*)I.mac_f), I.g, glob(I.itf),
                             (int64_t)w.idx * 64 + threadIdx.x);
   }
+}
+
+// D2Q9 H-RR: one-pass levels, as the single grid's five launches
+// (k_capture_macro, k_hrr2, k_fict_strain_time, k_hrr2c, k_hrr2), items of 64
+// interface nodes one per wave beside tiles.
+template <int LAT, bool DEV, typename S>
+__global__ __launch_bounds__(64) void kb_capture_macro(const InstDev* __restrict__ inst, const Work* __restrict__ ritems,
+                                                       const int* __restrict__ rcount, const Work* __restrict__ hitems,
+                                                       const int* __restrict__ hcount, int nrb) {
+  const int b = blockIdx.x;
+  if (b < nrb) {
+    const int it = item_in(b, *rcount);
+    if (it < 0) return;
+    const Work w = load_item(ritems, it);
+    const InstDev& I = inst[w.inst];
+    ring_macro_half_body<LAT, DEV, S>(glob((const S*)I.ccur), glob(I.hist[I.hs[0]]), glob(I.hist[I.hs[1]]),
+                                      glob((S*)I.mac_f), I.g, glob(I.itf), (int64_t)w.idx * 64 + threadIdx.x);
+  } else {
+    const int it = item_in(b - nrb, *hcount);
+    if (it < 0) return;
+    const Work w = load_item(hitems, it);
+    const InstDev& I = inst[w.inst];
+    hist_capture_body<LAT, DEV, S, M_HRR>(glob((const S*)I.ccur), glob(I.hist[I.hs[2]]), I.g, glob(I.itf),
+                                          (int64_t)w.idx * 64 + threadIdx.x);
+  }
+}
+template <int LAT, bool DEV, typename S>
+__global__ __launch_bounds__(64) void kb_fict_strain_time(const InstDev* __restrict__ inst,
+                                                          const Work* __restrict__ titems, const int* __restrict__ tcount,
+                                                          const Work* __restrict__ hitems, const int* __restrict__ hcount,
+                                                          int nfb) {
+  const int b = blockIdx.x;
+  if (b < nfb) {
+    const int it = item_in(b, *tcount);
+    if (it < 0) return;
+    const Work w = load_item(titems, it);
+    const InstDev& I = inst[w.inst];
+    fict_body<LAT, DEV, S, S>(glob((const S*)I.fbuf[I.fpar ^ 1]), glob((S*)I.mac_c), I.g, glob(I.itf),
+                              (int64_t)w.idx * 64 + threadIdx.x);
+  } else {
+    const int it = item_in(b - nfb, *hcount);
+    if (it < 0) return;
+    const Work w = load_item(hitems, it);
+    const InstDev& I = inst[w.inst];
+    strain_time_body<LAT, DEV, S>(glob((const S*)I.ccur), glob((const S*)I.fbuf[I.fpar ^ 1]), glob(I.hist[I.hs[0]]),
+                                  glob(I.hist[I.hs[1]]), glob(I.hist[I.hs[2]]), glob(I.G), I.g, glob(I.itf),
+                                  (int64_t)w.idx * 64 + threadIdx.x);
+  }
+}
+// The coarse step beside the t+1/2 ring and the t+1 ring rho, u (blocks
+// [0, nrb) and [nrb, 2 nrb)).
+template <int LAT, bool DEV, typename S, bool NT, int HXV, int HYR>
+__global__ __launch_bounds__(HXV * HYR) void kb_hrr2c(const InstDev* __restrict__ inst, const Work* __restrict__ ritems,
+                                                      const int* __restrict__ rcount, const Work* __restrict__ items,
+                                                      const int* __restrict__ count, int nrb) {
+  __shared__ __attribute__((aligned(16))) char raw[2 * HYR * HXV * 16];
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
+  if (b < 2 * nrb) {
+    const int it = wave_item<HXV * HYR / 64>(b < nrb ? b : b - nrb, *rcount);
+    if (it < 0) return;
+    const Work w = load_item(ritems, it);
+    const InstDev& I = inst[w.inst];
+    if (b < nrb) kb_ring_item<LAT, DEV, S, M_HRR, 0>(I, w.idx, lane);
+    else
+      ring_macro_body<LAT, S>(glob(I.hist[I.hs[0]]), glob(I.hist[I.hs[1]]), glob(I.hist[I.hs[2]]), 0.0, 0.0, 1.0,
+                              glob((S*)I.mac_f), I.g, glob(I.itf), (int64_t)w.idx * 64 + lane);
+    return;
+  }
+  const int it = item_in(b - 2 * nrb, *count);
+  if (it < 0) return;  // whole work group
+  const Work w = load_item(items, it);
+  const InstDev& I = inst[w.inst];
+  hrr2c_tile<LAT, DEV, S, NT, HXV, HYR>(glob((const S*)I.ccur), glob((S*)I.cnext), glob((const S*)I.mac_c), I.g,
+                                        (S)(1.0 - 1.0 / I.tau_c), (S)I.tau_c, (S)I.sig, I.ntxc, w.idx, raw);
+}
+// A fine substep: SUB 0 A -> B; SUB 1 B -> A beside the transfer (blocks
+// [0, ncb)) and the t+1 ring (the next nrb).
+template <int LAT, bool DEV, typename S, int SUB, bool NT, int HXV, int HYR>
+__global__ __launch_bounds__(HXV * HYR) void kb_hrr2(const InstDev* __restrict__ inst, const Work* __restrict__ sitems,
+                                                     const int* __restrict__ scount, const Work* __restrict__ ritems,
+                                                     const int* __restrict__ rcount, const Work* __restrict__ items,
+                                                     const int* __restrict__ count, int ncb, int nrb) {
+  __shared__ __attribute__((aligned(16))) char raw[hrr2_lds<S, HXV, HYR>()];
+  const int b = blockIdx.x;
+  if (SUB == 1 && b < ncb) {
+    const int it = item_in(b, *scount);
+    if (it < 0) return;  // whole work group: the transfer synchronises its lanes
+    const Work w = load_item(sitems, it);
+    const InstDev& I = inst[w.inst];
+    coalesce2_table<LAT, DEV, S, M_HRR>(raw, glob((const S*)I.fbuf[I.fpar ^ 1]), glob((S*)I.cnext), I.g, glob(I.itf),
+                                        2.0 * I.tau_c / I.tau_f, 1.0 - 1.0 / I.tau_c, I.tau_c, I.sig, w.idx, nullptr,
+                                        nullptr);
+    return;
+  }
+  if (SUB == 1 && b < ncb + nrb) {
+    const int it = wave_item<HXV * HYR / 64>(b - ncb, *rcount);
+    if (it < 0) return;
+    const Work w = load_item(ritems, it);
+    kb_ring_item<LAT, DEV, S, M_HRR, 1>(inst[w.inst], w.idx, threadIdx.x & 63);
+    return;
+  }
+  const int it = item_in(b - ncb - nrb, *count);
+  if (it < 0) return;  // whole work group
+  const Work w = load_item(items, it);
+  const InstDev& I = inst[w.inst];
+  hrr2_tile<LAT, DEV, S, NT, HXV, HYR>(glob((const S*)I.fbuf[I.fpar ^ SUB]), glob((S*)I.fbuf[I.fpar ^ SUB ^ 1]),
+                                       glob((const S*)I.mac_f), I.g, (S)(1.0 - 1.0 / I.tau_f), (S)I.tau_f, (S)I.sig,
+                                       I.ntx, w.idx, raw);
 }
 
 template <int LAT, bool DEV, typename S>

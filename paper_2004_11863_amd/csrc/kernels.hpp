@@ -641,16 +641,26 @@ __global__ void k_hist_capture(const S* __restrict__ src, double* __restrict__ H
 // fictitious propagation on the fine level).
 // With PULL (the one-pass coarse H-RR path, which writes no velocity
 // planes) the velocities of the neighbours are the moments of their pulled
-// coarse state, computed here exactly as the velocity pass would (TN nodes:
-// the planes, where the fictitious propagation stored them).
+// coarse state, computed here exactly as the velocity pass would.  TN nodes:
+// the planes, where the fictitious propagation stored them, or with the fine
+// state src_f at t+1/2 that propagation itself (fict_u), so that it need not
+// run before.
+template <int LAT, bool DEV, typename T>
+__device__ __forceinline__ void fict_u(const T* __restrict__ src_f, const Geo& g, int x, int y, int z, T& rho, T* u);
 template <int LAT, bool DEV, typename T, bool PULL>
-__device__ __forceinline__ void hist_u(const T* __restrict__ src, const T* __restrict__ mac_c, const Geo& g, int x, int y,
-                                       int z, T* u) {
+__device__ __forceinline__ void hist_u(const T* __restrict__ src, const T* __restrict__ mac_c,
+                                       const T* __restrict__ src_f, const Geo& g, int x, int y, int z, T* u) {
   using L = Lattice<LAT>;
   using N = Node<LAT, DEV, T>;
   constexpr int Q = L::Q;
   const int64_t ip = cpos(g, x, y, z);
-  if (!PULL || coarse_class(g, x, y, z) == CC_TN) {
+  const bool tn = coarse_class(g, x, y, z) == CC_TN;
+  if (src_f && tn) {
+    T r;
+    fict_u<LAT, DEV, T>(src_f, g, 2 * (x - g.a[0]), 2 * (y - g.a[1]), L::D == 3 ? 2 * (z - g.a[2]) : 0, r, u);
+    return;
+  }
+  if (!PULL || tn) {
 #pragma unroll
     for (int b = 0; b < L::D; ++b) u[b] = mac_c[(1 + b) * g.Ncp + ip];
     return;
@@ -668,7 +678,8 @@ __device__ __forceinline__ void hist_u(const T* __restrict__ src, const T* __res
 }
 template <int LAT, bool DEV, typename T, bool PULL>
 __device__ __forceinline__ void hist_strain_body(const T* __restrict__ src, const T* __restrict__ mac_c,
-                                                 double* __restrict__ H, const Geo& g, const Iface& itf, int64_t h) {
+                                                 double* __restrict__ H, const Geo& g, const Iface& itf, int64_t h,
+                                                 const T* __restrict__ src_f = nullptr) {
   using L = Lattice<LAT>;
   using F = HF<LAT, M_HRR>;
   constexpr int D = L::D;
@@ -680,8 +691,8 @@ __device__ __forceinline__ void hist_strain_body(const T* __restrict__ src, cons
   for (int a = 0; a < D; ++a) {
     T up[D], um[D];
     const int ex = a == 0, ey = a == 1, ez = a == 2;
-    hist_u<LAT, DEV, T, PULL>(src, mac_c, g, wrap(x + ex, g.n[0]), wrap(y + ey, g.n[1]), wrap(z + ez, g.n[2]), up);
-    hist_u<LAT, DEV, T, PULL>(src, mac_c, g, wrap(x - ex, g.n[0]), wrap(y - ey, g.n[1]), wrap(z - ez, g.n[2]), um);
+    hist_u<LAT, DEV, T, PULL>(src, mac_c, src_f, g, wrap(x + ex, g.n[0]), wrap(y + ey, g.n[1]), wrap(z + ez, g.n[2]), up);
+    hist_u<LAT, DEV, T, PULL>(src, mac_c, src_f, g, wrap(x - ex, g.n[0]), wrap(y - ey, g.n[1]), wrap(z - ez, g.n[2]), um);
 #pragma unroll
     for (int b = 0; b < D; ++b) gr[a][b] = 0.5 * ((double)up[b] - (double)um[b]);
   }
@@ -760,6 +771,50 @@ __global__ void k_ring_macro(const double* __restrict__ Hm, const double* __rest
   ring_macro_body<LAT, T>(Hm, H0, Hp, c0, c1, c2, mac_f, g, itf, xcd_block() * blockDim.x + threadIdx.x);
 }
 
+
+// H-RR, D2Q9: the history capture at t+1 (into Hp) and the ring's rho, u at
+// t+1/2 in one launch: each ring node captures the t+1 values of its (at most
+// four) points itself, with the arithmetic of capture and ring_macro_body.
+template <int LAT, bool DEV, typename S>
+__device__ __forceinline__ void ring_macro_half_body(const S* __restrict__ src, const double* __restrict__ Hm,
+                                                     const double* __restrict__ H0, S* __restrict__ mac_f, const Geo& g,
+                                                     const Iface& itf, int64_t r) {
+  using L = Lattice<LAT>;
+  using F = HF<LAT, M_HRR>;
+  static_assert(L::D == 2, "stencils of at most four points");
+  if (r >= itf.NR) return;
+  const int np = itf.rnp[r];
+  const int32_t* pt = itf.rpt + 16 * r;
+  double v[1 + L::D];
+#pragma unroll
+  for (int k = 0; k < 1 + L::D; ++k) v[k] = 0.0;
+  for (int s = 0; s < np; ++s) {
+    const int64_t h = pt[s];
+    const double ws = ring_w(np, s);
+    double c[F::S];
+    hist_values<LAT, DEV, S, M_HRR>(src, g, itf.hnode[h], c);
+#pragma unroll
+    for (int k = 0; k < 1 + L::D; ++k) {
+      const int64_t o = (int64_t)k * itf.NH + h;
+      v[k] += ws * (-0.125 * Hm[o] + 0.75 * H0[o] + 0.375 * c[k]);
+    }
+  }
+  int x, y, z;
+  fdecode(g, itf.rnode[r], x, y, z);
+  const int64_t fi = fpos(g, x, y, z);
+#pragma unroll
+  for (int k = 0; k < 1 + L::D; ++k) mac_f[(int64_t)k * g.Nfp + fi] = (S)v[k];
+}
+// Blocks [0, nrb) take the ring, the rest the history nodes (both
+// XCD-contiguous, multiples of 8).
+template <int LAT, bool DEV, typename S>
+__global__ void k_capture_macro(const S* __restrict__ src, const double* __restrict__ Hm, const double* __restrict__ H0,
+                                double* __restrict__ Hp, S* __restrict__ mac_f, const Geo g, const Iface itf, int nrb) {
+  const int b = blockIdx.x, c = b < nrb ? b : b - nrb, per = (b < nrb ? nrb : (int)gridDim.x - nrb) / kXCD;
+  const int64_t k = ((int64_t)(c % kXCD) * per + c / kXCD) * blockDim.x + threadIdx.x;
+  if (b < nrb) ring_macro_half_body<LAT, DEV, S>(src, Hm, H0, mac_f, g, itf, k);
+  else hist_capture_body<LAT, DEV, S, M_HRR>(src, Hp, g, itf, k);
+}
 
 // Ring nodes: rho, u, the non-equilibrium part (and S) interpolated from the
 // (time-interpolated) history G; populations rebuilt as f0(rho, u) +
@@ -909,27 +964,62 @@ __device__ __forceinline__ void pull_fine(const S* __restrict__ src, const Geo& 
 
 // H-RR: fictitious propagation onto TN^f (Sec. 4.3, step e): u(TN, t+1) from
 // the fine post-collision state at t+1/2, written to the coarse macro planes.
+template <int LAT, bool DEV, typename T>
+__device__ __forceinline__ void fict_u(const T* __restrict__ src_f, const Geo& g, int x, int y, int z, T& rho, T* u) {
+  using L = Lattice<LAT>;
+  double f[L::Q], r, r0, v[3];
+  pull_fine<LAT, DEV, T>(src_f, g, x, y, z, f);
+  Node<LAT, false, double>::moments(f, r, r0, v);
+  rho = (T)r;
+#pragma unroll
+  for (int d = 0; d < L::D; ++d) u[d] = (T)v[d];
+}
 template <int LAT, bool DEV, typename S, typename T>
 __device__ __forceinline__ void fict_body(const S* __restrict__ src_f, T* __restrict__ mac_c, const Geo& g, const Iface& itf,
                                  int64_t t) {
   using L = Lattice<LAT>;
-  using N = Node<LAT, false, double>;
   if (t >= itf.NT) return;
   int x, y, z;
   fdecode(g, itf.tnf[t], x, y, z);
-  double f[L::Q], rho, r0, u[3];
-  pull_fine<LAT, DEV, S>(src_f, g, x, y, z, f);
-  N::moments(f, rho, r0, u);
+  T rho, u[3];
+  fict_u<LAT, DEV, T>(src_f, g, x, y, z, rho, u);
   int cx, cy, cz;
   cdecode(g, itf.tnc[t], cx, cy, cz);
   const int64_t ci = cpos(g, cx, cy, cz);
-  mac_c[ci] = (T)rho;
+  mac_c[ci] = rho;
 #pragma unroll
-  for (int d = 0; d < L::D; ++d) mac_c[(int64_t)(1 + d) * g.Ncp + ci] = (T)u[d];
+  for (int d = 0; d < L::D; ++d) mac_c[(int64_t)(1 + d) * g.Ncp + ci] = u[d];
 }
 template <int LAT, bool DEV, typename S, typename T>
 __global__ void k_fict(const S* __restrict__ src_f, T* __restrict__ mac_c, const Geo g, const Iface itf) {
   fict_body<LAT, DEV, S, T>(src_f, mac_c, g, itf, xcd_block() * blockDim.x + threadIdx.x);
+}
+// One-pass coarse H-RR: the fictitious propagation (blocks [0, nfb)) beside the
+// strain rate and temporal interpolation of the history nodes (the rest),
+// which propagate the TN velocities they need themselves.
+template <int LAT, bool DEV, typename T>
+__device__ __forceinline__ void strain_time_body(const T* __restrict__ src, const T* __restrict__ src_f,
+                                                 const double* __restrict__ Hm, const double* __restrict__ H0,
+                                                 double* __restrict__ Hp, double* __restrict__ G, const Geo& g,
+                                                 const Iface& itf, int64_t h) {
+  using F = HF<LAT, M_HRR>;
+  if (h >= itf.NH) return;
+  hist_strain_body<LAT, DEV, T, true>(src, nullptr, Hp, g, itf, h, src_f);
+#pragma unroll
+  for (int f = 0; f < F::N; ++f) {
+    const int64_t k = (int64_t)f * itf.NH + h;
+    G[k] = time_half(Hm[k], H0[k], Hp[k]);
+  }
+}
+template <int LAT, bool DEV, typename T>
+__global__ void k_fict_strain_time(const T* __restrict__ src, const T* __restrict__ src_f, T* __restrict__ mac_c,
+                                   const double* __restrict__ Hm, const double* __restrict__ H0,
+                                   double* __restrict__ Hp, double* __restrict__ G, const Geo g, const Iface itf,
+                                   int nfb) {
+  const int b = blockIdx.x, c = b < nfb ? b : b - nfb, per = (b < nfb ? nfb : (int)gridDim.x - nfb) / kXCD;
+  const int64_t k = ((int64_t)(c % kXCD) * per + c / kXCD) * blockDim.x + threadIdx.x;
+  if (b < nfb) fict_body<LAT, DEV, T, T>(src_f, mac_c, g, itf, k);
+  else strain_time_body<LAT, DEV, T>(src, src_f, Hm, H0, Hp, G, g, itf, k);
 }
 
 
@@ -940,17 +1030,17 @@ __global__ void k_fict(const S* __restrict__ src_f, T* __restrict__ mac_c, const
 // (eq filterFneq), rescaled by 2 tau_c / tau_f (eq rescfc) and added to f0
 // of the co-located fine node; H-RR takes S^c = 2 S^f (eq PijResc) with S^f
 // by fine centred differences.  The coarse node is then collided with tau_c.
-// A work group handles up to PER TN nodes (cnt of them live): lane (stencil
+// D2Q9: a work group handles up to PER TN nodes (cnt of them live): lane (stencil
 // point s, TN node t), t fastest so neighbouring lanes read neighbouring
 // nodes, computes the weighted non-equilibrium part of one stencil node into
 // LDS; lanes per (TN node, component) sum the stencil in a fixed order; one
-// lane per TN node rebuilds and collides.  pull(t, ox, oy, oz, f) gives the
-// populations that arrive at the stencil node, tnode(t, cx, cy, cz) the coarse
+// lane per TN node rebuilds and collides.  pull(t, ox, oy, f) gives the
+// populations that arrive at the stencil node, tnode(t, cx, cy) the coarse
 // TN node; raw: LDS of coalesce_lds() bytes.  su: the node's record for the
 // NH sensors, as in stream_body, or null.
 template <int LAT, int MODEL, int PER>
 constexpr int coalesce_lds() {
-  constexpr int NST = Lattice<LAT>::D == 2 ? 9 : 27, NC = HF<LAT, MODEL>::NF1;
+  constexpr int NST = 9, NC = HF<LAT, MODEL>::NF1;
   return (int)sizeof(double) * PER * (NST * (NC + 4) + NC);
 }
 template <int LAT, bool DEV, typename S, int MODEL, int PER, typename PullF, typename NodeF>
@@ -960,20 +1050,19 @@ __device__ __forceinline__ void coalesce_nodes(char* raw, int cnt, PullF&& pull,
   using L = Lattice<LAT>;
   using N = Node<LAT, false, double>;
   using F = HF<LAT, MODEL>;
-  constexpr int Q = L::Q, D = L::D;
-  constexpr int NST = (D == 2) ? 9 : 27;
-  constexpr int CEN = (D == 2) ? 4 : 13;
+  constexpr int Q = L::Q, D = L::D, NST = 9, CEN = 4;
+  static_assert(D == 2, "D3Q19: coalesce3_tile");
   constexpr int NC = F::NF1;  // components filtered per stencil node
   double(*sf1)[NST][NC] = reinterpret_cast<double(*)[NST][NC]>(raw);
   double(*sm)[NST][4] = reinterpret_cast<double(*)[NST][4]>(raw + sizeof(double) * PER * NST * NC);
   double(*sacc)[NC] = reinterpret_cast<double(*)[NC]>(raw + sizeof(double) * PER * NST * (NC + 4));
   const int lt = threadIdx.x % PER, s = threadIdx.x / PER;
   if (s < NST && lt < cnt) {
-    const int ox = s % 3 - 1, oy = (s / 3) % 3 - 1, oz = (D == 3) ? s / 9 - 1 : 0;
+    const int ox = s % 3 - 1, oy = s / 3 - 1;
     double f[Q], rho, r0, u[3];
-    pull(lt, ox, oy, oz, f);
+    pull(lt, ox, oy, f);
     N::moments(f, rho, r0, u);
-    const double w = (ox ? 0.25 : 0.5) * (oy ? 0.25 : 0.5) * (D == 3 ? (oz ? 0.25 : 0.5) : 1.0);
+    const double w = (ox ? 0.25 : 0.5) * (oy ? 0.25 : 0.5);
     if (MODEL == M_BGK) {
       double f0[Q];
       N::feq(rho, r0, u, f0);
@@ -1011,8 +1100,8 @@ __device__ __forceinline__ void coalesce_nodes(char* raw, int cnt, PullF&& pull,
   } else {
     Sym<double> a = sym_get<D>(sacc[l3], kc);
     if (MODEL == M_HRR) {
-      // neighbours along +-x, +-y, +-z are stencil entries CEN +- 1, 3, 9
-      const int st[3] = {1, 3, 9};
+      // neighbours along +-x, +-y are stencil entries CEN +- 1, 3
+      const int st[3] = {1, 3, 0};
       double gr[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
       for (int aa = 0; aa < D; ++aa)
         for (int b = 0; b < D; ++b) gr[aa][b] = 0.5 * (sm[l3][CEN + st[aa]][1 + b] - sm[l3][CEN - st[aa]][1 + b]);
@@ -1026,9 +1115,9 @@ __device__ __forceinline__ void coalesce_nodes(char* raw, int cnt, PullF&& pull,
     }
     N::regular(rc, rc, uc, om_c, a, f);
   }
-  int cx, cy, cz;
-  tnode(l3, cx, cy, cz);
-  const int64_t ci = cpos(g, cx, cy, cz);
+  int cx, cy;
+  tnode(l3, cx, cy);
+  const int64_t ci = cpos(g, cx, cy, 0);
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const S st = store_pop<S, DEV, LAT>(f[i], i);
@@ -1043,27 +1132,196 @@ __device__ __forceinline__ void coalesce_nodes(char* raw, int cnt, PullF&& pull,
   }
 }
 
-// The TN nodes [blk PER, (blk + 1) PER) of the table, from the fine state
-// src_f (and the compact copy xb of its x-bands); the whole work group of 256
-// lanes calls it.
+// D3Q19: the TN shell is cut into tiles of 8 x 2 TN nodes on its six faces (a
+// z face holds its edges, a y face its x edges), one work group of 256 lanes
+// each.  The stencils of neighbouring TN nodes overlap (they are two fine
+// nodes apart), so the tile's 17 x 5 x 3 fine nodes are pulled once each, one
+// lane per node in memory order, and their density, velocity and
+// non-equilibrium part shared through LDS: 16 pulls per TN node instead of the
+// 27 of one stencil per node, in rows of up to 17 nodes.  Bound by the latency
+// and the line granularity of those pulls.
+constexpr int kTnU = 8, kTnV = 2, kTnNodes = (2 * kTnU + 1) * (2 * kTnV + 1) * 3;
+// Tiles of one face with normal axis w (0, 1, 2) along its two axes: the TN
+// nodes of a z face are x, y in [1, m - 1], of a y face x in [1, m - 1] and z
+// in [2, m - 2], of an x face y, z in [2, m - 2].
+__host__ __device__ inline int tn_nu(const Geo& g, int w) { return w == 0 ? g.m[1] - 3 : g.m[0] - 1; }
+__host__ __device__ inline int tn_nv(const Geo& g, int w) { return w == 2 ? g.m[1] - 1 : g.m[2] - 3; }
+__host__ __device__ inline int tn_face_tiles(const Geo& g, int w) {
+  return ((tn_nu(g, w) + kTnU - 1) / kTnU) * ((tn_nv(g, w) + kTnV - 1) / kTnV);
+}
+__host__ __device__ inline int tn_tiles(const Geo& g) {
+  return 2 * (tn_face_tiles(g, 0) + tn_face_tiles(g, 1) + tn_face_tiles(g, 2));
+}
+template <int LAT, bool DEV, typename S, int MODEL>
+__device__ __forceinline__ void coalesce3_tile(const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g,
+                                               double kc, double om_c, double tau_c, double sig, int64_t blk,
+                                               const S* __restrict__ xb, double* __restrict__ su) {
+  using L = Lattice<LAT>;
+  using N = Node<LAT, false, double>;
+  using F = HF<LAT, MODEL>;
+  constexpr int Q = L::Q, NC = F::NF1, PER = kTnU * kTnV;
+  static_assert(L::D == 3 && kTnNodes <= 256, "one lane per fine node of a tile");
+  __shared__ double ne[NC][kTnNodes], mo[4][kTnNodes], sacc[NC][PER];
+  // face and tile (scalars, not arrays indexed by the axis: those would live
+  // in scratch memory)
+  const int n2 = tn_face_tiles(g, 2), n1 = tn_face_tiles(g, 1), n0 = tn_face_tiles(g, 0);
+  int t = (int)blk, w, nt;
+  if (t < 2 * n2) {
+    w = 2;
+    nt = n2;
+  } else if (t < 2 * (n2 + n1)) {
+    w = 1;
+    nt = n1;
+    t -= 2 * n2;
+  } else if (t < 2 * (n2 + n1 + n0)) {
+    w = 0;
+    nt = n0;
+    t -= 2 * (n2 + n1);
+  } else {
+    return;  // whole work group
+  }
+  const int side = t / nt;
+  t -= side * nt;
+  const int tu = (tn_nu(g, w) + kTnU - 1) / kTnU, iv = t / tu, iu = t - iv * tu;
+  const int nu = min(kTnU, tn_nu(g, w) - kTnU * iu), nv = min(kTnV, tn_nv(g, w) - kTnV * iv);
+  const int cnt = nu * nv;
+  // first TN node (patch vertices), extent of the pulled box (its first fine
+  // node is one before), LDS strides (x fastest)
+  const int cu = kTnU * iu + (w == 0 ? 2 : 1), cv = kTnV * iv + (w == 2 ? 1 : 2);
+  const int mw = w == 2 ? g.m[2] : (w == 1 ? g.m[1] : g.m[0]), cw = side == 0 ? 1 : mw - 1;
+  const int eu = 2 * nu + 1, ev = 2 * nv + 1;
+  const int cx0 = w == 0 ? cw : cu, cy0 = w == 0 ? cu : (w == 1 ? cw : cv), cz0 = w == 2 ? cw : cv;
+  const int ex = w == 0 ? 3 : eu, ey = w == 0 ? eu : (w == 1 ? 3 : ev);
+  const int sy = ex, sz = ex * ey, total = 3 * eu * ev;
+  const int su_ = w == 0 ? sy : 1, sv_ = w == 2 ? sy : sz, sw_ = w == 2 ? sz : (w == 1 ? sy : 1);
+  const int p = threadIdx.x;
+  if (p < total) {
+    const int pz = p / sz, py = (p - pz * sz) / sy, px = p - pz * sz - py * sy;
+    double f[Q], rho, r0, uu[3];
+    pull_fine<LAT, DEV, S>(src_f, g, 2 * cx0 - 1 + px, 2 * cy0 - 1 + py, 2 * cz0 - 1 + pz, f, xb);
+    N::moments(f, rho, r0, uu);
+    if (MODEL == M_BGK) {
+      double f0[Q];
+      N::feq(rho, r0, uu, f0);
+#pragma unroll
+      for (int i = 0; i < Q; ++i) ne[i][p] = f[i] - f0[i];
+    } else {
+      double a[NS<3>::value];
+      sym_put<3>(a1_of<LAT>(f, rho, uu), a, 1.0);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) ne[k][p] = a[k];
+    }
+    mo[0][p] = rho;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) mo[1 + d][p] = uu[d];
+  }
+  __syncthreads();
+  // node (i, j) of the tile sits at i = l % nu, j = l / nu
+  auto centre = [&](int l) __attribute__((always_inline)) {
+    const int j = l / nu, i = l - j * nu;
+    return sw_ + (1 + 2 * i) * su_ + (1 + 2 * j) * sv_;
+  };
+  for (int k = p; k < cnt * NC; k += 256) {
+    const int q = k / cnt, l = k - q * cnt, c = centre(l);
+    double acc = 0.0;
+    for (int s = 0; s < 27; ++s) {
+      const int ox = s % 3 - 1, oy = (s / 3) % 3 - 1, oz = s / 9 - 1;
+      const double wt = (ox ? 0.25 : 0.5) * (oy ? 0.25 : 0.5) * (oz ? 0.25 : 0.5);
+      acc += wt * ne[q][c + ox + oy * sy + oz * sz];
+    }
+    sacc[q][l] = acc;
+  }
+  __syncthreads();
+  if (p >= cnt) return;
+  const int c = centre(p);
+  const double rc = mo[0][c];
+  double uc[3] = {mo[1][c], mo[2][c], mo[3][c]};
+  double f[Q], av[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) av[k] = sacc[k][p];
+  if (MODEL == M_BGK) {
+    N::feq(rc, rc, uc, f);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) f[i] += kc * av[i];
+    N::collide(f, M_BGK, om_c, tau_c, sig, nullptr);
+  } else {
+    Sym<double> a = sym_get<3>(av, kc);
+    if (MODEL == M_HRR) {
+      double gr[3][3];
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        gr[0][b] = 0.5 * (mo[1 + b][c + 1] - mo[1 + b][c - 1]);
+        gr[1][b] = 0.5 * (mo[1 + b][c + sy] - mo[1 + b][c - sy]);
+        gr[2][b] = 0.5 * (mo[1 + b][c + sz] - mo[1 + b][c - sz]);
+      }
+      const Sym<double> Sc{2.0 * gr[0][0],
+                           2.0 * gr[1][1],
+                           2.0 * gr[2][2],
+                           2.0 * (0.5 * (gr[0][1] + gr[1][0])),
+                           2.0 * (0.5 * (gr[0][2] + gr[2][0])),
+                           2.0 * (0.5 * (gr[1][2] + gr[2][1]))};
+      a = hrr_mix(a, Sc, sig, tau_c, rc);
+    }
+    N::regular(rc, rc, uc, om_c, a, f);
+  }
+  const int jv = p / nu, ju = p - jv * nu;
+  const int64_t ci = cpos(g, g.a[0] + cx0 + (w == 0 ? 0 : ju), g.a[1] + cy0 + (w == 0 ? ju : (w == 2 ? jv : 0)),
+                          g.a[2] + cz0 + (w == 2 ? 0 : jv));
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const S sv = store_pop<S, DEV, LAT>(f[i], i);
+    dst_c[pop_at<S, Q>(ci, i)] = sv;
+    f[i] = full_pop<S, DEV, LAT>(sv, i);
+  }
+  if (su) {
+    double r, r0, us[3];
+    N::moments(f, r, r0, us);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) su[(int64_t)(1 + d) * g.Ncp + ci] = us[d];
+  }
+}
+
+// D2Q9: the TN nodes [blk kTn2, (blk + 1) kTn2) of the table; a whole work
+// group of 9 kTn2 lanes or more calls it.
+constexpr int kTn2 = 256 / 9;
+template <int LAT, bool DEV, typename S, int MODEL>
+__device__ __forceinline__ void coalesce2_table(char* raw, const S* __restrict__ src_f, S* __restrict__ dst_c,
+                                                const Geo& g, const Iface& itf, double kc, double om_c, double tau_c,
+                                                double sig, int64_t blk, const S* __restrict__ xb,
+                                                double* __restrict__ su) {
+  const int64_t t0 = blk * kTn2;
+  const int cnt = (int)min((int64_t)kTn2, itf.NT - t0);
+  if (cnt <= 0) return;  // whole work group
+  coalesce_nodes<LAT, DEV, S, MODEL, kTn2>(
+      raw, cnt,
+      [&](int lt, int ox, int oy, double* f) __attribute__((always_inline)) {
+        int x, y, z;
+        fdecode(g, itf.tnf[t0 + lt], x, y, z);
+        pull_fine<LAT, DEV, S>(src_f, g, x + ox, y + oy, z, f, xb);
+      },
+      [&](int lt, int& cx, int& cy) __attribute__((always_inline)) {
+        int cz;
+        cdecode(g, itf.tnc[t0 + lt], cx, cy, cz);
+      },
+      dst_c, g, kc, om_c, tau_c, sig, su);
+}
+// Work groups of the transfer of one level.
+__host__ __device__ inline int coalesce_blocks(const Geo& g, int64_t NT) {
+  return g.D == 3 ? tn_tiles(g) : (int)((NT + kTn2 - 1) / kTn2);
+}
+// Work group blk of the transfer from the fine state src_f (and the compact
+// copy xb of its x-bands): a tile (D3Q19), or the TN nodes [blk PER, (blk + 1)
+// PER) of the table; the whole work group of 256 lanes calls it.
 template <int LAT, bool DEV, typename S, int MODEL>
 __device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g, const Iface& itf,
                                      double kc, double om_c, double tau_c, double sig, int64_t blk,
                                      const S* __restrict__ xb = nullptr, double* __restrict__ su = nullptr) {
-  constexpr int PER = 256 / (Lattice<LAT>::D == 2 ? 9 : 27);
-  __shared__ __attribute__((aligned(16))) char raw[coalesce_lds<LAT, MODEL, PER>()];
-  const int64_t t0 = blk * PER;
-  const int cnt = (int)min((int64_t)PER, itf.NT - t0);
-  if (cnt <= 0) return;  // whole work group
-  coalesce_nodes<LAT, DEV, S, MODEL, PER>(
-      raw, cnt,
-      [&](int lt, int ox, int oy, int oz, double* f) __attribute__((always_inline)) {
-        int x, y, z;
-        fdecode(g, itf.tnf[t0 + lt], x, y, z);
-        pull_fine<LAT, DEV, S>(src_f, g, x + ox, y + oy, z + oz, f, xb);
-      },
-      [&](int lt, int& cx, int& cy, int& cz) __attribute__((always_inline)) { cdecode(g, itf.tnc[t0 + lt], cx, cy, cz); },
-      dst_c, g, kc, om_c, tau_c, sig, su);
+  if constexpr (Lattice<LAT>::D == 3) {
+    coalesce3_tile<LAT, DEV, S, MODEL>(src_f, dst_c, g, kc, om_c, tau_c, sig, blk, xb, su);
+  } else {
+    __shared__ __attribute__((aligned(16))) char raw[coalesce_lds<LAT, MODEL, kTn2>()];
+    coalesce2_table<LAT, DEV, S, MODEL>(raw, src_f, dst_c, g, itf, kc, om_c, tau_c, sig, blk, xb, su);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1142,15 +1400,14 @@ __device__ __forceinline__ void coalesce2_segment(const S* __restrict__ src, con
   __syncthreads();
   coalesce_nodes<LAT, DEV, S, MODEL, NSEG>(
       rest, cnt,
-      [&](int lt, int ox, int oy, int, double* f) __attribute__((always_inline)) {
+      [&](int lt, int ox, int oy, double* f) __attribute__((always_inline)) {
         const int c = (2 + ox + (hor ? 2 * lt : 0)) + pw * (2 + oy + (hor ? 0 : 2 * lt));
 #pragma unroll
         for (int i = 0; i < Q; ++i) f[i] = full_pop<S, DEV, LAT>(st[i][c - L::cx(i) - pw * L::cy(i)], i);
       },
-      [&](int lt, int& cx, int& cy, int& cz) __attribute__((always_inline)) {
+      [&](int lt, int& cx, int& cy) __attribute__((always_inline)) {
         cx = g.a[0] + (tx0 + (hor ? 2 * lt : 0)) / 2;
         cy = g.a[1] + (ty0 + (hor ? 0 : 2 * lt)) / 2;
-        cz = 0;
       },
       dst_c, g, kc, om_c, tau_c, 0.0, su);
 }
@@ -1419,6 +1676,13 @@ __host__ __device__ inline int fine2_ntx(const Geo& g, int HXV) {
 }
 __host__ __device__ inline int fine2_nty(const Geo& g, int HYR) { return (g.nf[1] - 2 + HYR - 3) / (HYR - 2); }
 
+// Tiles of the one-pass coarse H-RR level.
+template <typename S>
+__host__ __device__ inline int hrr2c_ntx(const Geo& g, int HXV) {
+  return ((g.n[0] + VecOf<S>::V - 1) / VecOf<S>::V + HXV - 3) / (HXV - 2);
+}
+__host__ __device__ inline int hrr2c_nty(const Geo& g, int HYR) { return (g.n[1] + HYR - 3) / (HYR - 2); }
+
 // TN nodes per transfer segment of a launch of NL lanes, and its LDS: the
 // tile's t+1/2 state, which the segment's fits into.
 template <int NL>
@@ -1542,7 +1806,7 @@ __device__ __forceinline__ void dyn2_collide(typename VT<S, VecOf<S>::V>::a* v, 
 template <int LAT, bool DEV, typename S, bool NT, int HXV, int HYR, bool DYN = false>
 __device__ __forceinline__ void hrr2_tile(const S* __restrict__ src, S* __restrict__ dst, const S* __restrict__ mac,
                                           const Geo& g, const S om, const S tau, const S sig, int ntx, int tile,
-                                          S* __restrict__ dyn = nullptr, const S sig_dyn = S(0),
+                                          char* raw, S* __restrict__ dyn = nullptr, const S sig_dyn = S(0),
                                           const S dthr = S(0)) {
   using L = Lattice<LAT>;
   using N = Node<LAT, DEV, S>;
@@ -1550,7 +1814,7 @@ __device__ __forceinline__ void hrr2_tile(const S* __restrict__ src, S* __restri
   using VA = typename VT<S, V>::a;
   constexpr int TXV = HXV - 2, TY = HYR - 2, RW = HXV * V;
   static_assert(L::D == 2, "the one-pass H-RR tile is two-dimensional");
-  __shared__ S lu[2][HYR][RW];
+  S(*lu)[HYR][RW] = reinterpret_cast<S(*)[HYR][RW]>(raw);
   const int tx = tile % ntx, ty = tile / ntx;
   const int nx = g.nf[0], ny = g.nf[1];
   const int nv = (nx - 1 + V - 1) / V;
@@ -1605,19 +1869,32 @@ __device__ __forceinline__ void hrr2_tile(const S* __restrict__ src, S* __restri
   const int c = rv * V;
   const int64_t own = fpos(g, x0, y, 0);
   dyn2_collide<LAT, DEV, S, DYN>(v, lu[0], lu[1], rr, c, om, tau, sig, dyn, g.Nfp, own, sig_dyn, dthr);
+  if (x0 + V - 1 <= nx - 2) {
 #pragma unroll
-  for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), v[i]);
+    for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), v[i]);
+  } else {
+    // the last vector of a row holds ring node x = nx - 1, which the ring
+    // reconstruction may write in the same launch: middle nodes only
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      if (x0 + j > nx - 2) continue;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) dst[pop_at<S, Q>(own + j, i)] = v[i][j];
+    }
+  }
 }
 
-// The coarse level in one pass (D2Q9 H-RR; rows a whole number of vectors):
-// as hrr2_tile, periodic -- halo lanes take the wrapped neighbour vector and
-// row -- with the velocity of TN nodes from the velocity planes (the
-// fictitious propagation stored it there) and vectors wholly inside the
-// covered box skipped, as k_collide_hrr does.
+// The coarse level in one pass (D2Q9 H-RR): as hrr2_tile, periodic -- halo
+// lanes take the neighbouring vectors and rows across the period; a vector
+// that reaches past either row end (halo lanes, and the last vector of rows
+// that are no whole number of vectors) takes its nodes one by one -- with the
+// velocity of TN nodes from the velocity planes (the fictitious propagation
+// stored it there) and vectors wholly inside the covered box skipped, as
+// k_collide_hrr does.
 template <int LAT, bool DEV, typename S, bool NT, int HXV, int HYR, bool DYN = false>
 __device__ __forceinline__ void hrr2c_tile(const S* __restrict__ src, S* __restrict__ dst, const S* __restrict__ mac,
                                            const Geo& g, const S om, const S tau, const S sig, int ntx, int tile,
-                                           S* __restrict__ dyn = nullptr, const S sig_dyn = S(0),
+                                           char* raw, S* __restrict__ dyn = nullptr, const S sig_dyn = S(0),
                                            const S dthr = S(0)) {
   using L = Lattice<LAT>;
   using N = Node<LAT, DEV, S>;
@@ -1625,17 +1902,18 @@ __device__ __forceinline__ void hrr2c_tile(const S* __restrict__ src, S* __restr
   using VA = typename VT<S, V>::a;
   constexpr int TXV = HXV - 2, TY = HYR - 2, RW = HXV * V;
   static_assert(L::D == 2, "the one-pass H-RR tile is two-dimensional");
-  __shared__ S lu[2][HYR][RW];
+  S(*lu)[HYR][RW] = reinterpret_cast<S(*)[HYR][RW]>(raw);
   const int tx = tile % ntx, ty = tile / ntx;
   const int nx = g.n[0], ny = g.n[1];
-  const int nv = nx / V;
+  const int nv = (nx + V - 1) / V;
   const int64_t NP = g.Ncp;
   const int t = threadIdx.x;
   const int rv = t % HXV, rr = t / HXV;
   const int kr = tx * TXV - 1 + rv, yr = ty * TY - 1 + rr;  // unwrapped vector and row (>= -1)
-  const int k = (kr + nv) % nv, y = (yr + ny) % ny;          // a tile may be wider than the period
-  const int x0 = V * k;
-  const bool skip = skip_vec<0>(g, x0, V, y, 0, nx);
+  const int y = (yr + ny) % ny;                              // a tile may be wider than the period
+  const int x0 = V * kr;
+  const bool edge = x0 < 0 || x0 + V > nx;
+  const bool skip = !edge && skip_vec<0>(g, x0, V, y, 0, nx);
   const bool inner = rr >= 1 && rr <= TY && rv >= 1 && rv <= TXV && kr < nv && yr < ny && !skip;
   VA v[Q];
   // a skipped (wholly covered) vector stores zero velocities: only its TN
@@ -1643,12 +1921,25 @@ __device__ __forceinline__ void hrr2c_tile(const S* __restrict__ src, S* __restr
   // covered nodes are not evolved), but every slot a lane reads is defined
   VA ux = VA(S(0)), uy = VA(S(0));
   if (!skip) {
-    const Pull<S, Q, V, 0, 2> pl(g.pc, 0, x0, y, 0, nx, ny, 1);
-    pl.template load_all<L>(src, v);
+    if (!edge) {
+      const Pull<S, Q, V, 0, 2> pl(g.pc, 0, x0, y, 0, nx, ny, 1);
+      pl.template load_all<L>(src, v);
+    } else {
+      static_for<Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const int ys = wrap(y - L::cy(i), ny);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+          const int xs = (x0 + j - L::cx(i) + 2 * nx) % nx;
+          v[i][j] = src[pop_at<S, Q>(cpos(g, xs, ys, 0), i)];
+        }
+      });
+    }
 #pragma unroll
     for (int j = 0; j < V; ++j) {
-      if (coarse_class(g, x0 + j, y, 0) == CC_TN) {
-        const int64_t p = cpos(g, x0 + j, y, 0);
+      const int x = edge ? (x0 + j + 2 * nx) % nx : x0 + j;
+      if (coarse_class(g, x, y, 0) == CC_TN) {
+        const int64_t p = cpos(g, x, y, 0);
         ux[j] = mac[NP + p];
         uy[j] = mac[2 * NP + p];
       } else {
@@ -1668,31 +1959,77 @@ __device__ __forceinline__ void hrr2c_tile(const S* __restrict__ src, S* __restr
   const int c = rv * V;
   const int64_t own = cpos(g, x0, y, 0);
   dyn2_collide<LAT, DEV, S, DYN>(v, lu[0], lu[1], rr, c, om, tau, sig, dyn, g.Ncp, own, sig_dyn, dthr);
+  // (the last vector of a ragged row reaches into the row's padding)
 #pragma unroll
   for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), v[i]);
+}
+
+// Interface work that shares a launch with the D2Q9 H-RR tiles, in work groups
+// of `lanes` nodes each: beside the coarse step (k_hrr2c) the t+1/2 ring (G ->
+// half) and the t+1 ring velocities (Hp -> mac_f), nrb groups each; beside the
+// second fine substep (k_hrr2) the transfer (the t+1/2 state -> the TN nodes
+// of dst_c, ncb groups, first) and the t+1 ring (Hp -> the substep's output).
+// Every part is XCD-contiguous; none reads what another part of its launch
+// writes.
+template <typename S>
+struct Hrr2Iface {
+  Iface itf;
+  const double *G, *Hm, *H0, *Hp;
+  S *half, *mac_f, *dst_c;
+  double kf, om_f, tau_f, kc, om_c, tau_c, sig;
+  int lanes, ncb, nrb;
+};
+template <typename S, int HXV, int HYR>
+constexpr int hrr2_lds() {
+  constexpr int tile = 2 * HYR * HXV * 16, tn = coalesce_lds<0, M_HRR, kTn2>();
+  return tile > tn ? tile : tn;
 }
 
 // DYN: dynamic sigma (dyn, sig_dyn, dthr as for k_collide_hrr).
 template <int LAT, bool DEV, typename S, bool NT, int HXV, int HYR, bool DYN = false>
 __global__ __launch_bounds__(HXV * HYR) void k_hrr2c(const S* __restrict__ src, S* __restrict__ dst,
                                                      const S* __restrict__ mac, const Geo g, const S om, const S tau,
-                                                     const S sig, int ntx, int nty, int per_xcd, S* __restrict__ dyn,
-                                                     const S sig_dyn, const S dthr) {
-  const int b = blockIdx.x;
+                                                     const S sig, const Hrr2Iface<S> fi, int ntx, int nty, int per_xcd,
+                                                     S* __restrict__ dyn, const S sig_dyn, const S dthr) {
+  __shared__ __attribute__((aligned(16))) char raw[2 * HYR * HXV * 16];
+  int b = blockIdx.x;
+  if (b < 2 * fi.nrb) {
+    if ((int)threadIdx.x >= fi.lanes) return;
+    const int c = b < fi.nrb ? b : b - fi.nrb;
+    const int64_t r = ((int64_t)(c % kXCD) * (fi.nrb / kXCD) + c / kXCD) * fi.lanes + threadIdx.x;
+    if (b < fi.nrb) ring_body<LAT, DEV, S, M_HRR, true>(fi.G, fi.half, g, fi.itf, fi.kf, fi.om_f, fi.tau_f, fi.sig, r);
+    else ring_macro_body<LAT, S>(fi.Hm, fi.H0, fi.Hp, 0.0, 0.0, 1.0, fi.mac_f, g, fi.itf, r);
+    return;
+  }
+  b -= 2 * fi.nrb;
   const int tile = (b % kXCD) * per_xcd + b / kXCD;
   if (tile >= ntx * nty) return;  // whole work group, before any barrier
-  hrr2c_tile<LAT, DEV, S, NT, HXV, HYR, DYN>(src, dst, mac, g, om, tau, sig, ntx, tile, dyn, sig_dyn, dthr);
+  hrr2c_tile<LAT, DEV, S, NT, HXV, HYR, DYN>(src, dst, mac, g, om, tau, sig, ntx, tile, raw, dyn, sig_dyn, dthr);
 }
 
 template <int LAT, bool DEV, typename S, bool NT, int HXV, int HYR, bool DYN = false>
 __global__ __launch_bounds__(HXV * HYR) void k_hrr2(const S* __restrict__ src, S* __restrict__ dst,
                                                     const S* __restrict__ mac, const Geo g, const S om, const S tau,
-                                                    const S sig, int ntx, int nty, int per_xcd, S* __restrict__ dyn,
-                                                    const S sig_dyn, const S dthr) {
-  const int b = blockIdx.x;
+                                                    const S sig, const Hrr2Iface<S> fi, int ntx, int nty, int per_xcd,
+                                                    S* __restrict__ dyn, const S sig_dyn, const S dthr) {
+  __shared__ __attribute__((aligned(16))) char raw[hrr2_lds<S, HXV, HYR>()];
+  int b = blockIdx.x;
+  if (b < fi.ncb) {
+    coalesce2_table<LAT, DEV, S, M_HRR>(raw, src, fi.dst_c, g, fi.itf, fi.kc, fi.om_c, fi.tau_c, fi.sig,
+                                        (int64_t)(b % kXCD) * (fi.ncb / kXCD) + b / kXCD, nullptr, nullptr);
+    return;
+  }
+  b -= fi.ncb;
+  if (b < fi.nrb) {
+    if ((int)threadIdx.x >= fi.lanes) return;
+    const int64_t r = ((int64_t)(b % kXCD) * (fi.nrb / kXCD) + b / kXCD) * fi.lanes + threadIdx.x;
+    ring_body<LAT, DEV, S, M_HRR, true>(fi.Hp, dst, g, fi.itf, fi.kf, fi.om_f, fi.tau_f, fi.sig, r);
+    return;
+  }
+  b -= fi.nrb;
   const int tile = (b % kXCD) * per_xcd + b / kXCD;
   if (tile >= ntx * nty) return;  // whole work group, before any barrier
-  hrr2_tile<LAT, DEV, S, NT, HXV, HYR, DYN>(src, dst, mac, g, om, tau, sig, ntx, tile, dyn, sig_dyn, dthr);
+  hrr2_tile<LAT, DEV, S, NT, HXV, HYR, DYN>(src, dst, mac, g, om, tau, sig, ntx, tile, raw, dyn, sig_dyn, dthr);
 }
 
 // ---------------------------------------------------------------------------

@@ -466,8 +466,7 @@ struct Grid final : GridBase {
   template <int MODEL>
   void launch_ring_coalesce(const double* Hp, S* fdst, const S* src_f, S* cdst, const S* xb, double* su,
                             hipStream_t s) {
-    constexpr int PER = 256 / (D == 2 ? 9 : 27);
-    const unsigned br2 = xblocks(itf.NR, 256), bc = xblocks(itf.NT, PER);
+    const unsigned br2 = xblocks(itf.NR, 256), bc = xblocks(coalesce_blocks(g, itf.NT), 1);
     const double kf = tau_f / (2.0 * tau_c), kc = 2.0 * tau_c / tau_f;
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
     hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, MODEL>), dim3(br2 + bc), dim3(256), 0, s, Hp, fdst, src_f, cdst, g,
@@ -479,59 +478,98 @@ struct Grid final : GridBase {
   // 32 x 16, 128 x 4.
   // dyn: with dynamic sigma on, the DYN kernels and the fine level's state
   // (stepping only; the tuner's trial launches leave the state alone)
+  // sh: interface work that shares the launch (share_coarse, share_fine), or
+  // none.
   template <int HXV, int HYR>
-  void go_hrr2(const S* src, S* dst, const S* mac, hipStream_t s, bool dyn) {
+  void go_hrr2(const S* src, S* dst, const S* mac, hipStream_t s, bool dyn, Hrr2Iface<S> sh) {
     if constexpr (D == 2) {
       const int ntx = fine2_ntx<S>(g, HXV), nty = fine2_nty(g, HYR);
       const int per = (ntx * nty + kXCD - 1) / kXCD;
-      const dim3 gr((unsigned)(per * kXCD)), bl(HXV * HYR);
+      if (sh.dst_c) {
+        sh.lanes = iface_lanes(itf.NR, HXV * HYR);
+        sh.nrb = (int)xblocks(itf.NR, sh.lanes);
+        sh.ncb = (int)xblocks(coalesce_blocks(g, itf.NT), 1);
+      }
+      const dim3 gr((unsigned)(sh.ncb + sh.nrb + per * kXCD)), bl(HXV * HYR);
       if (dyn && dyn_on)
         hipLaunchKernelGGL((k_hrr2<LAT, DEV, S, NT, HXV, HYR, true>), gr, bl, 0, s, src, dst, mac, g,
-                           (S)(1.0 - 1.0 / tau_f), (S)tau_f, (S)sig, ntx, nty, per, dynF.as<S>(), (S)sig_dyn,
+                           (S)(1.0 - 1.0 / tau_f), (S)tau_f, (S)sig, sh, ntx, nty, per, dynF.as<S>(), (S)sig_dyn,
                            (S)dyn_thr);
       else
         hipLaunchKernelGGL((k_hrr2<LAT, DEV, S, NT, HXV, HYR, false>), gr, bl, 0, s, src, dst, mac, g,
-                           (S)(1.0 - 1.0 / tau_f), (S)tau_f, (S)sig, ntx, nty, per, (S*)nullptr, (S)0, (S)0);
+                           (S)(1.0 - 1.0 / tau_f), (S)tau_f, (S)sig, sh, ntx, nty, per, (S*)nullptr, (S)0, (S)0);
     }
   }
-  // The coarse level in one pass (D2Q9 H-RR, rows a whole number of vectors:
-  // coarse_one_pass()); same tile variants, role 2.
-  bool coarse_one_pass2() const {
-    return D == 2 && desc.collision == LBM_HRR && g.n[0] % V == 0 && !nested_child;
-  }
+  // The D2Q9 coarse H-RR level runs in one pass (same tile variants, role 2).
+  bool coarse_one_pass2() const { return D == 2 && desc.collision == LBM_HRR && !nested_child; }
   // D2Q9 H-RR fine substeps in one pass (k_hrr2)
   bool fine_one_pass2() const { return D == 2; }
   template <int HXV, int HYR>
-  void go_hrr2c(const S* src, S* dst, const S* mac, hipStream_t s, bool dyn) {
+  void go_hrr2c(const S* src, S* dst, const S* mac, hipStream_t s, bool dyn, Hrr2Iface<S> sh) {
     if constexpr (D == 2) {
-      const int ntx = (g.n[0] / V + HXV - 3) / (HXV - 2), nty = (g.n[1] + HYR - 3) / (HYR - 2);
+      const int ntx = hrr2c_ntx<S>(g, HXV), nty = hrr2c_nty(g, HYR);
       const int per = (ntx * nty + kXCD - 1) / kXCD;
-      const dim3 gr((unsigned)(per * kXCD)), bl(HXV * HYR);
+      if (sh.half) {
+        sh.lanes = iface_lanes(itf.NR, HXV * HYR);
+        sh.nrb = (int)xblocks(itf.NR, sh.lanes);
+      }
+      const dim3 gr((unsigned)(2 * sh.nrb + per * kXCD)), bl(HXV * HYR);
       if (dyn && dyn_on)
         hipLaunchKernelGGL((k_hrr2c<LAT, DEV, S, NT, HXV, HYR, true>), gr, bl, 0, s, src, dst, mac, g,
-                           (S)(1.0 - 1.0 / tau_c), (S)tau_c, (S)sig, ntx, nty, per, dynC.as<S>(), (S)sig_dyn,
+                           (S)(1.0 - 1.0 / tau_c), (S)tau_c, (S)sig, sh, ntx, nty, per, dynC.as<S>(), (S)sig_dyn,
                            (S)dyn_thr);
       else
         hipLaunchKernelGGL((k_hrr2c<LAT, DEV, S, NT, HXV, HYR, false>), gr, bl, 0, s, src, dst, mac, g,
-                           (S)(1.0 - 1.0 / tau_c), (S)tau_c, (S)sig, ntx, nty, per, (S*)nullptr, (S)0, (S)0);
+                           (S)(1.0 - 1.0 / tau_c), (S)tau_c, (S)sig, sh, ntx, nty, per, (S*)nullptr, (S)0, (S)0);
     }
   }
-  void launch_hrr2c(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1, bool dyn = false) {
+  // The interface data every shared part reads; share_coarse / share_fine add
+  // the outputs that ask for it.
+  Hrr2Iface<S> share_base() const {
+    Hrr2Iface<S> h{};
+    h.itf = itf;
+    h.G = G.as<double>();
+    h.Hm = hist[hs[0]].as<double>();
+    h.H0 = hist[hs[1]].as<double>();
+    h.Hp = hist[hs[2]].as<double>();
+    h.kf = tau_f / (2.0 * tau_c);
+    h.om_f = 1.0 - 1.0 / tau_f;
+    h.tau_f = tau_f;
+    h.kc = 2.0 * tau_c / tau_f;
+    h.om_c = 1.0 - 1.0 / tau_c;
+    h.tau_c = tau_c;
+    h.sig = sig;
+    return h;
+  }
+  Hrr2Iface<S> share_coarse(S* half, S* mac_fine) const {
+    Hrr2Iface<S> h = share_base();
+    h.half = half;
+    h.mac_f = mac_fine;
+    return h;
+  }
+  Hrr2Iface<S> share_fine(S* dst_c) const {
+    Hrr2Iface<S> h = share_base();
+    h.dst_c = dst_c;
+    return h;
+  }
+  void launch_hrr2c(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1, bool dyn = false,
+                    const Hrr2Iface<S>& sh = Hrr2Iface<S>{}) {
     if (v < 0) v = var[2];
     switch (v) {
-      case 0: go_hrr2c<64, 8>(src, dst, mac, s, dyn); break;
-      case 1: go_hrr2c<32, 8>(src, dst, mac, s, dyn); break;
-      case 2: go_hrr2c<32, 16>(src, dst, mac, s, dyn); break;
-      default: go_hrr2c<128, 4>(src, dst, mac, s, dyn); break;
+      case 0: go_hrr2c<64, 8>(src, dst, mac, s, dyn, sh); break;
+      case 1: go_hrr2c<32, 8>(src, dst, mac, s, dyn, sh); break;
+      case 2: go_hrr2c<32, 16>(src, dst, mac, s, dyn, sh); break;
+      default: go_hrr2c<128, 4>(src, dst, mac, s, dyn, sh); break;
     }
   }
-  void launch_hrr2(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1, bool dyn = false) {
+  void launch_hrr2(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1, bool dyn = false,
+                   const Hrr2Iface<S>& sh = Hrr2Iface<S>{}) {
     if (v < 0) v = var[3];
     switch (v) {
-      case 0: go_hrr2<64, 8>(src, dst, mac, s, dyn); break;
-      case 1: go_hrr2<32, 8>(src, dst, mac, s, dyn); break;
-      case 2: go_hrr2<32, 16>(src, dst, mac, s, dyn); break;
-      default: go_hrr2<128, 4>(src, dst, mac, s, dyn); break;
+      case 0: go_hrr2<64, 8>(src, dst, mac, s, dyn, sh); break;
+      case 1: go_hrr2<32, 8>(src, dst, mac, s, dyn, sh); break;
+      case 2: go_hrr2<32, 16>(src, dst, mac, s, dyn, sh); break;
+      default: go_hrr2<128, 4>(src, dst, mac, s, dyn, sh); break;
     }
   }
 
@@ -878,13 +916,12 @@ struct Grid final : GridBase {
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
     const double c0 = -1.0 / 8.0, c1 = 3.0 / 4.0, c2 = 3.0 / 8.0;  // eq TempInt at t+1/2
     constexpr int IB = kIfaceBlock;
-    constexpr int PER = 256 / (D == 2 ? 9 : 27);
     const unsigned bh = xblocks(NH, IB), br = xblocks(itf.NR, IB), bt = xblocks(itf.NT, IB);
-    const unsigned bc = xblocks(itf.NT, PER), br2 = xblocks(itf.NR, 256);
+    const unsigned bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(itf.NR, 256);
     // D3Q19 BGK / RR: the capture also interpolates every history value to
     // t+1/2 (G); H-RR fills its strain-rate fields later and interpolates
     // then.  D2Q9 BGK / RR: it shares the coarse stream's launch.
-    if (D == 3 || MODEL == M_HRR)
+    if (D == 3 || (MODEL == M_HRR && !coarse_one_pass2()))
       hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
                          MODEL == M_HRR ? nullptr : G.as<double>(), Hm, H0);
     timed_factor = fused_now() ? 2 : 1;
@@ -911,6 +948,22 @@ struct Grid final : GridBase {
       launch_stream_ring<MODEL>(csrc, cdst, fB, kf, omf, s, xb, scn);
       fine_stream_timed(MODEL, fB, fA, s);
       launch_ring_coalesce<MODEL>(Hp, fA, fB, cdst, xb, scn, s);
+    } else if (coarse_one_pass2()) {
+      // D2Q9 H-RR in five launches: capture + t+1/2 ring rho, u; fine substep 1;
+      // fictitious propagation + strain rate + temporal interpolation of the
+      // history; coarse step + t+1/2 ring + t+1 ring rho, u; fine substep 2 +
+      // t+1 ring + transfer
+      if constexpr (D == 2) {
+        S* mc = mac_c.as<S>();
+        S* mf = mac_f.as<S>();
+        hipLaunchKernelGGL((k_capture_macro<LAT, DEV, S>), dim3(br + bh), dim3(IB), 0, s, csrc, Hm, H0, Hp, mf, g, itf,
+                           (int)br);
+        timed(s, [&] { launch_hrr2(fA, fB, mf, s, -1, true); });
+        hipLaunchKernelGGL((k_fict_strain_time<LAT, DEV, S>), dim3(bt + bh), dim3(IB), 0, s, csrc, fB, mc, Hm, H0, Hp,
+                           G.as<double>(), g, itf, (int)bt);
+        launch_hrr2c(csrc, cdst, mc, s, -1, true, share_coarse(fB, mf));
+        timed(s, [&] { launch_hrr2(fB, fA, mf, s, -1, true, share_fine(cdst)); });
+      }
     } else {
       S* mc = mac_c.as<S>();
       S* mf = mac_f.as<S>();
@@ -994,8 +1047,7 @@ struct Grid final : GridBase {
     const double kf = tau_f / (2.0 * tau_c), kc = 2.0 * tau_c / tau_f;
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
     constexpr int IB = kIfaceBlock;
-    constexpr int PER = 256 / (D == 2 ? 9 : 27);
-    const unsigned bh = xblocks(NH, IB), bc = xblocks(itf.NT, PER), br2 = xblocks(itf.NR, 256);
+    const unsigned bh = xblocks(NH, IB), bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(itf.NR, 256);
     if (D == 3)
       hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
                          G.as<double>(), Hm, H0);
@@ -1035,9 +1087,8 @@ struct Grid final : GridBase {
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
     const double c0 = -1.0 / 8.0, c1 = 3.0 / 4.0, c2 = 3.0 / 8.0;  // eq TempInt at t+1/2
     constexpr int IB = kIfaceBlock;
-    constexpr int PER = 256 / (D == 2 ? 9 : 27);
     const unsigned bh = xblocks(NH, IB), br = xblocks(itf.NR, IB), bt = xblocks(itf.NT, IB);
-    const unsigned bc = xblocks(itf.NT, PER), br2 = xblocks(itf.NR, 256);
+    const unsigned bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(itf.NR, 256);
     const Geo gg = g;
     const Iface it = itf;
     hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, M_HRR>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf, nullptr, Hm,
@@ -1567,7 +1618,10 @@ struct Batch final : BatchBase {
   // D2Q9 BGK / RR instances run both fine substeps in one phase (kb_fine2),
   // in tiles of shape tile_var (kTileX, kTileY).
   bool fused() const { return D == 2 && collision != LBM_HRR; }
-  int tile_var = 0;
+  // D2Q9 H-RR instances run their levels in one pass (kb_hrr2, kb_hrr2c), in
+  // tiles of shape tile_var (fine) and ctile_var (coarse).
+  bool hrr2() const { return D == 2 && collision == LBM_HRR; }
+  int tile_var = 0, ctile_var = 0;
   std::vector<std::unique_ptr<Inst>> slots;
   std::vector<InstDev> hinst;
   std::vector<int64_t> steps_done;
@@ -1628,25 +1682,31 @@ struct Batch final : BatchBase {
   // Work lists of every phase from the active instances.
   void rebuild_lists() {
     std::vector<Work> lists[W_KINDS];
-    constexpr int PER = 256 / (D == 2 ? 9 : 27);
     const int hfields = collision == LBM_BGK ? HF<LAT, M_BGK>::N : (collision == LBM_RR ? HF<LAT, M_RR>::N
                                                                                          : HF<LAT, M_HRR>::N);
     for (int sl = 0; sl < capacity; ++sl) {
       if (!slots[(size_t)sl]) continue;
       const InstDev& I = hinst[(size_t)sl];
-      for (int t = 0; t < I.fc.nchunks; ++t) lists[W_COARSE].push_back({sl, t});
+      if (hrr2()) {
+        const int nc = hrr2c_ntx<S>(I.g, kTileX[ctile_var]) * hrr2c_nty(I.g, kTileY[ctile_var]);
+        for (int c = 0; c < nc; ++c) lists[W_CTILE].push_back({sl, c});
+      } else {
+        for (int t = 0; t < I.fc.nchunks; ++t) lists[W_COARSE].push_back({sl, t});
+      }
       if (!I.g.has_fine) continue;
-      for (int t = 0; t < I.ff.nchunks; ++t) lists[W_FINE].push_back({sl, t});
+      if (D == 3)
+        for (int t = 0; t < I.ff.nchunks; ++t) lists[W_FINE].push_back({sl, t});
       const int64_t nh = I.itf.NH, nr = I.itf.NR, nt = I.itf.NT;
       for (int64_t c = 0; c < (nh + 63) / 64; ++c) lists[W_HIST].push_back({sl, (int)c});
-      for (int64_t c = 0; c < (nh * hfields + 63) / 64; ++c) lists[W_HTIME].push_back({sl, (int)c});
+      if (D == 3 && collision == LBM_HRR)
+        for (int64_t c = 0; c < (nh * hfields + 63) / 64; ++c) lists[W_HTIME].push_back({sl, (int)c});
       for (int64_t c = 0; c < (nr + 63) / 64; ++c) lists[W_RING].push_back({sl, (int)c});
       for (int64_t c = 0; c < (nt + 63) / 64; ++c) lists[W_TN].push_back({sl, (int)c});
       const int64_t ntb =
           I.fused ? coalesce2_count(I.g, tile_var == 0 ? fine2_nseg<kTileX[0] * kTileY[0]>() : fine2_nseg<kTileX[1] * kTileY[1]>())
-                  : (nt + PER - 1) / PER;
+                  : coalesce_blocks(I.g, nt);
       for (int64_t c = 0; c < ntb; ++c) lists[W_TNB].push_back({sl, (int)c});
-      if (I.fused) {
+      if (D == 2) {
         const int ntile = fine2_ntx<S>(I.g, kTileX[tile_var]) * fine2_nty(I.g, kTileY[tile_var]);
         for (int c = 0; c < ntile; ++c) lists[W_TILE].push_back({sl, c});
       }
@@ -1739,6 +1799,7 @@ struct Batch final : BatchBase {
     I.fpar = 0;
     I.fused = (g.has_fine && fused()) ? 1 : 0;
     I.ntx = g.has_fine ? fine2_ntx<S>(g, kTileX[tile_var]) : 0;
+    I.ntxc = hrr2c_ntx<S>(g, kTileX[ctile_var]);
     I.mac_c = in->mac_c.p;
     I.mac_f = in->mac_f.p;
     for (int k = 0; k < 3; ++k) I.hist[k] = in->hist[k].template as<double>();
@@ -1929,26 +1990,60 @@ struct Batch final : BatchBase {
     if (tile_var == 0) go_fine2<MODEL, 0>(s, alone);
     else go_fine2<MODEL, 1>(s, alone);
   }
-  // Sets the fused tile shape: every instance's tile count per row on the
-  // device (that field only: the rest of a descriptor advances on the device)
-  // and the tile list.
-  void set_tile_var(int tv) {
+  // Sets the D2Q9 tile shapes: every instance's tile counts per row on the
+  // device (those fields only: the rest of a descriptor advances on the
+  // device) and the tile lists.
+  void set_tile_var(int tv, int ctv = 0) {
     tile_var = tv;
+    ctile_var = ctv;
     for (int sl = 0; sl < capacity; ++sl) {
-      if (!slots[(size_t)sl] || !hinst[(size_t)sl].fused) continue;
-      const int ntx = fine2_ntx<S>(hinst[(size_t)sl].g, kTileX[tv]);
-      hinst[(size_t)sl].ntx = ntx;
-      HIPCHK(hipMemcpy(&(d_inst.template as<InstDev>() + sl)->ntx, &ntx, sizeof(int), hipMemcpyHostToDevice));
+      if (!slots[(size_t)sl]) continue;
+      InstDev& I = hinst[(size_t)sl];
+      I.ntx = I.g.has_fine ? fine2_ntx<S>(I.g, kTileX[tv]) : 0;
+      I.ntxc = hrr2c_ntx<S>(I.g, kTileX[ctv]);
+      InstDev* dI = d_inst.template as<InstDev>() + sl;
+      HIPCHK(hipMemcpy(&dI->ntx, &I.ntx, sizeof(int), hipMemcpyHostToDevice));
+      HIPCHK(hipMemcpy(&dI->ntxc, &I.ntxc, sizeof(int), hipMemcpyHostToDevice));
     }
     rebuild_lists();
     drop_graph();
+  }
+  // D2Q9 H-RR phases; alone: without the interface work that shares the launch
+  // (the tuner's trial launches).
+  template <int TV>
+  void go_hrr2c(hipStream_t s, bool alone) {
+    if constexpr (D == 2) {
+      constexpr int NL = kTileX[TV] * kTileY[TV];
+      const unsigned nrb = alone ? 0 : groups_of(W_RING, NL / 64);
+      hipLaunchKernelGGL((kb_hrr2c<LAT, DEV, S, NT, kTileX[TV], kTileY[TV]>), dim3(2 * nrb + grid_of(W_CTILE).x), dim3(NL),
+                         0, s, di(), items(W_RING), cnt(W_RING), items(W_CTILE), cnt(W_CTILE), (int)nrb);
+    }
+  }
+  void phase_hrr2c(hipStream_t s, bool alone = false) {
+    if (ctile_var == 0) go_hrr2c<0>(s, alone);
+    else go_hrr2c<1>(s, alone);
+  }
+  template <int SUB, int TV>
+  void go_hrr2(hipStream_t s) {
+    if constexpr (D == 2) {
+      constexpr int NL = kTileX[TV] * kTileY[TV];
+      const unsigned ncb = SUB ? grid_of(W_TNB).x : 0, nrb = SUB ? groups_of(W_RING, NL / 64) : 0;
+      hipLaunchKernelGGL((kb_hrr2<LAT, DEV, S, SUB, NT, kTileX[TV], kTileY[TV]>), dim3(ncb + nrb + grid_of(W_TILE).x),
+                         dim3(NL), 0, s, di(), items(W_TNB), cnt(W_TNB), items(W_RING), cnt(W_RING), items(W_TILE),
+                         cnt(W_TILE), (int)ncb, (int)nrb);
+    }
+  }
+  template <int SUB>
+  void phase_hrr2(hipStream_t s) {
+    if (tile_var == 0) go_hrr2<SUB, 0>(s);
+    else go_hrr2<SUB, 1>(s);
   }
 
   template <int MODEL>
   void launch_step_model(hipStream_t s) {
     using F = HF<LAT, MODEL>;
     const dim3 ib(64);
-    if (D == 3 || MODEL == M_HRR)
+    if (D == 3)
       hipLaunchKernelGGL((kb_hist_capture<LAT, DEV, S, MODEL>), grid_of(W_HIST), ib, 0, s, di(), items(W_HIST),
                          cnt(W_HIST));
     if constexpr (MODEL != M_HRR) {
@@ -1972,6 +2067,16 @@ struct Batch final : BatchBase {
         hipLaunchKernelGGL((kb_ring_coalesce<LAT, DEV, S, MODEL>), dim3(nrb + grid_of(W_TNB).x), dim3(256), 0, s, di(),
                            items(W_RING), cnt(W_RING), items(W_TNB), cnt(W_TNB), (int)nrb);
       }
+    } else if constexpr (D == 2) {
+      // as the single grid's five launches
+      const unsigned nrb = grid_of(W_RING).x, ntn = grid_of(W_TN).x, nh = grid_of(W_HIST).x;
+      hipLaunchKernelGGL((kb_capture_macro<LAT, DEV, S>), dim3(nrb + nh), ib, 0, s, di(), items(W_RING), cnt(W_RING),
+                         items(W_HIST), cnt(W_HIST), (int)nrb);
+      phase_hrr2<0>(s);
+      hipLaunchKernelGGL((kb_fict_strain_time<LAT, DEV, S>), dim3(ntn + nh), ib, 0, s, di(), items(W_TN), cnt(W_TN),
+                         items(W_HIST), cnt(W_HIST), (int)ntn);
+      phase_hrr2c(s);
+      phase_hrr2<1>(s);
     } else {
       phase_stream<M_HRR, 0, 0>(s, var_c);
       phase_stream<M_HRR, 1, 0>(s, var_f);
@@ -2044,7 +2149,38 @@ struct Batch final : BatchBase {
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
-    if (fused() && counts[W_FINE] > 0) {
+    if (hrr2()) {
+      // one pass per level: one variant per tile shape, coarse and fine apart
+      // (they rewrite the buffers the next step rewrites)
+      int bv[2] = {0, 0};
+      for (int level = 0; level < 2; ++level) {
+        if (counts[level == 0 ? W_CTILE : W_TILE] == 0) continue;
+        float best = -1.f;
+        for (int tv = 0; tv < kNTile; ++tv) {
+          if (level == 0) set_tile_var(tile_var, tv);
+          else set_tile_var(tv, bv[0]);
+          auto run = [&] {
+            if (level == 0) phase_hrr2c(stream, true);
+            else phase_hrr2<0>(stream);
+          };
+          run();
+          HIPCHK(hipEventRecord(e0, stream));
+          for (int k = 0; k < reps; ++k) run();
+          HIPCHK(hipEventRecord(e1, stream));
+          HIPCHK(hipEventSynchronize(e1));
+          float ms = 0.f;
+          HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+          if (best < 0.f || ms < best) {
+            best = ms;
+            bv[level] = tv;
+          }
+        }
+      }
+      set_tile_var(bv[1], bv[0]);
+      var_c = bv[0];
+      var_f = bv[1];
+    }
+    if (fused() && counts[W_TILE] > 0) {
       // fused fine phase: one variant per tile shape (it rewrites B, which the
       // next step rewrites)
       float best = -1.f;
@@ -2073,6 +2209,7 @@ struct Batch final : BatchBase {
     for (int level = 0; level < 2; ++level) {
       if (counts[level == 0 ? W_COARSE : W_FINE] == 0) continue;
       if (level == 1 && fused()) continue;  // tuned above
+      if (hrr2()) continue;
       float best = -1.f;
       int bv = 0;
       for (int v = 0; v < NVAR; ++v) {
@@ -2120,6 +2257,9 @@ struct Batch final : BatchBase {
     var_c = v[0];
     var_f = v[1];
     if (fused()) set_tile_var(v[1]);
+    // (D2Q9 H-RR: kNTile tile shapes per level; the indices of the two-pass
+    // form it had before stay accepted)
+    if (hrr2()) set_tile_var(v[1] % kNTile, v[0] % kNTile);
     drop_graph();
   }
 
