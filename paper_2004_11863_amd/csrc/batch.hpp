@@ -76,7 +76,7 @@ enum WorkKind : int {
   W_FINE = 1,    // fine bulk chunks
   W_HIST = 2,    // 64 history nodes
   W_HTIME = 3,   // 64 history values (all fields)
-  W_RING = 4,    // 64 ring nodes
+  W_RING = 4,    // 64 ring nodes (D3Q19: a ring tile)
   W_TN = 5,      // 64 TN nodes
   W_TNB = 6,     // PER TN nodes (one fine-to-coarse work group)
   W_TILE = 7,    // D2Q9 fine tile (the batch's tile shape)
@@ -201,23 +201,27 @@ __global__ __launch_bounds__(64) void kb_hist_time(const InstDev* __restrict__ i
   }
 }
 
-// Ring reconstruction of one 64-node item: SUB 0 (t+1/2, from G, or in D2Q9
+// Ring reconstruction of one item, 64 nodes (D2Q9, one wave) or a tile (D3Q19,
+// a work group of 256 lanes with LDS raw): SUB 0 (t+1/2, from G, or in D2Q9
 // BGK / RR with the capture of ring_half_body, into the half-time buffer: fh
 // when fused, else B), SUB 1 (t+1, from the t+1 history, into the buffer that
 // holds t+1 after the step: B when fused, else A); only the populations the
 // stepping reads (the full ring of A is completed before it is observed).
 template <int LAT, bool DEV, typename S, int MODEL, int SUB>
-__device__ __forceinline__ void kb_ring_item(const InstDev& I, int idx, int lane) {
+__device__ __forceinline__ void kb_ring_item(const InstDev& I, int idx, int lane, char* raw = nullptr) {
   S* dst = glob((S*)(SUB == 0 ? (I.fused ? I.fh : I.fbuf[I.fpar ^ 1]) : I.fbuf[I.fpar ^ I.fused]));
   const double kf = I.tau_f / (2.0 * I.tau_c), om_f = 1.0 - 1.0 / I.tau_f;
   const int64_t r = (int64_t)idx * 64 + lane;
-  if constexpr (SUB == 0 && Lattice<LAT>::D == 2 && MODEL != M_HRR) {
+  if constexpr (Lattice<LAT>::D == 3) {
+    S* xb = (SUB == 0 && I.xb) ? glob((S*)I.xb) : nullptr;  // the t+1/2 ring fills the x-band copy
+    ring3_body<LAT, DEV, S, MODEL, true>(raw, glob(SUB == 0 ? I.G : I.hist[I.hs[2]]), dst, I.g, I.itf.NH, kf, om_f,
+                                         I.tau_f, I.sig, idx, xb);
+  } else if constexpr (SUB == 0 && MODEL != M_HRR) {
     ring_half_body<LAT, DEV, S, MODEL>(glob((const S*)I.ccur), glob(I.hist[I.hs[0]]), glob(I.hist[I.hs[1]]), dst, I.g,
                                        glob(I.itf), kf, om_f, I.tau_f, I.sig, r);
   } else {
     const double* G = glob(SUB == 0 ? I.G : I.hist[I.hs[2]]);
-    S* xb = (SUB == 0 && I.xb) ? glob((S*)I.xb) : nullptr;  // the t+1/2 ring fills the x-band copy
-    ring_body<LAT, DEV, S, MODEL, true>(G, dst, I.g, glob(I.itf), kf, om_f, I.tau_f, I.sig, r, xb);
+    ring_body<LAT, DEV, S, MODEL, true>(G, dst, I.g, glob(I.itf), kf, om_f, I.tau_f, I.sig, r);
   }
 }
 // Item of this wave, or -1: block b of one part of a launch takes W
@@ -229,14 +233,14 @@ __device__ __forceinline__ int wave_item(int b, int n) {
   return grp < 0 || it >= n ? -1 : it;
 }
 template <int LAT, bool DEV, typename S, int MODEL, int SUB>
-__global__ __launch_bounds__(64) void kb_ring(const InstDev* __restrict__ inst, const Work* __restrict__ items,
-                                              const int* __restrict__ count) {
+__global__ __launch_bounds__(256) void kb_ring(const InstDev* __restrict__ inst, const Work* __restrict__ items,
+                                               const int* __restrict__ count) {
+  static_assert(Lattice<LAT>::D == 3, "D2Q9 rings share other launches");
+  __shared__ __attribute__((aligned(16))) char raw[ring3_lds(HF<LAT, MODEL>::N)];
   const int it = item_of(*count);
-  if (it < 0) return;
-  {
-    const Work w = load_item(items, it);
-    kb_ring_item<LAT, DEV, S, MODEL, SUB>(inst[w.inst], w.idx, threadIdx.x);
-  }
+  if (it < 0) return;  // whole work group
+  const Work w = load_item(items, it);
+  kb_ring_item<LAT, DEV, S, MODEL, SUB>(inst[w.inst], w.idx, threadIdx.x, raw);
 }
 
 // Coarse stream (BGK, RR), the t+1/2 ring and, D2Q9, the history capture in
@@ -249,10 +253,18 @@ __global__ __launch_bounds__(256) void kb_stream_ring(const InstDev* __restrict_
                                                       const int* __restrict__ ccount, int nrb, int nhb) {
   const int b = blockIdx.x, lane = threadIdx.x & 63;
   if (b < nrb) {
-    const int it = wave_item<4>(b, *rcount);
-    if (it < 0) return;
-    const Work w = load_item(ritems, it);
-    kb_ring_item<LAT, DEV, S, MODEL, 0>(inst[w.inst], w.idx, lane);
+    if constexpr (Lattice<LAT>::D == 3) {
+      __shared__ __attribute__((aligned(16))) char raw[ring3_lds(HF<LAT, MODEL>::N)];
+      const int it = item_in(b, *rcount);
+      if (it < 0) return;  // whole work group
+      const Work w = load_item(ritems, it);
+      kb_ring_item<LAT, DEV, S, MODEL, 0>(inst[w.inst], w.idx, threadIdx.x, raw);
+    } else {
+      const int it = wave_item<4>(b, *rcount);
+      if (it < 0) return;
+      const Work w = load_item(ritems, it);
+      kb_ring_item<LAT, DEV, S, MODEL, 0>(inst[w.inst], w.idx, lane);
+    }
   } else if (b < nrb + nhb) {
     const int it = wave_item<4>(b - nrb, *hcount);
     if (it < 0) return;
@@ -306,20 +318,18 @@ __global__ __launch_bounds__(HXV * HYR) void kb_fine2(const InstDev* __restrict_
                                                glob((S*)I.fh), I.g, (S)(1.0 - 1.0 / I.tau_f), I.ntx, w.idx, raw);
 }
 
-// H-RR ring rho, u at t+1/2 (SUB 0) or t+1 (SUB 1).
+// D3Q19 H-RR ring rho, u at t+1/2 (SUB 0) or t+1 (SUB 1).
 template <int LAT, typename S, int SUB>
-__global__ __launch_bounds__(64) void kb_ring_macro(const InstDev* __restrict__ inst, const Work* __restrict__ items,
-                                                    const int* __restrict__ count) {
+__global__ __launch_bounds__(256) void kb_ring_macro(const InstDev* __restrict__ inst, const Work* __restrict__ items,
+                                                     const int* __restrict__ count) {
+  __shared__ __attribute__((aligned(16))) char raw[ring3_lds(4)];
   const int it = item_of(*count);
-  if (it < 0) return;
-  {
-    const Work w = load_item(items, it);
-    const InstDev& I = inst[w.inst];
-    const double c0 = SUB == 0 ? -0.125 : 0.0, c1 = SUB == 0 ? 0.75 : 0.0, c2 = SUB == 0 ? 0.375 : 1.0;
-    ring_macro_body<LAT, S>(glob(I.hist[I.hs[0]]), glob(I.hist[I.hs[1]]), glob(I.hist[I.hs[2]]), c0, c1, c2,
-                            glob((S*)I.mac_f), I.g, glob(I.itf),
-                            (int64_t)w.idx * 64 + threadIdx.x);
-  }
+  if (it < 0) return;  // whole work group
+  const Work w = load_item(items, it);
+  const InstDev& I = inst[w.inst];
+  const double c0 = SUB == 0 ? -0.125 : 0.0, c1 = SUB == 0 ? 0.75 : 0.0, c2 = SUB == 0 ? 0.375 : 1.0;
+  ring3_macro_body<S>(raw, glob(I.hist[I.hs[0]]), glob(I.hist[I.hs[1]]), glob(I.hist[I.hs[2]]), c0, c1, c2,
+                      glob((S*)I.mac_f), I.g, I.itf.NH, w.idx);
 }
 
 // D2Q9 H-RR: one-pass levels, as the single grid's five launches
@@ -442,33 +452,26 @@ __global__ __launch_bounds__(64) void kb_fict(const InstDev* __restrict__ inst, 
   }
 }
 
-// Fine-to-coarse transfer from the t+1/2 state (fh when fused, else B).
-template <int LAT, bool DEV, typename S, int MODEL>
-__device__ __forceinline__ void kb_coalesce_item(const InstDev& I, int idx) {
-  const S* xb = I.xb ? glob((const S*)I.xb) : nullptr;
-  coalesce_body<LAT, DEV, S, MODEL>(glob((const S*)(I.fused ? I.fh : I.fbuf[I.fpar ^ 1])), glob((S*)I.cnext), I.g,
-                                    glob(I.itf),
-                                    2.0 * I.tau_c / I.tau_f, 1.0 - 1.0 / I.tau_c, I.tau_c, I.sig, idx, xb);
-}
-
-// The t+1 ring and the fine-to-coarse transfer in one launch: blocks
-// [0, nrb) take ring items (64 lanes each), the rest TN blocks.
+// The t+1 ring and the fine-to-coarse transfer (from the t+1/2 state in B) of
+// D3Q19 instances in one launch: blocks [0, nrb) take ring tiles, the rest TN
+// tiles.
 template <int LAT, bool DEV, typename S, int MODEL>
 __global__ __launch_bounds__(256) void kb_ring_coalesce(const InstDev* __restrict__ inst, const Work* __restrict__ ritems,
                                                         const int* __restrict__ rcount, const Work* __restrict__ titems,
                                                         const int* __restrict__ tcount, int nrb) {
+  static_assert(Lattice<LAT>::D == 3, "D2Q9: in kb_fine2 / kb_hrr2");
+  __shared__ __attribute__((aligned(16))) char raw[ring_coalesce_lds<LAT, MODEL>()];
   const int b = blockIdx.x;
+  const int it = b < nrb ? item_in(b, *rcount) : item_in(b - nrb, *tcount);
+  if (it < 0) return;  // whole work group
+  const Work w = load_item(b < nrb ? ritems : titems, it);
+  const InstDev& I = inst[w.inst];
   if (b < nrb) {
-    if (threadIdx.x >= 64) return;
-    const int it = item_in(b, *rcount);
-    if (it < 0) return;
-    const Work w = load_item(ritems, it);
-    kb_ring_item<LAT, DEV, S, MODEL, 1>(inst[w.inst], w.idx, threadIdx.x);
+    kb_ring_item<LAT, DEV, S, MODEL, 1>(I, w.idx, threadIdx.x, raw);
   } else {
-    const int it = item_in(b - nrb, *tcount);
-    if (it < 0) return;  // whole work group: the transfer synchronises its lanes
-    const Work w = load_item(titems, it);
-    kb_coalesce_item<LAT, DEV, S, MODEL>(inst[w.inst], w.idx);
+    coalesce_body<LAT, DEV, S, MODEL>(raw, glob((const S*)I.fbuf[I.fpar ^ 1]), glob((S*)I.cnext), I.g, glob(I.itf),
+                                      2.0 * I.tau_c / I.tau_f, 1.0 - 1.0 / I.tau_c, I.tau_c, I.sig, w.idx,
+                                      I.xb ? glob((const S*)I.xb) : nullptr);
   }
 }
 

@@ -102,6 +102,71 @@ __host__ __device__ inline int fine_class(const Geo& g, int x, int y, int z) {
   return (even && in_tn && on_tn) ? FC_TN : FC_MIDDLE;
 }
 
+// History entry of the coarse vertex (X, Y, Z) - 1 of a three-dimensional patch
+// (offsets from its lower corner, so X, Y, Z in [0, m + 2]) that lies on a face
+// plane: the closed form of the table's order (coarse node order over the face
+// planes within one vertex of the patch).  A z plane holds all (m0 + 3)(m1 + 3)
+// vertices where it is a face plane, else rows of m0 + 3 on the y face planes
+// and of two vertices elsewhere.
+__host__ __device__ inline int hist3_index(const Geo& g, int X, int Y, int Z) {
+  const int row = g.m[0] + 3, full = row * (g.m[1] + 3), rim = 2 * row + 2 * (g.m[1] + 1);
+  const int base = Z * rim + (full - rim) * ((Z > 1 ? 1 : 0) + (Z > g.m[2] + 1 ? 1 : 0));
+  if (Z == 1 || Z == g.m[2] + 1) return base + Y * row + X;
+  const int r = base + 2 * Y + (row - 2) * ((Y > 1 ? 1 : 0) + (Y > g.m[1] + 1 ? 1 : 0));
+  return Y == 1 || Y == g.m[1] + 1 ? r + X : r + (X == 1 ? 0 : 1);
+}
+// Tiles of kRingU x kRingV ring nodes on the six faces of a three-dimensional
+// patch (normal axis w; a z face holds its edges, a y face its x edges).  (pick
+// evaluates both values: loads behind a branch on w are merged into one load
+// from a chosen address, which puts the geometry in scratch memory.)
+__host__ __device__ inline int pick(bool c, int a, int b) { return c ? a : b; }
+constexpr int kRingU = 32, kRingV = 8;
+__host__ __device__ inline int ring3_nu(const Geo& g, int w) { return pick(w == 0, g.nf[1], g.nf[0]); }
+__host__ __device__ inline int ring3_nv(const Geo& g, int w) { return pick(w == 2, g.nf[1], g.nf[2]); }
+__host__ __device__ inline int ring3_face_tiles(const Geo& g, int w) {
+  return ((ring3_nu(g, w) + kRingU - 1) / kRingU) * ((ring3_nv(g, w) + kRingV - 1) / kRingV);
+}
+__host__ __device__ inline int ring3_tiles(const Geo& g) {
+  return 2 * (ring3_face_tiles(g, 0) + ring3_face_tiles(g, 1) + ring3_face_tiles(g, 2));
+}
+// Vertex patch of a tile: the stencils reach from one vertex before its first
+// node's to two past its last.
+constexpr int kRingPU = kRingU / 2 + 3, kRingPV = kRingV / 2 + 3;
+// Face, side and first node of tile t; false past the last tile.
+__host__ __device__ inline bool ring3_tile(const Geo& g, int t, int& w, int& side, int& u0, int& v0) {
+  const int n2 = ring3_face_tiles(g, 2), n1 = ring3_face_tiles(g, 1), n0 = ring3_face_tiles(g, 0);
+  int n;
+  if (t < 2 * n2) {
+    w = 2;
+    n = n2;
+  } else if (t < 2 * (n2 + n1)) {
+    w = 1;
+    n = n1;
+    t -= 2 * n2;
+  } else if (t < 2 * (n2 + n1 + n0)) {
+    w = 0;
+    n = n0;
+    t -= 2 * (n2 + n1);
+  } else {
+    return false;
+  }
+  side = t / n;
+  t -= side * n;
+  const int tu = (ring3_nu(g, w) + kRingU - 1) / kRingU, iv = t / tu;
+  u0 = (t - iv * tu) * kRingU;
+  v0 = iv * kRingV;
+  return true;
+}
+// History entry of vertex (pu, pv) of the patch of a tile, or -1 outside the
+// history set.
+__host__ __device__ inline int ring3_vertex(const Geo& g, int w, int side, int u0, int v0, int pu, int pv) {
+  const int mu = pick(w == 0, g.m[1], g.m[0]), mv = pick(w == 2, g.m[1], g.m[2]);
+  const int U = u0 / 2 + pu, V = v0 / 2 + pv;  // (vertex + 1)
+  if (U > mu + 2 || V > mv + 2) return -1;
+  const int mw = pick(w == 2, g.m[2], pick(w == 1, g.m[1], g.m[0])), W = side == 0 ? 1 : mw + 1;
+  return hist3_index(g, pick(w == 0, W, U), pick(w == 0, U, pick(w == 1, W, V)), pick(w == 2, W, V));
+}
+
 // Compact copy of the fine state in the two x-normal bands of the patch,
 // x in [0, 4] (side 0) and [nx - 5, nx - 1] (side 1), five nodes per row:
 // [side][population][z][y][x offset].  In the row-major layout every

@@ -764,12 +764,6 @@ __device__ __forceinline__ void ring_macro_body(const double* __restrict__ Hm, c
 #pragma unroll
   for (int k = 0; k < 1 + L::D; ++k) mac_f[(int64_t)k * g.Nfp + fi] = (T)v[k];
 }
-template <int LAT, typename T>
-__global__ void k_ring_macro(const double* __restrict__ Hm, const double* __restrict__ H0,
-                             const double* __restrict__ Hp, double c0, double c1, double c2,
-                             T* __restrict__ mac_f, const Geo g, const Iface itf) {
-  ring_macro_body<LAT, T>(Hm, H0, Hp, c0, c1, c2, mac_f, g, itf, xcd_block() * blockDim.x + threadIdx.x);
-}
 
 
 // H-RR, D2Q9: the history capture at t+1 (into Hp) and the ring's rho, u at
@@ -830,9 +824,8 @@ __global__ void k_capture_macro(const S* __restrict__ src, const double* __restr
 // With xb set (the t+1/2 ring of the two-launch D3Q19 path) ring nodes in
 // the x-bands also store the same populations into the compact band copy.
 template <int LAT, bool DEV, typename S, int MODEL, bool PARTIAL>
-__device__ __forceinline__ void ring_store(const double* v, S* __restrict__ dst, const Geo& g, const Iface& itf,
-                                           double kf, double om_f, double tau_f, double sig, int64_t r,
-                                           S* __restrict__ xb) {
+__device__ __forceinline__ void ring_store(const double* v, S* __restrict__ dst, const Geo& g, int x, int y, int z,
+                                           double kf, double om_f, double tau_f, double sig, S* __restrict__ xb) {
   using L = Lattice<LAT>;
   using F = HF<LAT, MODEL>;
   using N = Node<LAT, false, double>;
@@ -850,8 +843,6 @@ __device__ __forceinline__ void ring_store(const double* v, S* __restrict__ dst,
     if (MODEL == M_HRR) a = hrr_mix(a, sym_get<D>(v + F::S, 0.5), sig, tau_f, rho);
     N::regular(rho, rho, u, om_f, a, f);
   }
-  int x, y, z;
-  fdecode(g, itf.rnode[r], x, y, z);
   const int64_t fi = fpos(g, x, y, z);
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -869,11 +860,12 @@ __device__ __forceinline__ void ring_store(const double* v, S* __restrict__ dst,
     }
   }
 }
+// D2Q9: node r of the ring table.
 template <int LAT, bool DEV, typename S, int MODEL, bool PARTIAL>
 __device__ __forceinline__ void ring_body(const double* __restrict__ G, S* __restrict__ dst, const Geo& g, const Iface& itf,
-                                 double kf, double om_f, double tau_f, double sig, int64_t r,
-                                 S* __restrict__ xb = nullptr) {
+                                 double kf, double om_f, double tau_f, double sig, int64_t r) {
   using F = HF<LAT, MODEL>;
+  static_assert(Lattice<LAT>::D == 2, "D3Q19: ring3_body");
   if (r >= itf.NR) return;
   const int np = itf.rnp[r];
   const int32_t* pt = itf.rpt + 16 * r;
@@ -887,7 +879,93 @@ __device__ __forceinline__ void ring_body(const double* __restrict__ G, S* __res
 #pragma unroll
     for (int k = 0; k < F::N; ++k) v[k] += ws * G[(int64_t)k * NH + h];
   }
-  ring_store<LAT, DEV, S, MODEL, PARTIAL>(v, dst, g, itf, kf, om_f, tau_f, sig, r, xb);
+  int x, y, z;
+  fdecode(g, itf.rnode[r], x, y, z);
+  ring_store<LAT, DEV, S, MODEL, PARTIAL>(v, dst, g, x, y, z, kf, om_f, tau_f, sig, nullptr);
+}
+// D3Q19: a work group of 256 lanes takes tile t of the ring (ring3_tile): the
+// fields of the tile's 19 x 7 vertices go to LDS once, then every lane
+// interpolates one node from there.  Read per node through the table, a face
+// node took 16 entries and 16 values per field from the caches (RR on the
+// 385^3 patch: 887 k nodes, 1.1 GB); a tile reads 5.2 values per lane and two
+// vertices.  load(k, h) gives field k of history entry h; the sum is that of
+// ring_w over the table's points in its order.  Returns false where the lane
+// has no node; the whole work group calls it.
+constexpr int ring3_lds(int nf) { return (int)sizeof(double) * nf * kRingPU * kRingPV; }
+template <int NF, typename LoadF>
+__device__ __forceinline__ bool ring3_interp(char* raw, const Geo& g, int t, LoadF&& load, double* v, int& x, int& y,
+                                             int& z) {
+  constexpr int NPT = kRingPU * kRingPV;
+  double(*sv)[NPT] = reinterpret_cast<double(*)[NPT]>(raw);
+  int w, side, u0, v0;
+  if (!ring3_tile(g, t, w, side, u0, v0)) return false;  // whole work group
+  for (int p = threadIdx.x; p < NPT; p += 256) {
+    const int pv = p / kRingPU, h = ring3_vertex(g, w, side, u0, v0, p - pv * kRingPU, pv);
+    if (h >= 0) {
+#pragma unroll
+      for (int k = 0; k < NF; ++k) sv[k][p] = load(k, h);
+    }
+  }
+  __syncthreads();
+  const int lu = threadIdx.x % kRingU, lv = threadIdx.x / kRingU;
+  const int uu = u0 + lu, vv = v0 + lv, nu = ring3_nu(g, w), nv = ring3_nv(g, w);
+  // (a y face leaves its z edges to the z faces, an x face all edges)
+  if (uu >= nu || vv >= nv || (w < 2 && (vv == 0 || vv == nv - 1)) || (w == 0 && (uu == 0 || uu == nu - 1))) return false;
+  const int ou = uu & 1, ov = vv & 1;
+  // first stencil point inside the patch (odd: vertex (u - 3)/2; even: u/2)
+  const int bu = ou ? lu / 2 : lu / 2 + 1, bv = ov ? lv / 2 : lv / 2 + 1;
+#pragma unroll
+  for (int k = 0; k < NF; ++k) v[k] = 0.0;
+  for (int s1 = 0; s1 < (ov ? 4 : 1); ++s1)
+    for (int s0 = 0; s0 < (ou ? 4 : 1); ++s0) {
+      const double ws = (ou ? cubic_w(s0) : 1.0) * (ov ? cubic_w(s1) : 1.0);
+      const int p = bu + s0 + kRingPU * (bv + s1);
+#pragma unroll
+      for (int k = 0; k < NF; ++k) v[k] += ws * sv[k][p];
+    }
+  const int ww = side == 0 ? 0 : pick(w == 2, g.nf[2], pick(w == 1, g.nf[1], g.nf[0])) - 1;
+  x = w == 0 ? ww : uu;
+  y = w == 0 ? uu : (w == 1 ? ww : vv);
+  z = w == 2 ? ww : vv;
+  return true;
+}
+template <int LAT, bool DEV, typename S, int MODEL, bool PARTIAL>
+__device__ __forceinline__ void ring3_body(char* raw, const double* __restrict__ G, S* __restrict__ dst, const Geo& g,
+                                           int64_t NH, double kf, double om_f, double tau_f, double sig, int t,
+                                           S* __restrict__ xb) {
+  using F = HF<LAT, MODEL>;
+  double v[F::N];
+  int x, y, z;
+  if (ring3_interp<F::N>(raw, g, t, [&](int k, int h) __attribute__((always_inline)) { return G[(int64_t)k * NH + h]; }, v,
+                         x, y, z))
+    ring_store<LAT, DEV, S, MODEL, PARTIAL>(v, dst, g, x, y, z, kf, om_f, tau_f, sig, xb);
+}
+// rho, u only (as ring_macro_body), tile t.
+template <typename T>
+__device__ __forceinline__ void ring3_macro_body(char* raw, const double* __restrict__ Hm, const double* __restrict__ H0,
+                                                 const double* __restrict__ Hp, double c0, double c1, double c2,
+                                                 T* __restrict__ mac_f, const Geo& g, int64_t NH, int t) {
+  double v[4];
+  int x, y, z;
+  if (!ring3_interp<4>(raw, g, t,
+                       [&](int k, int h) __attribute__((always_inline)) {
+                         const int64_t o = (int64_t)k * NH + h;
+                         return c0 * Hm[o] + c1 * H0[o] + c2 * Hp[o];
+                       },
+                       v, x, y, z))
+    return;
+  const int64_t fi = fpos(g, x, y, z);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) mac_f[(int64_t)k * g.Nfp + fi] = (T)v[k];
+}
+// Ring nodes per work group of the launches that hold nothing but ring work:
+// kIfaceBlock table entries (D2Q9), a tile of 256 lanes (D3Q19).
+template <int LAT>
+constexpr int ring_block() {
+  return Lattice<LAT>::D == 2 ? kIfaceBlock : 256;
+}
+__host__ __device__ inline int64_t ring_groups(const Geo& g, int64_t NR, int lanes) {
+  return g.D == 3 ? ring3_tiles(g) : (NR + lanes - 1) / lanes;
 }
 // The t+1/2 ring of a D2Q9 BGK / RR level without the history capture before
 // it: the t+1 values of the node's (at most four) history points are captured
@@ -919,13 +997,32 @@ __device__ __forceinline__ void ring_half_body(const S* __restrict__ src, const 
       v[k] += ws * gv;
     }
   }
-  ring_store<LAT, DEV, S, MODEL, true>(v, dst, g, itf, kf, om_f, tau_f, sig, r, nullptr);
+  int x, y, z;
+  fdecode(g, itf.rnode[r], x, y, z);
+  ring_store<LAT, DEV, S, MODEL, true>(v, dst, g, x, y, z, kf, om_f, tau_f, sig, nullptr);
 }
+// Launches of ring work alone: work groups of ring_block lanes, XCD-contiguous.
 template <int LAT, bool DEV, typename S, int MODEL, bool PARTIAL>
 __global__ void k_ring(const double* __restrict__ G, S* __restrict__ dst, const Geo g, const Iface itf,
                        double kf, double om_f, double tau_f, double sig) {
-  ring_body<LAT, DEV, S, MODEL, PARTIAL>(G, dst, g, itf, kf, om_f, tau_f, sig,
-                                         xcd_block() * blockDim.x + threadIdx.x);
+  if constexpr (Lattice<LAT>::D == 3) {
+    __shared__ __attribute__((aligned(16))) char raw[ring3_lds(HF<LAT, MODEL>::N)];
+    ring3_body<LAT, DEV, S, MODEL, PARTIAL>(raw, G, dst, g, itf.NH, kf, om_f, tau_f, sig, (int)xcd_block(), nullptr);
+  } else {
+    ring_body<LAT, DEV, S, MODEL, PARTIAL>(G, dst, g, itf, kf, om_f, tau_f, sig,
+                                           xcd_block() * blockDim.x + threadIdx.x);
+  }
+}
+template <int LAT, typename T>
+__global__ void k_ring_macro(const double* __restrict__ Hm, const double* __restrict__ H0,
+                             const double* __restrict__ Hp, double c0, double c1, double c2,
+                             T* __restrict__ mac_f, const Geo g, const Iface itf) {
+  if constexpr (Lattice<LAT>::D == 3) {
+    __shared__ __attribute__((aligned(16))) char raw[ring3_lds(4)];
+    ring3_macro_body<T>(raw, Hm, H0, Hp, c0, c1, c2, mac_f, g, itf.NH, (int)xcd_block());
+  } else {
+    ring_macro_body<LAT, T>(Hm, H0, Hp, c0, c1, c2, mac_f, g, itf, xcd_block() * blockDim.x + threadIdx.x);
+  }
 }
 
 // H-RR: the t+1/2 ring populations (as k_ring, from G into dst) and the
@@ -939,9 +1036,17 @@ __global__ void k_ring_half_macro(const double* __restrict__ G, S* __restrict__ 
                                   int half) {
   const int part = (int)blockIdx.x >= half;
   const int b = (int)blockIdx.x - part * half, per = half / kXCD;
-  const int64_t r = ((int64_t)(b % kXCD) * per + b / kXCD) * blockDim.x + threadIdx.x;
-  if (part == 0) ring_body<LAT, DEV, S, MODEL, true>(G, dst, g, itf, kf, om_f, tau_f, sig, r);
-  else ring_macro_body<LAT, S>(Hm, H0, Hp, 0.0, 0.0, 1.0, mac_f, g, itf, r);
+  const int blk = (b % kXCD) * per + b / kXCD;
+  if constexpr (Lattice<LAT>::D == 3) {
+    __shared__ __attribute__((aligned(16))) char raw[ring3_lds(HF<LAT, MODEL>::N)];
+    if (part == 0)
+      ring3_body<LAT, DEV, S, MODEL, true>(raw, G, dst, g, itf.NH, kf, om_f, tau_f, sig, blk, nullptr);
+    else ring3_macro_body<S>(raw, Hm, H0, Hp, 0.0, 0.0, 1.0, mac_f, g, itf.NH, blk);
+  } else {
+    const int64_t r = (int64_t)blk * blockDim.x + threadIdx.x;
+    if (part == 0) ring_body<LAT, DEV, S, MODEL, true>(G, dst, g, itf, kf, om_f, tau_f, sig, r);
+    else ring_macro_body<LAT, S>(Hm, H0, Hp, 0.0, 0.0, 1.0, mac_f, g, itf, r);
+  }
 }
 
 
@@ -1144,8 +1249,8 @@ constexpr int kTnU = 8, kTnV = 2, kTnNodes = (2 * kTnU + 1) * (2 * kTnV + 1) * 3
 // Tiles of one face with normal axis w (0, 1, 2) along its two axes: the TN
 // nodes of a z face are x, y in [1, m - 1], of a y face x in [1, m - 1] and z
 // in [2, m - 2], of an x face y, z in [2, m - 2].
-__host__ __device__ inline int tn_nu(const Geo& g, int w) { return w == 0 ? g.m[1] - 3 : g.m[0] - 1; }
-__host__ __device__ inline int tn_nv(const Geo& g, int w) { return w == 2 ? g.m[1] - 1 : g.m[2] - 3; }
+__host__ __device__ inline int tn_nu(const Geo& g, int w) { return pick(w == 0, g.m[1] - 3, g.m[0] - 1); }
+__host__ __device__ inline int tn_nv(const Geo& g, int w) { return pick(w == 2, g.m[1] - 1, g.m[2] - 3); }
 __host__ __device__ inline int tn_face_tiles(const Geo& g, int w) {
   return ((tn_nu(g, w) + kTnU - 1) / kTnU) * ((tn_nv(g, w) + kTnV - 1) / kTnV);
 }
@@ -1153,7 +1258,7 @@ __host__ __device__ inline int tn_tiles(const Geo& g) {
   return 2 * (tn_face_tiles(g, 0) + tn_face_tiles(g, 1) + tn_face_tiles(g, 2));
 }
 template <int LAT, bool DEV, typename S, int MODEL>
-__device__ __forceinline__ void coalesce3_tile(const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g,
+__device__ __forceinline__ void coalesce3_tile(char* raw, const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g,
                                                double kc, double om_c, double tau_c, double sig, int64_t blk,
                                                const S* __restrict__ xb, double* __restrict__ su) {
   using L = Lattice<LAT>;
@@ -1161,7 +1266,9 @@ __device__ __forceinline__ void coalesce3_tile(const S* __restrict__ src_f, S* _
   using F = HF<LAT, MODEL>;
   constexpr int Q = L::Q, NC = F::NF1, PER = kTnU * kTnV;
   static_assert(L::D == 3 && kTnNodes <= 256, "one lane per fine node of a tile");
-  __shared__ double ne[NC][kTnNodes], mo[4][kTnNodes], sacc[NC][PER];
+  double(*ne)[kTnNodes] = reinterpret_cast<double(*)[kTnNodes]>(raw);
+  double(*mo)[kTnNodes] = ne + NC;
+  double(*sacc)[PER] = reinterpret_cast<double(*)[PER]>(mo + 4);
   // face and tile (scalars, not arrays indexed by the axis: those would live
   // in scratch memory)
   const int n2 = tn_face_tiles(g, 2), n1 = tn_face_tiles(g, 1), n0 = tn_face_tiles(g, 0);
@@ -1188,7 +1295,7 @@ __device__ __forceinline__ void coalesce3_tile(const S* __restrict__ src_f, S* _
   // first TN node (patch vertices), extent of the pulled box (its first fine
   // node is one before), LDS strides (x fastest)
   const int cu = kTnU * iu + (w == 0 ? 2 : 1), cv = kTnV * iv + (w == 2 ? 1 : 2);
-  const int mw = w == 2 ? g.m[2] : (w == 1 ? g.m[1] : g.m[0]), cw = side == 0 ? 1 : mw - 1;
+  const int mw = pick(w == 2, g.m[2], pick(w == 1, g.m[1], g.m[0])), cw = side == 0 ? 1 : mw - 1;
   const int eu = 2 * nu + 1, ev = 2 * nv + 1;
   const int cx0 = w == 0 ? cw : cu, cy0 = w == 0 ? cu : (w == 1 ? cw : cv), cz0 = w == 2 ? cw : cv;
   const int ex = w == 0 ? 3 : eu, ey = w == 0 ? eu : (w == 1 ? 3 : ev);
@@ -1313,15 +1420,21 @@ __host__ __device__ inline int coalesce_blocks(const Geo& g, int64_t NT) {
 // copy xb of its x-bands): a tile (D3Q19), or the TN nodes [blk PER, (blk + 1)
 // PER) of the table; the whole work group of 256 lanes calls it.
 template <int LAT, bool DEV, typename S, int MODEL>
-__device__ __forceinline__ void coalesce_body(const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g, const Iface& itf,
-                                     double kc, double om_c, double tau_c, double sig, int64_t blk,
+__device__ __forceinline__ void coalesce_body(char* raw, const S* __restrict__ src_f, S* __restrict__ dst_c, const Geo& g,
+                                     const Iface& itf, double kc, double om_c, double tau_c, double sig, int64_t blk,
                                      const S* __restrict__ xb = nullptr, double* __restrict__ su = nullptr) {
-  if constexpr (Lattice<LAT>::D == 3) {
-    coalesce3_tile<LAT, DEV, S, MODEL>(src_f, dst_c, g, kc, om_c, tau_c, sig, blk, xb, su);
-  } else {
-    __shared__ __attribute__((aligned(16))) char raw[coalesce_lds<LAT, MODEL, kTn2>()];
-    coalesce2_table<LAT, DEV, S, MODEL>(raw, src_f, dst_c, g, itf, kc, om_c, tau_c, sig, blk, xb, su);
-  }
+  if constexpr (Lattice<LAT>::D == 3)
+    coalesce3_tile<LAT, DEV, S, MODEL>(raw, src_f, dst_c, g, kc, om_c, tau_c, sig, blk, xb, su);
+  else coalesce2_table<LAT, DEV, S, MODEL>(raw, src_f, dst_c, g, itf, kc, om_c, tau_c, sig, blk, xb, su);
+}
+// LDS of a work group that takes either part of k_ring_coalesce.
+template <int LAT, int MODEL>
+constexpr int ring_coalesce_lds() {
+  constexpr int NC = HF<LAT, MODEL>::NF1;
+  constexpr int tn = Lattice<LAT>::D == 2 ? coalesce_lds<LAT, MODEL, kTn2>()
+                                          : (int)sizeof(double) * ((NC + 4) * kTnNodes + NC * kTnU * kTnV);
+  constexpr int ring = Lattice<LAT>::D == 2 ? 0 : ring3_lds(HF<LAT, MODEL>::N);
+  return tn > ring ? tn : ring;
 }
 
 // ---------------------------------------------------------------------------
@@ -1418,8 +1531,8 @@ __device__ __forceinline__ void coalesce2_segment(const S* __restrict__ src, con
 // bandwidth-bound, so they hide inside the stream.  D2Q9 rings capture the
 // history values they need themselves (ring_half_body); D3Q19 rings read G,
 // which the capture filled.  Blocks [0, nrb) take lanes ring nodes each
-// (dispatched first), the next nhb as many history nodes, the rest are the
-// stream's chunks; every part is XCD-contiguous.
+// (dispatched first; D3Q19: a tile), the next nhb as many history nodes, the
+// rest are the stream's chunks; every part is XCD-contiguous.
 // SENS: the stream also records the NH sensors' coarse velocities into su.
 template <int LAT, bool DEV, typename S, int MODEL, bool NT, bool SENS = false>
 __global__ __launch_bounds__(256) void k_stream_ring(const S* __restrict__ src, S* __restrict__ dst, const Geo g,
@@ -1430,14 +1543,16 @@ __global__ __launch_bounds__(256) void k_stream_ring(const S* __restrict__ src, 
                                                      int nrb, int nhb, S* __restrict__ xb, double* __restrict__ su) {
   const int b = blockIdx.x;
   if (b < nrb + nhb) {
-    if ((int)threadIdx.x >= lanes) return;
     const int c = b < nrb ? b : b - nrb, per = (b < nrb ? nrb : nhb) / kXCD;
-    const int64_t k = ((int64_t)(c % kXCD) * per + c / kXCD) * lanes + threadIdx.x;
+    const int64_t blk = (int64_t)(c % kXCD) * per + c / kXCD;
     if constexpr (Lattice<LAT>::D == 2) {
+      if ((int)threadIdx.x >= lanes) return;
+      const int64_t k = blk * lanes + threadIdx.x;
       if (b < nrb) ring_half_body<LAT, DEV, S, MODEL>(src, Hm, H0, fdst, g, itf, kf, om_f, tau_f, sig, k);
       else hist_capture_body<LAT, DEV, S, MODEL>(src, Hp, g, itf, k);
     } else {
-      ring_body<LAT, DEV, S, MODEL, true>(G, fdst, g, itf, kf, om_f, tau_f, sig, k, xb);
+      __shared__ __attribute__((aligned(16))) char raw[ring3_lds(HF<LAT, MODEL>::N)];
+      ring3_body<LAT, DEV, S, MODEL, true>(raw, G, fdst, g, itf.NH, kf, om_f, tau_f, sig, (int)blk, xb);
     }
   } else {
     const int b2 = b - nrb - nhb;
@@ -1460,14 +1575,17 @@ __global__ __launch_bounds__(256) void k_ring_coalesce(const double* __restrict_
                                                        double tau_f, double kc, double om_c, double tau_c, double sig,
                                                        int nrb, const S* __restrict__ xb, double* __restrict__ su) {
   const int b = blockIdx.x;
+  __shared__ __attribute__((aligned(16))) char raw[ring_coalesce_lds<LAT, MODEL>()];
   if (b < nrb) {
     const int per = nrb / kXCD;
     const int64_t blk = (int64_t)(b % kXCD) * per + b / kXCD;
-    ring_body<LAT, DEV, S, MODEL, true>(Hp, fdst, g, itf, kf, om_f, tau_f, sig, blk * 256 + threadIdx.x);
+    if constexpr (Lattice<LAT>::D == 3)
+      ring3_body<LAT, DEV, S, MODEL, true>(raw, Hp, fdst, g, itf.NH, kf, om_f, tau_f, sig, (int)blk, nullptr);
+    else ring_body<LAT, DEV, S, MODEL, true>(Hp, fdst, g, itf, kf, om_f, tau_f, sig, blk * 256 + threadIdx.x);
   } else {
     const int b2 = b - nrb, per = ((int)gridDim.x - nrb) / kXCD;
-    coalesce_body<LAT, DEV, S, MODEL>(src_f, dst_c, g, itf, kc, om_c, tau_c, sig,
-                                            (int64_t)(b2 % kXCD) * per + b2 / kXCD, xb, su);
+    coalesce_body<LAT, DEV, S, MODEL>(raw, src_f, dst_c, g, itf, kc, om_c, tau_c, sig,
+                                      (int64_t)(b2 % kXCD) * per + b2 / kXCD, xb, su);
   }
 }
 

@@ -432,6 +432,8 @@ struct Grid final : GridBase {
     hipLaunchKernelGGL((k_stream<LAT, DEV, S, MODEL, LEVEL, NT>), dim3((unsigned)(f.per_xcd * kXCD)), dim3(256),
                        (unsigned)kVarLds[v], s, src, dst, mac, g, f, (S)(1.0 - 1.0 / tau), xb);
   }
+  // Unused dynamic LDS of launch variant v for a kernel with `own` bytes.
+  static unsigned var_lds(int v, int own) { return (unsigned)std::max(0, kVarLds[v] - own); }
   // Interface nodes per work group of a launch shared with bulk work: one
   // wave while that spreads them over the chip (each lane's chain of dependent
   // loads and double-precision arithmetic is what such a part takes), whole
@@ -445,10 +447,10 @@ struct Grid final : GridBase {
                           double* su = nullptr) {
     if constexpr (MODEL != M_HRR) {
       const Flat f = flat(0);
-      const int lanes = iface_lanes(itf.NR, 256);
-      const unsigned nrb = xblocks(itf.NR, lanes), nhb = D == 2 ? xblocks(itf.NH, lanes) : 0;
+      const int lanes = D == 2 ? iface_lanes(itf.NR, 256) : 256;
+      const unsigned nrb = xblocks(ring_groups(g, itf.NR, lanes), 1), nhb = D == 2 ? xblocks(itf.NH, lanes) : 0;
       const dim3 gr(nrb + nhb + (unsigned)(f.per_xcd * kXCD)), bl(256);
-      const unsigned lds = (unsigned)kVarLds[var[0]];
+      const unsigned lds = var_lds(var[0], D == 3 ? ring3_lds(HF<LAT, MODEL>::N) : 0);
       const S om = (S)(1.0 - 1.0 / tau_c);
       const double *Hm = hist[hs[0]].as<double>(), *H0 = hist[hs[1]].as<double>();
       double* Hp = hist[hs[2]].as<double>();
@@ -466,7 +468,7 @@ struct Grid final : GridBase {
   template <int MODEL>
   void launch_ring_coalesce(const double* Hp, S* fdst, const S* src_f, S* cdst, const S* xb, double* su,
                             hipStream_t s) {
-    const unsigned br2 = xblocks(itf.NR, 256), bc = xblocks(coalesce_blocks(g, itf.NT), 1);
+    const unsigned br2 = xblocks(ring_groups(g, itf.NR, 256), 1), bc = xblocks(coalesce_blocks(g, itf.NT), 1);
     const double kf = tau_f / (2.0 * tau_c), kc = 2.0 * tau_c / tau_f;
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
     hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, MODEL>), dim3(br2 + bc), dim3(256), 0, s, Hp, fdst, src_f, cdst, g,
@@ -915,9 +917,9 @@ struct Grid final : GridBase {
     const double kf = tau_f / (2.0 * tau_c), kc = 2.0 * tau_c / tau_f;
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
     const double c0 = -1.0 / 8.0, c1 = 3.0 / 4.0, c2 = 3.0 / 8.0;  // eq TempInt at t+1/2
-    constexpr int IB = kIfaceBlock;
-    const unsigned bh = xblocks(NH, IB), br = xblocks(itf.NR, IB), bt = xblocks(itf.NT, IB);
-    const unsigned bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(itf.NR, 256);
+    constexpr int IB = kIfaceBlock, RB = ring_block<LAT>();
+    const unsigned bh = xblocks(NH, IB), br = xblocks(ring_groups(g, itf.NR, IB), 1), bt = xblocks(itf.NT, IB);
+    const unsigned bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(ring_groups(g, itf.NR, 256), 1);
     // D3Q19 BGK / RR: the capture also interpolates every history value to
     // t+1/2 (G); H-RR fills its strain-rate fields later and interpolates
     // then.  D2Q9 BGK / RR: it shares the coarse stream's launch.
@@ -974,14 +976,14 @@ struct Grid final : GridBase {
       if (coarse_vel_hook) coarse_vel_hook(s);  // nested child: the parent's ring rho, u
       if (fine_one_pass2()) {
         // one pass per fine substep (k_hrr2): ring rho, u first
-        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
+        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
         timed(s, [&] { launch_hrr2(fA, fB, mf, s, -1, true); });
       } else if (hrr_one_pass3()) {
-        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
+        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
         timed(s, [&] { launch_hrr3<1>(fA, fB, mf, s); });
       } else {
         launch_stream<M_HRR, 1>(fA, fB, mf, tau_f, s);
-        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
+        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
         timed(s, [&] { launch_collide_hrr<1>(fA, fB, mf, tau_f, s, hrr_lds_var(var[3]), true); });
       }
       hipLaunchKernelGGL((k_fict<LAT, DEV, S, S>), dim3(bt), dim3(IB), 0, s, fB, mc, g, itf);
@@ -997,10 +999,10 @@ struct Grid final : GridBase {
                            G.as<double>(), g, itf);
       if (fine_one_pass2() || hrr_one_pass3()) {
         // the t+1/2 ring and the t+1 ring velocities in one launch
-        hipLaunchKernelGGL((k_ring_half_macro<LAT, DEV, S, M_HRR>), dim3(2 * br), dim3(IB), 0, s, G.as<double>(), fB, Hm,
+        hipLaunchKernelGGL((k_ring_half_macro<LAT, DEV, S, M_HRR>), dim3(2 * br), dim3(RB), 0, s, G.as<double>(), fB, Hm,
                            H0, Hp, mf, g, itf, kf, omf, tau_f, sig, (int)br);
       } else {
-        hipLaunchKernelGGL((k_ring<LAT, DEV, S, M_HRR, true>), dim3(br), dim3(IB), 0, s, G.as<double>(), fB, g, itf, kf,
+        hipLaunchKernelGGL((k_ring<LAT, DEV, S, M_HRR, true>), dim3(br), dim3(RB), 0, s, G.as<double>(), fB, g, itf, kf,
                            omf, tau_f, sig);
       }
       if (fine_one_pass2()) {
@@ -1009,7 +1011,7 @@ struct Grid final : GridBase {
         timed(s, [&] { launch_hrr3<1>(fB, fA, mf, s); });
       } else {
         launch_stream<M_HRR, 1>(fB, fA, mf, tau_f, s);
-        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, s, Hm, H0, Hp, 0.0, 0.0, 1.0, mf, g, itf);
+        hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, s, Hm, H0, Hp, 0.0, 0.0, 1.0, mf, g, itf);
         timed(s, [&] { launch_collide_hrr<1>(fB, fA, mf, tau_f, s, hrr_lds_var(var[3]), true); });
       }
       // coarse collision before the TN transfer: the vector kernel also
@@ -1046,8 +1048,8 @@ struct Grid final : GridBase {
     const int64_t NH = itf.NH;
     const double kf = tau_f / (2.0 * tau_c), kc = 2.0 * tau_c / tau_f;
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
-    constexpr int IB = kIfaceBlock;
-    const unsigned bh = xblocks(NH, IB), bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(itf.NR, 256);
+    constexpr int IB = kIfaceBlock, RB = ring_block<LAT>();
+    const unsigned bh = xblocks(NH, IB), bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(ring_groups(g, itf.NR, 256), 1);
     if (D == 3)
       hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
                          G.as<double>(), Hm, H0);
@@ -1086,9 +1088,9 @@ struct Grid final : GridBase {
     const double kf = tau_f / (2.0 * tau_c), kc = 2.0 * tau_c / tau_f;
     const double omf = 1.0 - 1.0 / tau_f, omc = 1.0 - 1.0 / tau_c;
     const double c0 = -1.0 / 8.0, c1 = 3.0 / 4.0, c2 = 3.0 / 8.0;  // eq TempInt at t+1/2
-    constexpr int IB = kIfaceBlock;
-    const unsigned bh = xblocks(NH, IB), br = xblocks(itf.NR, IB), bt = xblocks(itf.NT, IB);
-    const unsigned bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(itf.NR, 256);
+    constexpr int IB = kIfaceBlock, RB = ring_block<LAT>();
+    const unsigned bh = xblocks(NH, IB), br = xblocks(ring_groups(g, itf.NR, IB), 1), bt = xblocks(itf.NT, IB);
+    const unsigned bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(ring_groups(g, itf.NR, 256), 1);
     const Geo gg = g;
     const Iface it = itf;
     hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, M_HRR>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf, nullptr, Hm,
@@ -1096,7 +1098,7 @@ struct Grid final : GridBase {
     const bool one_c = coarse_one_pass();
     if (!one_c) launch_stream<M_HRR, 0>(csrc, cdst, mc, tau_c, s);
     child->coarse_vel_hook = [=](hipStream_t st) {
-      hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, st, Hm, H0, Hp, c0, c1, c2, mf, gg, it);
+      hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, st, Hm, H0, Hp, c0, c1, c2, mf, gg, it);
     };
     child->step(1, s);
     hipLaunchKernelGGL((k_fict<LAT, DEV, S, S>), dim3(bt), dim3(IB), 0, s, fB, mc, g, itf);
@@ -1106,10 +1108,10 @@ struct Grid final : GridBase {
     else
       hipLaunchKernelGGL((k_hist_strain_time<LAT, DEV, S, false>), dim3(bh), dim3(IB), 0, s, csrc, mc, Hm, H0, Hp,
                          G.as<double>(), g, itf);
-    hipLaunchKernelGGL((k_ring<LAT, DEV, S, M_HRR, true>), dim3(br), dim3(IB), 0, s, G.as<double>(), fB, g, itf, kf,
+    hipLaunchKernelGGL((k_ring<LAT, DEV, S, M_HRR, true>), dim3(br), dim3(RB), 0, s, G.as<double>(), fB, g, itf, kf,
                        omf, tau_f, sig);
     child->coarse_vel_hook = [=](hipStream_t st) {
-      hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(IB), 0, st, Hm, H0, Hp, 0.0, 0.0, 1.0, mf, gg, it);
+      hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, st, Hm, H0, Hp, 0.0, 0.0, 1.0, mf, gg, it);
     };
     child->step(1, s);
     child->coarse_vel_hook = nullptr;
@@ -1131,7 +1133,7 @@ struct Grid final : GridBase {
   void complete_ring() {
     if (!ring_partial || !g.has_fine) return;
     const double kf = tau_f / (2.0 * tau_c), omf = 1.0 - 1.0 / tau_f;
-    const dim3 gr(xblocks(itf.NR, kIfaceBlock)), bl(kIfaceBlock);
+    const dim3 gr(xblocks(ring_groups(g, itf.NR, kIfaceBlock), 1)), bl(ring_block<LAT>());
     const double* H = hist[hs[1]].as<double>();
     if (desc.collision == LBM_BGK)
       hipLaunchKernelGGL((k_ring<LAT, DEV, S, M_BGK, false>), gr, bl, 0, stream, H, fineA(), g, itf, kf, omf, tau_f, sig);
@@ -1196,7 +1198,8 @@ struct Grid final : GridBase {
   void sensors_after(hipStream_t s) {
     if (!g.has_fine) return;
     // after the step the history levels t-1, t, t+1 are hs[2], hs[0], hs[1]
-    hipLaunchKernelGGL((k_ring_macro<LAT, double>), dim3(xblocks(itf.NR, kIfaceBlock)), dim3(kIfaceBlock), 0, s,
+    hipLaunchKernelGGL((k_ring_macro<LAT, double>), dim3(xblocks(ring_groups(g, itf.NR, kIfaceBlock), 1)),
+                       dim3(ring_block<LAT>()), 0, s,
                        hist[hs[2]].as<double>(), hist[hs[0]].as<double>(), hist[hs[1]].as<double>(), -1.0 / 8.0,
                        3.0 / 4.0, 3.0 / 8.0, sUf.as<double>(), g, itf);
   }
@@ -1700,7 +1703,7 @@ struct Batch final : BatchBase {
       for (int64_t c = 0; c < (nh + 63) / 64; ++c) lists[W_HIST].push_back({sl, (int)c});
       if (D == 3 && collision == LBM_HRR)
         for (int64_t c = 0; c < (nh * hfields + 63) / 64; ++c) lists[W_HTIME].push_back({sl, (int)c});
-      for (int64_t c = 0; c < (nr + 63) / 64; ++c) lists[W_RING].push_back({sl, (int)c});
+      for (int64_t c = 0; c < ring_groups(I.g, nr, 64); ++c) lists[W_RING].push_back({sl, (int)c});
       for (int64_t c = 0; c < (nt + 63) / 64; ++c) lists[W_TN].push_back({sl, (int)c});
       const int64_t ntb =
           I.fused ? coalesce2_count(I.g, tile_var == 0 ? fine2_nseg<kTileX[0] * kTileY[0]>() : fine2_nseg<kTileX[1] * kTileY[1]>())
@@ -1845,7 +1848,7 @@ struct Batch final : BatchBase {
     const Inst& in = *slots[(size_t)sl];
     const InstDev& I = hinst[(size_t)sl];
     const double kf = I.tau_f / (2.0 * I.tau_c), omf = 1.0 - 1.0 / I.tau_f;
-    const dim3 gr((unsigned)((in.itf.NR + 8 * kIfaceBlock - 1) / (8 * kIfaceBlock) * 8)), bl(kIfaceBlock);
+    const dim3 gr((unsigned)((ring_groups(in.g, in.itf.NR, kIfaceBlock) + kXCD - 1) / kXCD * kXCD)), bl(ring_block<LAT>());
     const double* H = I.hist[I.hs[1]];
     S* A = (S*)I.fbuf[I.fpar];
     if (collision == LBM_BGK)
@@ -2051,9 +2054,9 @@ struct Batch final : BatchBase {
       // the history capture too; D3Q19: the capture interpolated G); the t+1
       // ring and the transfer share a launch (D2Q9: the fused fine phase's)
       auto stream_ring = [&] {
-        const unsigned nrb = groups_of(W_RING, 4), nhb = D == 2 ? groups_of(W_HIST, 4) : 0;
-        hipLaunchKernelGGL((kb_stream_ring<LAT, DEV, S, MODEL, NT>), dim3(nrb + nhb + grid_of(W_COARSE).x), dim3(256),
-                           (unsigned)kVarLds[var_c], s, di(), items(W_RING), cnt(W_RING), items(W_HIST), cnt(W_HIST),
+        const unsigned nrb = D == 2 ? groups_of(W_RING, 4) : grid_of(W_RING).x, nhb = D == 2 ? groups_of(W_HIST, 4) : 0;
+        const unsigned lds = Grid<LAT, PREC>::var_lds(var_c, D == 3 ? ring3_lds(F::N) : 0);
+        hipLaunchKernelGGL((kb_stream_ring<LAT, DEV, S, MODEL, NT>), dim3(nrb + nhb + grid_of(W_COARSE).x), dim3(256), lds, s, di(), items(W_RING), cnt(W_RING), items(W_HIST), cnt(W_HIST),
                            items(W_COARSE), cnt(W_COARSE), (int)nrb, (int)nhb);
       };
       if constexpr (D == 2) {  // fused() for BGK / RR
@@ -2080,14 +2083,14 @@ struct Batch final : BatchBase {
     } else {
       phase_stream<M_HRR, 0, 0>(s, var_c);
       phase_stream<M_HRR, 1, 0>(s, var_f);
-      hipLaunchKernelGGL((kb_ring_macro<LAT, S, 0>), grid_of(W_RING), ib, 0, s, di(), items(W_RING), cnt(W_RING));
+      hipLaunchKernelGGL((kb_ring_macro<LAT, S, 0>), grid_of(W_RING), dim3(256), 0, s, di(), items(W_RING), cnt(W_RING));
       phase_collide<1, 0>(s, var_f);
       hipLaunchKernelGGL((kb_fict<LAT, DEV, S>), grid_of(W_TN), ib, 0, s, di(), items(W_TN), cnt(W_TN));
       hipLaunchKernelGGL((kb_hist_strain<LAT, DEV, S>), grid_of(W_HIST), ib, 0, s, di(), items(W_HIST), cnt(W_HIST));
       hipLaunchKernelGGL((kb_hist_time<F::N>), grid_of(W_HTIME), ib, 0, s, di(), items(W_HTIME), cnt(W_HTIME));
-      hipLaunchKernelGGL((kb_ring<LAT, DEV, S, M_HRR, 0>), grid_of(W_RING), ib, 0, s, di(), items(W_RING), cnt(W_RING));
+      hipLaunchKernelGGL((kb_ring<LAT, DEV, S, M_HRR, 0>), grid_of(W_RING), dim3(256), 0, s, di(), items(W_RING), cnt(W_RING));
       phase_stream<M_HRR, 1, 1>(s, var_f);
-      hipLaunchKernelGGL((kb_ring_macro<LAT, S, 1>), grid_of(W_RING), ib, 0, s, di(), items(W_RING), cnt(W_RING));
+      hipLaunchKernelGGL((kb_ring_macro<LAT, S, 1>), grid_of(W_RING), dim3(256), 0, s, di(), items(W_RING), cnt(W_RING));
       phase_collide<1, 1>(s, var_f);
       phase_collide<0, 0>(s, var_c);
       // the t+1 ring shares the transfer's launch (as for BGK / RR)
