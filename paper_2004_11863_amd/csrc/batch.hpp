@@ -475,6 +475,55 @@ __global__ __launch_bounds__(256) void kb_ring_coalesce(const InstDev* __restric
   }
 }
 
+// D3Q19 BGK / RR fine substeps with the interface work that shares their
+// launches, as k_stream_hist (substep 1, A -> B: blocks [0, nhb) take history
+// items, one per wave) and k_stream_tail (substep 2, B -> A: blocks [0, ncb)
+// take TN tiles, the next nrb ring tiles).
+template <int LAT, bool DEV, typename S, int MODEL, bool NT>
+__global__ __launch_bounds__(256) void kb_stream_hist(const InstDev* __restrict__ inst, const Work* __restrict__ hitems,
+                                                      const int* __restrict__ hcount, const Work* __restrict__ items,
+                                                      const int* __restrict__ count, int nhb) {
+  const int b = blockIdx.x;
+  if (b < nhb) {
+    const int it = wave_item<4>(b, *hcount);
+    if (it < 0) return;
+    const Work w = load_item(hitems, it);
+    const InstDev& I = inst[w.inst];
+    hist_capture_body<LAT, DEV, S, MODEL>(glob((const S*)I.ccur), glob(I.hist[I.hs[2]]), I.g, glob(I.itf),
+                                          (int64_t)w.idx * 64 + (threadIdx.x & 63), glob(I.G), glob(I.hist[I.hs[0]]),
+                                          glob(I.hist[I.hs[1]]));
+    return;
+  }
+  const int it = item_in(b - nhb, *count);
+  if (it < 0) return;
+  const Work w = load_item(items, it);
+  const InstDev& I = inst[w.inst];
+  stream_body<LAT, DEV, S, MODEL, 1, NT>(glob((const S*)I.fbuf[I.fpar]), glob((S*)I.fbuf[I.fpar ^ 1]), nullptr, I.g, I.ff,
+                                         (S)(1.0 - 1.0 / I.tau_f), w.idx, I.xb ? glob((S*)I.xb) : nullptr);
+}
+template <int LAT, bool DEV, typename S, int MODEL, bool NT>
+__global__ __launch_bounds__(256) void kb_stream_tail(const InstDev* __restrict__ inst, const Work* __restrict__ titems,
+                                                      const int* __restrict__ tcount, const Work* __restrict__ ritems,
+                                                      const int* __restrict__ rcount, const Work* __restrict__ items,
+                                                      const int* __restrict__ count, int ncb, int nrb) {
+  __shared__ __attribute__((aligned(16))) char raw[ring_coalesce_lds<LAT, MODEL>()];
+  const int b = blockIdx.x;
+  const int it = b < ncb ? item_in(b, *tcount) : (b < ncb + nrb ? item_in(b - ncb, *rcount) : item_in(b - ncb - nrb, *count));
+  if (it < 0) return;  // whole work group
+  const Work w = load_item(b < ncb ? titems : (b < ncb + nrb ? ritems : items), it);
+  const InstDev& I = inst[w.inst];
+  if (b < ncb) {
+    coalesce_body<LAT, DEV, S, MODEL>(raw, glob((const S*)I.fbuf[I.fpar ^ 1]), glob((S*)I.cnext), I.g, glob(I.itf),
+                                      2.0 * I.tau_c / I.tau_f, 1.0 - 1.0 / I.tau_c, I.tau_c, I.sig, w.idx,
+                                      I.xb ? glob((const S*)I.xb) : nullptr);
+  } else if (b < ncb + nrb) {
+    kb_ring_item<LAT, DEV, S, MODEL, 1>(I, w.idx, threadIdx.x, raw);
+  } else {
+    stream_body<LAT, DEV, S, MODEL, 1, NT, false, true>(glob((const S*)I.fbuf[I.fpar ^ 1]), glob((S*)I.fbuf[I.fpar]),
+                                                        nullptr, I.g, I.ff, (S)(1.0 - 1.0 / I.tau_f), w.idx);
+  }
+}
+
 // Uniform (single-level) instances: stream (+ collide) of the coarse level.
 // Handled by kb_stream LEVEL 0; nothing else runs for them.
 

@@ -272,7 +272,9 @@ __device__ __forceinline__ bool skip_vec(const Geo& g, int x0, int V, int y, int
 // SENS (BGK, RR): the NH sensors' velocity record of the state this call
 // leaves, the moments of the stored post-collision values in double (as
 // k_sens_vel takes them), into the planes su ([1 + D][padded positions]).
-template <int LAT, bool DEV, typename S, int MODEL, int LEVEL, bool NT, bool SENS = false>
+// MASK (fine level): the last vector of a row does not store the ring node
+// x = nx - 1, which the ring reconstruction writes in the same launch.
+template <int LAT, bool DEV, typename S, int MODEL, int LEVEL, bool NT, bool SENS = false, bool MASK = false>
 __device__ __forceinline__ void stream_body(const S* __restrict__ src, S* __restrict__ dst, S* __restrict__ mac, const Geo& g,
                                    const Flat& fl, const S om, int chunk, S* __restrict__ xb = nullptr,
                                    double* __restrict__ su = nullptr) {
@@ -331,8 +333,17 @@ __device__ __forceinline__ void stream_body(const S* __restrict__ src, S* __rest
       }
     }
   }
+  if (!MASK || x0 + V - 1 <= nx - 2) {
 #pragma unroll
-  for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), v[i]);
+    for (int i = 0; i < Q; ++i) vstore<NT>((VA*)(dst + pop_at<S, Q>(own, i)), v[i]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      if (x0 + k > nx - 2) continue;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) dst[pop_at<S, Q>(own + k, i)] = v[i][k];
+    }
+  }
   if (LEVEL == 1 && xb && (x0 <= 4 || x0 + V - 1 >= nx - 5)) {
     // A vector wholly inside a band goes out as one 16-byte store per
     // population (it may hold the ring column x = nx - 1: the ring
@@ -782,9 +793,12 @@ __device__ __forceinline__ void ring_macro_half_body(const S* __restrict__ src, 
   double v[1 + L::D];
 #pragma unroll
   for (int k = 0; k < 1 + L::D; ++k) v[k] = 0.0;
-  for (int s = 0; s < np; ++s) {
-    const int64_t h = pt[s];
-    const double ws = ring_w(np, s);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    // (one-point nodes repeat their point with weight 0: no branch, so the
+    // loads of all points are in flight together)
+    const int64_t h = pt[np == 1 ? 0 : s];
+    const double ws = np == 1 ? (s == 0 ? 1.0 : 0.0) : cubic_w(s);
     double c[F::S];
     hist_values<LAT, DEV, S, M_HRR>(src, g, itf.hnode[h], c);
 #pragma unroll
@@ -985,9 +999,12 @@ __device__ __forceinline__ void ring_half_body(const S* __restrict__ src, const 
   double v[F::N];
 #pragma unroll
   for (int k = 0; k < F::N; ++k) v[k] = 0.0;
-  for (int s = 0; s < np; ++s) {
-    const int64_t h = pt[s];
-    const double ws = ring_w(np, s);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    // (one-point nodes repeat their point with weight 0: no branch, so the
+    // loads of all points are in flight together)
+    const int64_t h = pt[np == 1 ? 0 : s];
+    const double ws = np == 1 ? (s == 0 ? 1.0 : 0.0) : cubic_w(s);
     double c[F::S];
     hist_values<LAT, DEV, S, MODEL>(src, g, itf.hnode[h], c);
 #pragma unroll
@@ -1587,6 +1604,55 @@ __global__ __launch_bounds__(256) void k_ring_coalesce(const double* __restrict_
     coalesce_body<LAT, DEV, S, MODEL>(raw, src_f, dst_c, g, itf, kc, om_c, tau_c, sig,
                                       (int64_t)(b2 % kXCD) * per + b2 / kXCD, xb, su);
   }
+}
+
+// D3Q19 BGK / RR fine substeps as two launches, with the interface work that
+// nothing in them waits for: beside substep 1 the history capture (blocks
+// [0, nhb), 256 nodes each; it reads the coarse state only), beside substep 2
+// the transfer (the t+1/2 state -> the TN nodes of dst_c, ncb tiles, first) and
+// the t+1 ring (Hp -> the substep's output, nrb tiles).  Two launches less in
+// the chain of a step that a small grid spends in launch latencies and in
+// launches too small for the chip: 70x61x66 BGK FP64 92.7 -> 80.2 us per step.
+// The capture gains wherever the fine level has two launches (160^3 FP32 RR 452
+// -> 445 us); the rest does for levels below Grid::kTailBytes.
+template <int LAT, bool DEV, typename S, int MODEL, bool NT>
+__global__ __launch_bounds__(256) void k_stream_hist(const S* __restrict__ src, S* __restrict__ dst, const Geo g,
+                                                     const Flat fl, const S om, S* __restrict__ xb,
+                                                     const S* __restrict__ csrc, double* __restrict__ Hp,
+                                                     double* __restrict__ G, const double* __restrict__ Hm,
+                                                     const double* __restrict__ H0, const Iface itf, int nhb) {
+  int b = blockIdx.x;
+  if (b < nhb) {
+    hist_capture_body<LAT, DEV, S, MODEL>(csrc, Hp, g, itf,
+                                          ((int64_t)(b % kXCD) * (nhb / kXCD) + b / kXCD) * 256 + threadIdx.x, G, Hm,
+                                          H0);
+    return;
+  }
+  b -= nhb;
+  stream_body<LAT, DEV, S, MODEL, 1, NT>(src, dst, nullptr, g, fl, om, (b % kXCD) * fl.per_xcd + b / kXCD, xb);
+}
+template <int LAT, bool DEV, typename S, int MODEL, bool NT>
+__global__ __launch_bounds__(256) void k_stream_tail(const S* __restrict__ src, S* __restrict__ dst,
+                                                     S* __restrict__ dst_c, const Geo g, const Flat fl, const S om,
+                                                     const double* __restrict__ Hp, const S* __restrict__ xb,
+                                                     const Iface itf, double kf, double om_f, double tau_f, double kc,
+                                                     double om_c, double tau_c, int ncb, int nrb,
+                                                     double* __restrict__ su) {
+  __shared__ __attribute__((aligned(16))) char raw[ring_coalesce_lds<LAT, MODEL>()];
+  int b = blockIdx.x;
+  if (b < ncb) {
+    coalesce_body<LAT, DEV, S, MODEL>(raw, src, dst_c, g, itf, kc, om_c, tau_c, 0.0,
+                                      (int64_t)(b % kXCD) * (ncb / kXCD) + b / kXCD, xb, su);
+    return;
+  }
+  b -= ncb;
+  if (b < nrb) {
+    ring3_body<LAT, DEV, S, MODEL, true>(raw, Hp, dst, g, itf.NH, kf, om_f, tau_f, 0.0,
+                                         (b % kXCD) * (nrb / kXCD) + b / kXCD, nullptr);
+    return;
+  }
+  b -= nrb;
+  stream_body<LAT, DEV, S, MODEL, 1, NT, false, true>(src, dst, nullptr, g, fl, om, (b % kXCD) * fl.per_xcd + b / kXCD);
 }
 
 // ---------------------------------------------------------------------------

@@ -432,6 +432,14 @@ struct Grid final : GridBase {
     hipLaunchKernelGGL((k_stream<LAT, DEV, S, MODEL, LEVEL, NT>), dim3((unsigned)(f.per_xcd * kXCD)), dim3(256),
                        (unsigned)kVarLds[v], s, src, dst, mac, g, f, (S)(1.0 - 1.0 / tau), xb);
   }
+  // D3Q19 BGK / RR fine levels stored in double and below this many bytes (two
+  // buffers) run the t+1 ring and the transfer beside their second substep
+  // (k_stream_tail).  RR step, beside it / in a launch of their own: 64^3 70.3 /
+  // 74.7 us, 96^3 182 / 195, 112^3 (0.44 GB) 285 / 299, 128^3 (0.65 GB) 403 /
+  // 399.  In float never: 64^3 56.4 / 54.7, 96^3 121 / 120, 112^3 173 / 163 (the
+  // tail's registers halve the waves of a stream that has twice the lanes' work).
+  static constexpr bool kTail = sizeof(S) == 8;
+  static constexpr double kTailBytes = 5e8;
   // Unused dynamic LDS of launch variant v for a kernel with `own` bytes.
   static unsigned var_lds(int v, int own) { return (unsigned)std::max(0, kVarLds[v] - own); }
   // Interface nodes per work group of a launch shared with bulk work: one
@@ -749,7 +757,17 @@ struct Grid final : GridBase {
     if (v < 0) v = var[1];
     if constexpr (D == 2) {
       switch (v) {
-        case 0: go_fine2<MODEL, 64, 8>(src, dst, half, cdst, s, su, suc); break;
+        case 0:
+          // A grid whose tiles leave most of the chip idle takes small ones:
+          // more work groups, fewer waves to a SIMD.  Step with 64 x 8 / 16 x 8
+          // lanes, RR: 64^2 FP64 12.5 / 11.6 us, 128^2 15.7 / 12.4, 256^2 13.8 /
+          // 13.5; FP32 128^2 14.6 / 13.8, 256^2 14.9 / 13.6; even from 320^2 on
+          // (where 32 x 8 lanes make half as many tiles as there are CUs).
+          if (fine2_ntx<S>(g, 32) * fine2_nty(g, 8) < n_cu / 2)
+            go_fine2<MODEL, 16, 8>(src, dst, half, cdst, s, su, suc);
+          else
+            go_fine2<MODEL, 64, 8>(src, dst, half, cdst, s, su, suc);
+          break;
         case 1: go_fine2<MODEL, 64, 16>(src, dst, half, cdst, s, su, suc); break;
         case 2: go_fine2<MODEL, 32, 16>(src, dst, half, cdst, s, su, suc); break;
         default: go_fine2<MODEL, 32, 8>(src, dst, half, cdst, s, su, suc); break;
@@ -922,8 +940,9 @@ struct Grid final : GridBase {
     const unsigned bc = xblocks(coalesce_blocks(g, itf.NT), 1), br2 = xblocks(ring_groups(g, itf.NR, 256), 1);
     // D3Q19 BGK / RR: the capture also interpolates every history value to
     // t+1/2 (G); H-RR fills its strain-rate fields later and interpolates
-    // then.  D2Q9 BGK / RR: it shares the coarse stream's launch.
-    if (D == 3 || (MODEL == M_HRR && !coarse_one_pass2()))
+    // then.  D2Q9, and D3Q19 BGK / RR with two fine launches: it shares a
+    // launch with bulk work.
+    if ((D == 3 && (MODEL == M_HRR || fused_now())) || (MODEL == M_HRR && !coarse_one_pass2()))
       hipLaunchKernelGGL((k_hist_capture<LAT, DEV, S, MODEL>), dim3(bh), dim3(IB), 0, s, csrc, Hp, g, itf,
                          MODEL == M_HRR ? nullptr : G.as<double>(), Hm, H0);
     timed_factor = fused_now() ? 2 : 1;
@@ -945,11 +964,32 @@ struct Grid final : GridBase {
       // substep 1 writes the ring column x = nx - 1 of B, so the t+1/2 ring
       // (sharing a launch with the coarse stream) follows it; both also fill
       // the compact copy of the x-bands, from which the transfer reads
-      S* xb = xbuf.as<S>();
-      fine_stream_timed(MODEL, fA, fB, s, xb);
-      launch_stream_ring<MODEL>(csrc, cdst, fB, kf, omf, s, xb, scn);
-      fine_stream_timed(MODEL, fB, fA, s);
-      launch_ring_coalesce<MODEL>(Hp, fA, fB, cdst, xb, scn, s);
+      if constexpr (MODEL != M_HRR && D == 3) {
+        S* xb = xbuf.as<S>();
+        const Flat f = flat(1);
+        const S om = (S)omf;
+        const int lv = fine_lds_var(var[1]);
+        const unsigned nhb = xblocks(NH, 256), nch = (unsigned)(f.per_xcd * kXCD);
+        timed(s, [&] {
+          hipLaunchKernelGGL((k_stream_hist<LAT, DEV, S, MODEL, NT>), dim3(nhb + nch), dim3(256), (unsigned)kVarLds[lv], s,
+                             fA, fB, g, f, om, xb, csrc, Hp, G.as<double>(), Hm, H0, itf, (int)nhb);
+        });
+        launch_stream_ring<MODEL>(csrc, cdst, fB, kf, omf, s, xb, scn);
+        bool tail = false;
+        if constexpr (kTail) {
+          if ((tail = level_bytes(1) < kTailBytes)) {
+            const unsigned lds = var_lds(lv, ring_coalesce_lds<LAT, MODEL>());
+            timed(s, [&] {
+              hipLaunchKernelGGL((k_stream_tail<LAT, DEV, S, MODEL, NT>), dim3(bc + br2 + nch), dim3(256), lds, s, fB, fA,
+                                 cdst, g, f, om, Hp, xb, itf, kf, omf, tau_f, kc, omc, tau_c, (int)bc, (int)br2, scn);
+            });
+          }
+        }
+        if (!tail) {
+          fine_stream_timed(MODEL, fB, fA, s);
+          launch_ring_coalesce<MODEL>(Hp, fA, fB, cdst, xb, scn, s);
+        }
+      }
     } else if (coarse_one_pass2()) {
       // D2Q9 H-RR in five launches: capture + t+1/2 ring rho, u; fine substep 1;
       // fictitious propagation + strain rate + temporal interpolation of the
@@ -1625,6 +1665,9 @@ struct Batch final : BatchBase {
   // tiles of shape tile_var (fine) and ctile_var (coarse).
   bool hrr2() const { return D == 2 && collision == LBM_HRR; }
   int tile_var = 0, ctile_var = 0;
+  // D3Q19 BGK / RR: the t+1 ring and the transfer run beside substep 2 (as
+  // Grid::kTail, kTailBytes, for the fine levels of all grids together).
+  bool tail_shared = false;
   std::vector<std::unique_ptr<Inst>> slots;
   std::vector<InstDev> hinst;
   std::vector<int64_t> steps_done;
@@ -1687,9 +1730,11 @@ struct Batch final : BatchBase {
     std::vector<Work> lists[W_KINDS];
     const int hfields = collision == LBM_BGK ? HF<LAT, M_BGK>::N : (collision == LBM_RR ? HF<LAT, M_RR>::N
                                                                                          : HF<LAT, M_HRR>::N);
+    double fine_bytes = 0;
     for (int sl = 0; sl < capacity; ++sl) {
       if (!slots[(size_t)sl]) continue;
       const InstDev& I = hinst[(size_t)sl];
+      if (I.g.has_fine) fine_bytes += 2.0 * (double)sizeof(S) * (double)pop_elems<S>(I.g.Nfp, Q);
       if (hrr2()) {
         const int nc = hrr2c_ntx<S>(I.g, kTileX[ctile_var]) * hrr2c_nty(I.g, kTileY[ctile_var]);
         for (int c = 0; c < nc; ++c) lists[W_CTILE].push_back({sl, c});
@@ -1714,6 +1759,9 @@ struct Batch final : BatchBase {
         for (int c = 0; c < ntile; ++c) lists[W_TILE].push_back({sl, c});
       }
     }
+    const bool tail = Grid<LAT, PREC>::kTail && fine_bytes < Grid<LAT, PREC>::kTailBytes;
+    if (tail != tail_shared) drop_graph();  // another launch sequence
+    tail_shared = tail;
     for (int k = 0; k < W_KINDS; ++k) {
       grow_items(k, lists[k].size());
       counts[k] = (int)lists[k].size();
@@ -2046,7 +2094,7 @@ struct Batch final : BatchBase {
   void launch_step_model(hipStream_t s) {
     using F = HF<LAT, MODEL>;
     const dim3 ib(64);
-    if (D == 3)
+    if (D == 3 && MODEL == M_HRR)
       hipLaunchKernelGGL((kb_hist_capture<LAT, DEV, S, MODEL>), grid_of(W_HIST), ib, 0, s, di(), items(W_HIST),
                          cnt(W_HIST));
     if constexpr (MODEL != M_HRR) {
@@ -2063,12 +2111,25 @@ struct Batch final : BatchBase {
         stream_ring();
         phase_fine2<MODEL>(s);
       } else {
-        phase_stream<MODEL, 1, 0>(s, var_f);  // writes B's ring column: the t+1/2 ring follows
+        const unsigned nhb = groups_of(W_HIST, 4), ncb = grid_of(W_TNB).x, nrb = grid_of(W_RING).x;
+        // writes B's ring column: the t+1/2 ring follows
+        hipLaunchKernelGGL((kb_stream_hist<LAT, DEV, S, MODEL, NT>), dim3(nhb + grid_of(W_FINE).x), dim3(256),
+                           (unsigned)kVarLds[var_f], s, di(), items(W_HIST), cnt(W_HIST), items(W_FINE), cnt(W_FINE),
+                           (int)nhb);
         stream_ring();
-        phase_stream<MODEL, 1, 1>(s, var_f);
-        const unsigned nrb = grid_of(W_RING).x;
-        hipLaunchKernelGGL((kb_ring_coalesce<LAT, DEV, S, MODEL>), dim3(nrb + grid_of(W_TNB).x), dim3(256), 0, s, di(),
-                           items(W_RING), cnt(W_RING), items(W_TNB), cnt(W_TNB), (int)nrb);
+        if constexpr (Grid<LAT, PREC>::kTail) {
+          if (tail_shared) {
+            const unsigned lds = Grid<LAT, PREC>::var_lds(var_f, ring_coalesce_lds<LAT, MODEL>());
+            hipLaunchKernelGGL((kb_stream_tail<LAT, DEV, S, MODEL, NT>), dim3(ncb + nrb + grid_of(W_FINE).x), dim3(256),
+                               lds, s, di(), items(W_TNB), cnt(W_TNB), items(W_RING), cnt(W_RING), items(W_FINE),
+                               cnt(W_FINE), (int)ncb, (int)nrb);
+          }
+        }
+        if (!tail_shared) {
+          phase_stream<MODEL, 1, 1>(s, var_f);
+          hipLaunchKernelGGL((kb_ring_coalesce<LAT, DEV, S, MODEL>), dim3(nrb + ncb), dim3(256), 0, s, di(),
+                             items(W_RING), cnt(W_RING), items(W_TNB), cnt(W_TNB), (int)nrb);
+        }
       }
     } else if constexpr (D == 2) {
       // as the single grid's five launches

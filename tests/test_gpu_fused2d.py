@@ -40,3 +40,24 @@ def test_transfer_segments(model, mx, my):
                 ref = f
             for a, b in zip(f, ref):
                 assert np.array_equal(a, b), (prec, v)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_tiles_by_size(prec):
+    """The default takes small tiles where large ones would leave the chip idle;
+    a long patch on the other side of that line equals the named tile shapes."""
+    from paper_2004_11863_amd import lbm
+    n, lo, hi = (1100, 60, 1), (20, 10, 0), (1063, 49, 0)
+    wl = I.Workload(geom=I.Geometry(2, n, lo, hi), U=(0.05, -0.02, 0.0),
+                    vortices=[I.Vortex(center=(1050.0, 40.0), eps=0.01, Rc=4.0)])
+    ref = None
+    for v in range(lbm.LBM_N_VARIANTS):
+        gpu, _, levels = make_pair(wl, "RR", lbm.LBM_FP64 if prec == "fp64" else lbm.LBM_FP32_DEV, with_oracle=False)
+        gpu.set_variants([0, v, 0, 0])
+        gpu.step(4)
+        f = [gpu.get_populations(lv) for lv in levels]
+        f[0] = f[0][:, gpu.class_map(0) != lbm.LBM_C_COVERED]
+        gpu.close()
+        ref = f if ref is None else ref
+        for a, b in zip(f, ref):
+            assert np.isfinite(a).all() and np.array_equal(a, b), v

@@ -82,3 +82,37 @@ def test_d2q9_hrr_ragged_rows(n):
         assert np.array_equal(batch.get_populations(slots[1], 0), alone.get_populations(0))
         alone.close()
         batch.close()
+
+
+def test_d3q19_tail_limit():
+    """Small fine levels in double run the ring and the transfer beside substep
+    2, large ones behind it: a patch above the limit gives the bits of the
+    marching kernel, alone and in a batch that it takes over the limit."""
+    from paper_2004_11863_amd import lbm
+    small = _workload(3, (20, 18, 16), (3, 4, 5), (15, 13, 11))
+    large = _workload(3, (78, 70, 60), (4, 5, 5), (74, 65, 55))
+
+    def alone(wl, steps, v):
+        gpu, _, levels = make_pair(wl, "RR", lbm.LBM_FP64, with_oracle=False)
+        gpu.set_variants([0, v, 0, 0])
+        gpu.step(steps)
+        f = [gpu.get_populations(lv) for lv in levels]
+        live = gpu.class_map(0) != lbm.LBM_C_COVERED
+        gpu.close()
+        return [f[0][:, live], f[1]], live
+
+    b = lbm.Batch(lbm.LBM_D3Q19, lbm.LBM_RR, lbm.LBM_FP64, 2)
+    slots = []
+    for wl in (small, large):
+        g = wl.geom
+        slots.append(b.add(g.n, g.lo, g.hi, tau_coarse=0.51))
+        for lv in (0, 1):
+            b.set_state(slots[-1], lv, *I.fields(wl, lv))
+        b.step(2)
+    ref, live = alone(large, 2, 2)
+    for f in (alone(large, 2, 0)[0], [b.get_populations(slots[1], 0)[:, live], b.get_populations(slots[1], 1)]):
+        assert all(np.isfinite(a).all() and np.array_equal(a, r) for a, r in zip(f, ref))
+    ref, live = alone(small, 4, 0)
+    f = [b.get_populations(slots[0], 0)[:, live], b.get_populations(slots[0], 1)]
+    assert all(np.array_equal(a, r) for a, r in zip(f, ref))
+    b.close()
