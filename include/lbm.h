@@ -296,8 +296,8 @@ const char* lbm_last_error(lbm_handle h);
  * Batches: many independent grids of one lattice, collision model and
  * precision, each with its own geometry, tau and sigma, advanced together.
  * Each coarse step is one sequence of launches over the work of all grids
- * (bulk chunks, interface node blocks), captured once as a hipGraph and
- * replayed; grids may join and leave between steps (continuous batching),
+ * (bulk chunks, interface node blocks), captured once as a hipGraph (one step
+ * and a run of six) and replayed; grids may join and leave between steps (continuous batching),
  * which rewrites device work lists (the launch is captured again when a list
  * outgrows its buffer, after lbm_batch_tune or lbm_batch_set_variants, and
  * when graphs are switched off and on).  A grid in a batch computes exactly what the

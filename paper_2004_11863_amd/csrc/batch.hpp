@@ -45,6 +45,25 @@ struct InstDev {
   int ntxc;   // D2Q9 H-RR: coarse tiles per row of tiles
 };
 
+// One coarse step exchanges the two coarse buffers (and, fused, the two fine
+// ones) and rotates the three history buffers, so kPhases steps restore a
+// descriptor.  The table holds every descriptor at each of these phases, entry
+// kPhases k + p that of slot k after p steps: a run of kPhases steps reads
+// phase after phase and leaves the table as it is; a step on its own is
+// followed by kb_advance.
+constexpr int kPhases = 6;
+__host__ __device__ inline void advance(InstDev& I) {
+  I.cpar ^= 1;
+  I.fpar ^= I.fused;
+  void* t = I.ccur;
+  I.ccur = I.cnext;
+  I.cnext = t;
+  const int old = I.hs[0];
+  I.hs[0] = I.hs[1];
+  I.hs[1] = I.hs[2];
+  I.hs[2] = old;
+}
+
 // Pointers read from the descriptor table are generic to the compiler, which
 // then issues flat memory instructions; every buffer lives in device global
 // memory, and saying so gives global loads and stores (vector memory
@@ -527,19 +546,10 @@ __global__ __launch_bounds__(256) void kb_stream_tail(const InstDev* __restrict_
 // Uniform (single-level) instances: stream (+ collide) of the coarse level.
 // Handled by kb_stream LEVEL 0; nothing else runs for them.
 
-// End of a coarse step: every active instance moves to the next time level.
+// End of a coarse step outside a run of kPhases: the n descriptors move on.
 __global__ void kb_advance(InstDev* __restrict__ inst, int n) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n || !inst[k].active) return;
-  inst[k].cpar ^= 1;
-  inst[k].fpar ^= inst[k].fused;
-  void* t = inst[k].ccur;
-  inst[k].ccur = inst[k].cnext;
-  inst[k].cnext = t;
-  const int old = inst[k].hs[0];
-  inst[k].hs[0] = inst[k].hs[1];
-  inst[k].hs[1] = inst[k].hs[2];
-  inst[k].hs[2] = old;
+  if (k < n && inst[k].active) advance(inst[k]);
 }
 
 }  // namespace lbm

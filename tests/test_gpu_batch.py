@@ -274,3 +274,24 @@ def test_batch_d2q9_fp64_matches_oracle(model):
             assert np.abs(r1 - r0).max() <= 1e-12 * np.abs(r0).max(), (sl, lv)
             assert np.abs(u1 - u0).max() <= 1e-12 * np.abs(u0).max(), (sl, lv)
     batch.close()
+
+
+@pytest.mark.parametrize("graph", [True, False])
+@pytest.mark.parametrize("model", ["BGK", "HRR"])
+def test_runs_of_steps(model, graph):
+    """Runs of six steps, remainders, and a grid that joins between them."""
+    lbm = _lbm()
+    wl = [_wl(g, k) for k, g in enumerate(_geoms2d())]
+    code = {"BGK": lbm.LBM_BGK, "HRR": lbm.LBM_HRR}[model]
+    b = lbm.Batch(lbm.LBM_D2Q9, code, lbm.LBM_FP32_DEV, len(wl))
+    b.use_graph(graph)
+    slots, done = [], []
+    for joins, steps in ((2, 6), (1, 1), (0, 13), (1, 5), (0, 8)):
+        for _ in range(joins):
+            slots.append(_add(b, wl[len(slots)]))
+            done.append(0)
+        b.step(steps)
+        done = [d + steps for d in done]
+    for sl, w, n in zip(slots, wl, done):
+        _check_same(b, sl, _alone(w, model, lbm.LBM_FP32_DEV, n))
+    b.close()
