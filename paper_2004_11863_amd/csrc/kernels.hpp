@@ -2599,10 +2599,19 @@ __global__ __launch_bounds__(TXH * TYH) void k_fine3s(const S* __restrict__ src,
 // 945 -> 783 us for the 257^3 fine level of a 256^3 grid, FP32, 64 x 8
 // tiles), and rows are long (64 x 8 783 us, 34 x 15 659, 66 x 15 616,
 // 130 x 7 612).
+//
+// With out set (LEVEL 0) the velocities of the nodes up to two outside the
+// patch also go to the velocity planes out, where the strain rate at the
+// history nodes reads them; pulled there instead, six neighbours a node,
+// k_hist_strain_time took 104 us for the 128^3 patch of a 256^3 grid in FP32,
+// now 29.  (The same for the fine x-bands, which the transfer gathers: 211 ->
+// 99 us there, but the substep 612 -> 720 us: the edge waves' extra stores set
+// the pace of their work groups.)
 template <int LAT, bool DEV, typename S, int LEVEL, int TXH, int TYH>
 __global__ __launch_bounds__(TXH * TYH) void k_hrr3s(const S* __restrict__ src, S* __restrict__ dst,
                                                      const S* __restrict__ mac, const Geo g, const S om, const S tau,
-                                                     const S sig, int ntx, int nty, int nzc, int zlen, int per_xcd) {
+                                                     const S sig, int ntx, int nty, int nzc, int zlen, int per_xcd,
+                                                     S* __restrict__ out) {
   using L = Lattice<LAT>;
   using N = Node<LAT, DEV, S>;
   constexpr int Q = L::Q, NL = TXH * TYH;
@@ -2670,6 +2679,10 @@ __global__ __launch_bounds__(TXH * TYH) void k_hrr3s(const S* __restrict__ src, 
   auto zw = [&](int z) __attribute__((always_inline)) {
     return LEVEL == 0 ? wrap(z, nz) : min(max(z, 0), nz - 1);
   };
+  // lanes whose nodes also go to out, and whether the wave has any
+  const bool near = LEVEL == 0 && inner && xw >= g.a[0] - 2 && xw <= g.a[0] + g.m[0] + 2 && yw >= g.a[1] - 2 &&
+                    yw <= g.a[1] + g.m[1] + 2;
+  const int keep = LEVEL == 0 && out != nullptr ? __builtin_amdgcn_readfirstlane(__any(near)) : 0;
   S H[Q], P0[Q], P1[Q], U0[3], U1[3];
   // pulls of plane zq into P; given velocities from the velocity planes into UR
   auto load = [&](int zq, S (&P)[Q], S (&UR)[3]) __attribute__((always_inline)) {
@@ -2750,6 +2763,19 @@ __global__ __launch_bounds__(TXH * TYH) void k_hrr3s(const S* __restrict__ src, 
     const uint32_t bo = Wn::boff(q0 + (uint32_t)(pz * z - W.pb0)) | (gone(z) ? Wn::kOff : minner);
 #pragma unroll
     for (int i = 0; i < Q; ++i) Wn::template store<false>(rd, bo, i, Hc[i]);
+    if (keep && z >= g.a[2] - 2 && z <= g.a[2] + g.m[2] + 2) {
+      const uint32_t mo = (uint32_t)sizeof(S) * q0 | (near && !gone(z) ? 0u : Wn::kOff);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(out + (int64_t)(1 + k) * NP + pz * z), (short)0, (int)Wn::kOff, 0x00020000);
+        const S v = lu[z & 3][k][t];
+        if constexpr (sizeof(S) == 4)
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), ru, (int)mo, 0, 0);
+        else
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(typename Wn::u2, v), ru, (int)mo, 0, 0);
+      }
+    }
   };
   for (int z = zs; z <= ze; z += 2) {
     iter(z, P0, U0);

@@ -720,7 +720,7 @@ struct Grid final : GridBase {
   }
   int hrr_lds_var(int v) const { return (D == 3 && desc.collision == LBM_HRR) ? (v == 0 ? 2 : 1) : v; }
   template <int LEVEL, int TXH, int TYH>
-  void go_hrr3s(const S* src, S* dst, const S* mac, hipStream_t s, int v) {
+  void go_hrr3s(const S* src, S* dst, const S* mac, hipStream_t s, int v, S* out) {
     if constexpr (D == 3) {
       auto kern = k_hrr3s<LAT, DEV, S, LEVEL, TXH, TYH>;
       // coarse: every node; fine: the middle nodes
@@ -730,25 +730,27 @@ struct Grid final : GridBase {
                                   occupancy_slots(kern, h3_slots[2 * LEVEL + (v & 1)], TXH * TYH));
       const double tau = LEVEL == 0 ? tau_c : tau_f;
       hipLaunchKernelGGL(kern, dim3((unsigned)(r.per * kXCD)), dim3(TXH * TYH), 0, s, src, dst, mac, g,
-                         (S)(1.0 - 1.0 / tau), (S)tau, (S)sig, r.ntx, r.nty, r.nzc, r.zlen, r.per);
+                         (S)(1.0 - 1.0 / tau), (S)tau, (S)sig, r.ntx, r.nty, r.nzc, r.zlen, r.per, out);
     }
   }
+  // out (coarse): the velocity planes that keep the velocities around the
+  // patch, or null
   template <int LEVEL>
-  void launch_hrr3(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1) {
+  void launch_hrr3(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1, S* out = nullptr) {
     if (v < 0) v = var[2 + LEVEL];
     if constexpr (sizeof(S) == 4) {
-      if (v == 2) go_hrr3s<LEVEL, 130, 7>(src, dst, mac, s, v);
-      else go_hrr3s<LEVEL, 66, 15>(src, dst, mac, s, v);
+      if (v == 2) go_hrr3s<LEVEL, 130, 7>(src, dst, mac, s, v, out);
+      else go_hrr3s<LEVEL, 66, 15>(src, dst, mac, s, v, out);
     } else {
-      if (v == 2) go_hrr3s<LEVEL, 66, 7>(src, dst, mac, s, v);
-      else go_hrr3s<LEVEL, 34, 15>(src, dst, mac, s, v);
+      if (v == 2) go_hrr3s<LEVEL, 66, 7>(src, dst, mac, s, v, out);
+      else go_hrr3s<LEVEL, 34, 15>(src, dst, mac, s, v, out);
     }
   }
   // The coarse H-RR step: in one pass, or the collision after the velocity
   // pass (which the caller launched).
   void launch_coarse_hrr(const S* src, S* dst, const S* mac, hipStream_t s) {
     if (coarse_one_pass2()) launch_hrr2c(src, dst, mac, s, -1, true);
-    else if (coarse_one_pass()) launch_hrr3<0>(src, dst, mac, s);
+    else if (coarse_one_pass()) launch_hrr3<0>(src, dst, mac, s, -1, g.has_fine ? const_cast<S*>(mac) : nullptr);
     else launch_collide_hrr<0>(src, dst, mac, tau_c, s, hrr_lds_var(var[2]), true);
   }
   template <int MODEL>
@@ -1028,15 +1030,12 @@ struct Grid final : GridBase {
       }
       hipLaunchKernelGGL((k_fict<LAT, DEV, S, S>), dim3(bt), dim3(IB), 0, s, fB, mc, g, itf);
       // the coarse velocities at the history nodes' neighbours: from the
-      // velocity pass, or (one-pass coarse level) pulled here
-      // strain rate at the history nodes, then the temporal interpolation
-      // of their fields (one thread per history node, one launch)
-      if (one_c)
-        hipLaunchKernelGGL((k_hist_strain_time<LAT, DEV, S, true>), dim3(bh), dim3(IB), 0, s, csrc, mc, Hm, H0, Hp,
-                           G.as<double>(), g, itf);
-      else
-        hipLaunchKernelGGL((k_hist_strain_time<LAT, DEV, S, false>), dim3(bh), dim3(IB), 0, s, csrc, mc, Hm, H0, Hp,
-                           G.as<double>(), g, itf);
+      // velocity pass, or kept by the one-pass coarse step; then the strain
+      // rate at the history nodes and the temporal interpolation of their
+      // fields (one thread per history node, one launch)
+      if (one_c) launch_coarse_hrr(csrc, cdst, mc, s);
+      hipLaunchKernelGGL((k_hist_strain_time<LAT, DEV, S, false>), dim3(bh), dim3(IB), 0, s, csrc, mc, Hm, H0, Hp,
+                         G.as<double>(), g, itf);
       if (fine_one_pass2() || hrr_one_pass3()) {
         // the t+1/2 ring and the t+1 ring velocities in one launch
         hipLaunchKernelGGL((k_ring_half_macro<LAT, DEV, S, M_HRR>), dim3(2 * br), dim3(RB), 0, s, G.as<double>(), fB, Hm,
@@ -1057,7 +1056,7 @@ struct Grid final : GridBase {
       // coarse collision before the TN transfer: the vector kernel also
       // passes over TN nodes, which the transfer then overwrites; the t+1
       // ring (into fine A, independent of both) shares the transfer's launch
-      launch_coarse_hrr(csrc, cdst, mc, s);
+      if (!one_c) launch_coarse_hrr(csrc, cdst, mc, s);
       hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, M_HRR>), dim3(br2 + bc), dim3(256), 0, s, Hp, fA, fB, cdst, g,
                          itf, kf, omf, tau_f, kc, omc, tau_c, sig, (int)br2, (const S*)nullptr, (double*)nullptr);
     }
@@ -1142,7 +1141,11 @@ struct Grid final : GridBase {
     };
     child->step(1, s);
     hipLaunchKernelGGL((k_fict<LAT, DEV, S, S>), dim3(bt), dim3(IB), 0, s, fB, mc, g, itf);
-    if (one_c)
+    // (one pass: the D3Q19 coarse step keeps the velocities the strain rate
+    // reads, D2Q9 pulls them)
+    const bool keeps = one_c && D == 3;
+    if (keeps) launch_coarse_hrr(csrc, cdst, mc, s);
+    if (one_c && !keeps)
       hipLaunchKernelGGL((k_hist_strain_time<LAT, DEV, S, true>), dim3(bh), dim3(IB), 0, s, csrc, mc, Hm, H0, Hp,
                          G.as<double>(), g, itf);
     else
@@ -1155,7 +1158,7 @@ struct Grid final : GridBase {
     };
     child->step(1, s);
     child->coarse_vel_hook = nullptr;
-    launch_coarse_hrr(csrc, cdst, mc, s);
+    if (!keeps) launch_coarse_hrr(csrc, cdst, mc, s);
     hipLaunchKernelGGL((k_ring_coalesce<LAT, DEV, S, M_HRR>), dim3(br2 + bc), dim3(256), 0, s, Hp, fA, fB, cdst, g,
                        itf, kf, omf, tau_f, kc, omc, tau_c, sig, (int)br2, (const S*)nullptr, (double*)nullptr);
     HIPCHK(hipGetLastError());
