@@ -333,6 +333,14 @@ struct Grid final : GridBase {
     // H-RR, from 2 GB: 200^3 FP32 1437 us a step in two passes, 1483 in one;
     // 256^3 2481 and 2440; 384^3 7634 and 7320.  lbm_tune times them all.
     if (fused) var[1] = D == 2 || level_bytes(1) < 1e8 ? 0 : (DEV && g.nf[0] <= 256 ? 3 : 2);
+    // D2Q9 H-RR tiles by the size of the level: 32 x 8 lanes below 100 MB, 64 x 8
+    // above (more work groups against fewer halo nodes).  Both levels with
+    // 32 x 8 / 64 x 8 (/ 32 x 16, the default before) lanes, us a step, FP32: 512^2
+    // 41 / 52 (/ 43), 1024^2 79 / 83 (/ 81), 2048^2 - / 198 (/ 216); FP64: 128^2
+    // 32 / 39 (/ 41), 768^2 80 / 80 (/ 83), 1024^2 120 / 115 (/ 121), 2048^2 - /
+    // 360 (/ 417).
+    if (D == 2 && desc.collision == LBM_HRR)
+      for (int l = 0; l < 2; ++l) var[2 + l] = level_bytes(l) < 1e8 ? 1 : 0;
     if (D == 3 && desc.collision == LBM_HRR) {
       var[2] = level_bytes(0) < 2e9 ? 0 : 2;
       var[3] = level_bytes(1) < 1e8 ? 0 : 2;
@@ -1705,6 +1713,8 @@ struct Batch final : BatchBase {
     hinst.assign((size_t)cap, InstDev{});
     steps_done.assign((size_t)cap, 0);
     ring_partial.assign((size_t)cap, 0);
+    // (D2Q9 H-RR: narrow coarse tiles, 12 planes of 128-700 FP32: 7.35 -> 7.13 ms)
+    if (hrr2()) ctile_var = 1;
     d_inst.alloc(sizeof(InstDev) * (size_t)cap * kPhases);
     HIPCHK(hipMemset(d_inst.p, 0, d_inst.bytes));
     d_counts.alloc(sizeof(int) * W_KINDS);
