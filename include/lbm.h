@@ -264,18 +264,18 @@ int lbm_kernel_time(lbm_handle h, int64_t* launches, double* mean_ms, int64_t* n
  * which caps the work groups resident on a CU (no cap, 3, 2, 1).  For the
  * fine role of a D2Q9 BGK / RR grid, whose kernel runs both substeps with
  * the half-step state on chip, the variants are work-group tiles of one
- * lane per vector, halo included (vectors x rows): 64 x 8, 64 x 16, 32 x 16
- * and 32 x 8.  For the fine role of a D3Q19 BGK / RR grid, variants 0 and 1
+ * lane per vector, halo included (vectors x rows): 64 x 8 (16 x 8 on grids that
+ * leave most of the chip idle), 64 x 16, 32 x 16 and 32 x 8.  For the fine role of a D3Q19 BGK / RR grid, variants 0 and 1
  * run the two substeps as two launches (capped at 2 and 3 resident work
  * groups per CU), 2 and 3 as one kernel walking tiles of columns along z
- * (lanes, halo included: 130 x 7 and 66 x 15 in FP32, 34 x 15 and 66 x 7 in
- * FP64).  For the H-RR roles of a D2Q9 grid, whose kernels run a coarse
+ * (lanes, halo included: 130 x 7 -- 194 x 5 in rows of 129 to 192 nodes, which
+ * fill it better -- and 66 x 15 in FP32, 34 x 15 and 66 x 7 in FP64).  For the H-RR roles of a D2Q9 grid, whose kernels run a coarse
  * step or a fine substep in one pass (velocities of the tile in LDS), the
  * variants are tiles of 64 x 8, 32 x 8, 32 x 16 and 128 x 4 lanes; for the
  * H-RR roles of a D3Q19 grid, variants 0 and 1 run the velocity pass and the
  * collision (capped at 2 and 3 resident work groups per CU), 2 and 3 one
- * pass walking tiles of columns along z (130 x 7 and 66 x 15 lanes in FP32,
- * 66 x 7 and 34 x 15 in FP64).  Every variant computes
+ * pass walking tiles of columns along z (130 x 7 or 194 x 5 and 66 x 15 lanes
+ * in FP32, 66 x 7 and 34 x 15 in FP64).  Every variant computes
  * bitwise the same result. */
 enum { LBM_N_VARIANTS = 4 };
 /* Autotuner: times every bulk-kernel variant of each bulk role of this grid

@@ -336,7 +336,8 @@ struct Grid final : GridBase {
     // 7320.  lbm_tune times them all.
     if (fused) {
       const double lim = kTail ? kTailBytes : 1e8;
-      var[1] = D == 2 || level_bytes(1) < lim ? 0 : (DEV && g.nf[0] <= 256 ? 3 : 2);
+      // (one pass, FP32: wide tiles from 257 nodes a row or where they fit well)
+      var[1] = D == 2 || level_bytes(1) < lim ? 0 : (DEV && g.nf[0] <= 256 && !wide194(g.nf[0] - 2) ? 3 : 2);
     }
     // D2Q9 H-RR tiles by the size of the level: 32 x 8 lanes below 100 MB, 64 x 8
     // above (more work groups against fewer halo nodes).  Both levels with
@@ -691,6 +692,12 @@ struct Grid final : GridBase {
   // (k_fine3s): tiles of (TXH - 2) x (TYH - 2) middle nodes.  The tile
   // counts come from nodes, not vectors.  Longest run: its storage window
   // (zlen + 4 planes and one storage block) stays below 2^31 bytes.
+  // FP32 wide tiles (variant 2): 130 x 7 lanes, or 194 x 5 where they leave
+  // fewer idle columns in rows of n nodes (129 to 192).  Fine kernel with
+  // 130 x 7 / 194 x 5 / 66 x 15 lanes, us: RR 139^3 212 / 169 / 192, 159^3 277 /
+  // 229 / 246, 179^3 361 / 290 / 308, 199^3 (256 or 384 columns) 471 / 617 / 447;
+  // H-RR 139^3 169 / 123 / 153, 179^3 317 / 226 / 272, 199^3 407 / 532 / 381.
+  static bool wide194(int n) { return (n + 191) / 192 * 192 < (n + 127) / 128 * 128; }
   int window_zcap() const {
     const double plane = (double)g.pf * g.nf[1] * Q * sizeof(S);
     const double room = 2147483648.0 - 2.0 * (double)PopBlock<S>::B * Q * sizeof(S);
@@ -752,8 +759,9 @@ struct Grid final : GridBase {
   void launch_hrr3(const S* src, S* dst, const S* mac, hipStream_t s, int v = -1, S* out = nullptr) {
     if (v < 0) v = var[2 + LEVEL];
     if constexpr (sizeof(S) == 4) {
-      if (v == 2) go_hrr3s<LEVEL, 130, 7>(src, dst, mac, s, v, out);
-      else go_hrr3s<LEVEL, 66, 15>(src, dst, mac, s, v, out);
+      if (v != 2) go_hrr3s<LEVEL, 66, 15>(src, dst, mac, s, v, out);
+      else if (wide194(LEVEL == 0 ? g.n[0] : g.nf[0] - 2)) go_hrr3s<LEVEL, 194, 5>(src, dst, mac, s, v, out);
+      else go_hrr3s<LEVEL, 130, 7>(src, dst, mac, s, v, out);
     } else {
       if (v == 2) go_hrr3s<LEVEL, 66, 7>(src, dst, mac, s, v, out);
       else go_hrr3s<LEVEL, 34, 15>(src, dst, mac, s, v, out);
@@ -788,8 +796,9 @@ struct Grid final : GridBase {
         default: go_fine2<MODEL, 32, 8>(src, dst, half, cdst, s, su, suc); break;
       }
     } else if constexpr (sizeof(S) == 4) {
-      if (v == 2) go_fine3s<MODEL, 130, 7>(src, dst, half, s, 2);
-      else go_fine3s<MODEL, 66, 15>(src, dst, half, s, 3);
+      if (v != 2) go_fine3s<MODEL, 66, 15>(src, dst, half, s, 3);
+      else if (wide194(g.nf[0] - 2)) go_fine3s<MODEL, 194, 5>(src, dst, half, s, 2);
+      else go_fine3s<MODEL, 130, 7>(src, dst, half, s, 2);
     } else {
       if (v == 2) go_fine3s<MODEL, 34, 15>(src, dst, half, s, 2);
       else go_fine3s<MODEL, 66, 7>(src, dst, half, s, 3);

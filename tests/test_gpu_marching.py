@@ -65,3 +65,15 @@ def test_coarse_one_pass_tile_edges(nx, prec):
         ref = _run(wl, "HRR", p, [0, 0, 0, 0], steps=4)
         for v in (2, 3):
             _same(_run(wl, "HRR", p, [0, 0, v, 0], steps=4), ref, (lo, v))
+
+
+@pytest.mark.parametrize("m", [64, 65, 96, 97])
+def test_wide_tile_choice(m):
+    """FP32 variant 2 takes tiles of 192 nodes along x in rows of 129 to 192
+    nodes, of 128 on either side, fine and coarse."""
+    from paper_2004_11863_amd import lbm
+    wl = _workload((2 * m + 1, 17, 18), (20, 4, 3), (20 + m, 12, 12))
+    ref = _run(wl, "RR", lbm.LBM_FP32_DEV, [0, 0, 0, 0])
+    _same(_run(wl, "RR", lbm.LBM_FP32_DEV, [0, 2, 0, 0]), ref, "RR")
+    ref = _run(wl, "HRR", lbm.LBM_FP32_DEV, [0, 0, 0, 0])
+    _same(_run(wl, "HRR", lbm.LBM_FP32_DEV, [0, 0, 2, 2]), ref, "HRR")
