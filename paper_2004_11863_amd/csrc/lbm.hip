@@ -15,6 +15,7 @@
 #include "batch.hpp"
 #include "kernels.hpp"
 #include "lbm.h"
+#include "rules.hpp"
 
 namespace lbm {
 
@@ -337,7 +338,7 @@ struct Grid final : GridBase {
     if (fused) {
       const double lim = kTail ? kTailBytes : 1e8;
       // (one pass, FP32: wide tiles from 257 nodes a row or where they fit well)
-      var[1] = D == 2 || level_bytes(1) < lim ? 0 : (DEV && g.nf[0] <= 256 && !wide194(g.nf[0] - 2) ? 3 : 2);
+      var[1] = D == 2 || level_bytes(1) < lim || fine3_zcap<S>(g) < 1 ? 0 : (DEV && g.nf[0] <= 256 && !wide194(g.nf[0] - 2) ? 3 : 2);
     }
     // D2Q9 H-RR tiles by the size of the level: 32 x 8 lanes below 100 MB, 64 x 8
     // above (more work groups against fewer halo nodes).  Both levels with
@@ -690,29 +691,20 @@ struct Grid final : GridBase {
   }
   // Both fine substeps in one marching kernel with one node per lane
   // (k_fine3s): tiles of (TXH - 2) x (TYH - 2) middle nodes.  The tile
-  // counts come from nodes, not vectors.  Longest run: its storage window
-  // (zlen + 4 planes and one storage block) stays below 2^31 bytes.
+  // counts come from nodes, not vectors; runs hold at most fine3_zcap planes.
   // FP32 wide tiles (variant 2): 130 x 7 lanes, or 194 x 5 where they leave
   // fewer idle columns in rows of n nodes (129 to 192).  Fine kernel with
   // 130 x 7 / 194 x 5 / 66 x 15 lanes, us: RR 139^3 212 / 169 / 192, 159^3 277 /
   // 229 / 246, 179^3 361 / 290 / 308, 199^3 (256 or 384 columns) 471 / 617 / 447;
   // H-RR 139^3 169 / 123 / 153, 179^3 317 / 226 / 272, 199^3 407 / 532 / 381.
   static bool wide194(int n) { return (n + 191) / 192 * 192 < (n + 127) / 128 * 128; }
-  int window_zcap() const {
-    const double plane = (double)g.pf * g.nf[1] * Q * sizeof(S);
-    const double room = 2147483648.0 - 2.0 * (double)PopBlock<S>::B * Q * sizeof(S);
-    return std::max(0, (int)std::floor(room / plane) - 4);
-  }
   template <int MODEL, int TXH, int TYH>
   void go_fine3s(const S* src, S* dst, S* half, hipStream_t s, int v) {
     if constexpr (D == 3 && MODEL != M_HRR) {
       auto kern = k_fine3s<LAT, DEV, S, MODEL, TXH, TYH>;
       const int ntx = (g.nf[0] - 2 + TXH - 3) / (TXH - 2), nty = (g.nf[1] - 2 + TYH - 3) / (TYH - 2);
-      const int zcap = window_zcap();
-      if (zcap < 1) throw LbmError(LBM_EUNSUPPORTED, "fine planes too large for the one-pass fused kernel");
-      // the compact x-band copy is addressed with 32-bit byte offsets too
-      if ((double)xband_elems(g, Q) * sizeof(S) >= 2147483648.0)
-        throw LbmError(LBM_EUNSUPPORTED, "fine x-bands too large for the one-pass fused kernel");
+      const int zcap = fine3_zcap<S>(g);
+      if (zcap < 1) throw LbmError(LBM_EUNSUPPORTED, "fine planes or x-bands too large for the one-pass fused kernel");
       const ZRuns r = zruns_tiles(ntx, nty, g.nf[2] - 2, occupancy_slots(kern, f3_slots[v], TXH * TYH), zcap);
       hipLaunchKernelGGL(kern, dim3((unsigned)(r.per * kXCD)), dim3(TXH * TYH), 0, s, src, dst, half, xbuf.as<S>(),
                          g, (S)(1.0 - 1.0 / tau_f), r.ntx, r.nty, r.nzc, r.zlen, r.per);
@@ -822,7 +814,9 @@ struct Grid final : GridBase {
   }
   // True when this step runs both fine substeps in one kernel.
   // (D2Q9 stays fused when it records the NH sensors: k_fine2 SENS does)
-  bool fused_now() const { return fused && (D == 2 || (!rec_fine && var[1] >= 2)); }
+  // (D3Q19: variants 2 and 3 where k_fine3s can address the level, else its
+  // substeps are two launches)
+  bool fused_now() const { return fused && (D == 2 || (!rec_fine && var[1] >= 2 && fine3_zcap<S>(g) > 0)); }
   // LDS variant of the fine k_stream launches for fine-role variant v.
   int fine_lds_var(int v) const { return (fused && D == 3) ? (v == 0 ? 2 : 1) : v; }
   // Fine-level pull-stream + collide (BGK, RR): the timed kernel.

@@ -1,0 +1,84 @@
+"""The host rules that choose a kernel form or tile by sizes
+(paper_2004_11863_amd/csrc/rules.hpp), compiled for the CPU and asked on both
+sides of their lines."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2004_11863_amd", "csrc")
+
+DRIVER = r"""
+#include "rules.hpp"
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+using namespace lbm;
+static Geo geo(int mx, int my, int mz, int bytes) {
+  Geo g{};
+  g.D = 3;
+  g.has_fine = 1;
+  const int m[3] = {mx, my, mz};
+  for (int k = 0; k < 3; ++k) {
+    g.m[k] = m[k];
+    g.nf[k] = 2 * m[k] + 1;
+  }
+  const int xo = 16 / bytes - 1;
+  g.fxo = xo;
+  g.pf = (g.nf[0] + xo + 3) / 4 * 4;
+  g.Nf = (int64_t)g.nf[0] * g.nf[1] * g.nf[2];
+  g.Nfp = (int64_t)g.pf * g.nf[1] * g.nf[2];
+  return g;
+}
+int main(int argc, char** argv) {
+  const char* what = argv[1];
+  auto arg = [&](int k) { return atoi(argv[2 + k]); };
+  if (!strcmp(what, "zcap")) {
+    const Geo g = geo(arg(1), arg(2), arg(3), arg(0));
+    printf("%d\n", arg(0) == 4 ? fine3_zcap<float>(g) : fine3_zcap<double>(g));
+  }
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = d / "rules.cpp", d / "rules"
+    src.write_text(DRIVER)
+    subprocess.check_call(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-I", "/opt/rocm/include",
+                           "-Wno-attributes", "-o", str(exe), str(src)])
+
+    def call(*args):
+        return int(subprocess.check_output([str(exe), *map(str, args)]))
+
+    return call
+
+
+def longest_run(cells, nbytes):
+    """Planes of a run whose storage window (four planes more, and a storage block of 32 KB per population at
+    either end) stays below 2^31 bytes; none where the x-band copy (five nodes of every row on two sides) does not."""
+    nf = [2 * m + 1 for m in cells]
+    if 2 * 19 * 5 * nf[1] * nf[2] * nbytes >= 2 ** 31:
+        return 0
+    row = (nf[0] + 16 // nbytes - 1 + 3) // 4 * 4
+    return max(0, (2 ** 31 - 2 * 19 * 32768) // (row * nf[1] * 19 * nbytes) - 4)
+
+
+@pytest.mark.parametrize("cells,nbytes,fits", [
+    ((192, 192, 192), 4, True),
+    ((1186, 1186, 8), 4, True),     # planes of 428.5 MB: five of them and the blocks
+    ((1187, 1187, 8), 4, False),    # 429.6 MB
+    ((1200, 1200, 4), 4, False),
+    ((8, 839, 840), 4, True),       # x-band copies of 2.145e9 and
+    ((8, 840, 840), 4, False),      # 2.148e9 bytes
+    ((4, 593, 593), 8, True),
+    ((4, 594, 594), 8, False),
+    ((600, 1180, 4), 8, False),
+])
+def test_marching_fine_kernel_limits(ask, cells, nbytes, fits):
+    zcap = ask("zcap", nbytes, *cells)
+    assert zcap == longest_run(cells, nbytes)
+    assert (zcap > 0) == fits
