@@ -72,19 +72,24 @@ struct DevBuf {
   }
 };
 
-// Whether a kernel on `device` may use the caller's array p in place: device
-// memory of that device, aligned for doubles.  Anything else that the copies
-// of the runtime take (another device's memory, mapped host memory) goes
-// through a buffer of the library.  In place the fields move once instead of
+// Whether a kernel on `device` may use the caller's n doubles at p in place:
+// device memory of that device, aligned for doubles, all of them inside one
+// allocation.  Anything else goes through a buffer of the library, by the
+// runtime's copies: these take another device's memory and mapped host memory
+// and refuse an array that ends before n values.  In place the fields move once instead of
 // three times: 4096^2 + 4097 x 2049 nodes, set and read back 1110 -> 560 us.
-static bool in_place(const void* p, int device) {
+static bool in_place(const double* p, size_t n, int device) {
   if ((uintptr_t)p % sizeof(double)) return false;
   hipPointerAttribute_t a;
-  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t bytes = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != device ||
+      hipMemGetAddressRange(&base, &bytes, (hipDeviceptr_t)p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return a.type == hipMemoryTypeDevice && a.device == device;
+  const size_t before = (size_t)((const char*)p - (const char*)base);
+  return before <= bytes && n <= (bytes - before) / sizeof(double);
 }
 
 // ---------------------------------------------------------------------------
@@ -1358,7 +1363,7 @@ struct Grid final : GridBase {
 
   // The caller's n values on the device: in place, or copied to buf.
   const double* staged(DevBuf& buf, const double* src, size_t n, bool dev) {
-    if (dev && in_place(src, device)) return src;
+    if (dev && in_place(src, n, device)) return src;
     HIPCHK(hipMemcpyAsync(buf.p, src, sizeof(double) * n, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                           stream));
     return buf.as<double>();
@@ -1418,7 +1423,7 @@ struct Grid final : GridBase {
       child->get_macros(level - 1, rho, u, dev);
       return;
     }
-    const bool pr = dev && in_place(rho, device), pu = dev && in_place(u, device);
+    const bool pr = dev && in_place(rho, (size_t)N, device), pu = dev && in_place(u, (size_t)N * D, device);
     compute_macros(level, pr ? rho : tmp_rho.as<double>(), pu ? u : tmp_u.as<double>());
     const hipMemcpyKind k = dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     if (!pr) HIPCHK(hipMemcpyAsync(rho, tmp_rho.p, sizeof(double) * N, k, stream));
@@ -1448,7 +1453,7 @@ struct Grid final : GridBase {
     if (level == 0) complete_ring();
     else ring_partial = false;
     const int64_t N = nodes(level);
-    if (!dev || !in_place(f, device)) ensure_tmp_f(N);
+    if (!dev || !in_place(f, (size_t)(Q * N), device)) ensure_tmp_f(N);
     f = staged(tmp_f, f, (size_t)(Q * N), dev);
     S* dst = level == 0 ? cur_c() : fineA();
     hipLaunchKernelGGL((k_pops_in<LAT, DEV, S>), dim3(blocks(Q * N, 256)), dim3(256), 0, stream, f, dst, g, level);
@@ -1469,7 +1474,7 @@ struct Grid final : GridBase {
       child->get_pops(level - 1, f, dev);
       return;
     }
-    const bool pf = dev && in_place(f, device);
+    const bool pf = dev && in_place(f, (size_t)(Q * N), device);
     if (!pf) ensure_tmp_f(N);
     const S* src = level == 0 ? cur_c() : fineA();
     hipLaunchKernelGGL((k_pops_out<LAT, DEV, S>), dim3(blocks(Q * N, 256)), dim3(256), 0, stream, src,
@@ -1959,7 +1964,7 @@ struct Batch final : BatchBase {
     // library's stream does not wait for by itself)
     if (dev) HIPCHK(hipStreamSynchronize(nullptr));
     auto staged = [&](DevBuf& buf, const double* src, size_t n) -> const double* {
-      if (dev && in_place(src, device)) return src;
+      if (dev && in_place(src, n, device)) return src;
       HIPCHK(hipMemcpyAsync(buf.p, src, sizeof(double) * n, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                             stream));
       return buf.template as<double>();
@@ -2000,7 +2005,7 @@ struct Batch final : BatchBase {
     const InstDev& I = hinst[(size_t)sl];
     const int64_t N = level == 0 ? in.g.Nc : in.g.Nf;
     const S* src = (const S*)(level == 0 ? I.cbuf[I.cpar] : I.fbuf[I.fpar]);
-    const bool pr = dev && in_place(rho, device), pu = dev && in_place(u, device);
+    const bool pr = dev && in_place(rho, (size_t)N, device), pu = dev && in_place(u, (size_t)N * D, device);
     hipLaunchKernelGGL((k_macros<LAT, DEV, S>), dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, src,
                        (const S*)I.fbuf[I.fpar], pr ? rho : tmp_rho.template as<double>(),
                        pu ? u : tmp_u.template as<double>(), in.g, level);
