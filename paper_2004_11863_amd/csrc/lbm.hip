@@ -332,18 +332,16 @@ struct Grid final : GridBase {
   void init() override {
     fused = desc.collision != LBM_HRR && g.has_fine && !child;
     HIPCHK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
-    // D3Q19: the one-pass kernels by default in large levels (one work group
-    // a CU needs some planes of tiles to fill the device).  Fine, from 100 MB a
-    // level pair (BGK / RR in double: from kTailBytes), us a step in two launches /
-    // in one: FP32 RR 65^3 55 / 75, 97^3 119 / 111, 129^3 235 / 225; FP64 RR 81^3 115 /
-    // 129, 97^3 182 / 194, 113^3 285 / 287, 129^3 399 / 379; FP32 H-RR 65^3 107 / 124,
+    // D3Q19: the one-pass kernels by default in large levels, us a step in two
+    // passes / in one.  Fine H-RR, from 100 MB a level pair: FP32 65^3 107 / 124,
     // 97^3 211 / 182, 129^3 406 / 390.  Coarse H-RR, from 2 GB: 200^3 FP32 1406 us
     // a step in two passes, 1428 in one; 256^3 2389 and 2320; 384^3 7634 and
     // 7320.  lbm_tune times them all.
     if (fused) {
-      const double lim = kTail ? kTailBytes : 1e8;
+      var[1] = 0;
       // (one pass, FP32: wide tiles from 257 nodes a row or where they fit well)
-      var[1] = D == 2 || level_bytes(1) < lim || fine3_zcap<S>(g) < 1 ? 0 : (DEV && g.nf[0] <= 256 && !wide194(g.nf[0] - 2) ? 3 : 2);
+      if (D == 3 && fine3_by_default<S>(g, level_bytes(1)))
+        var[1] = DEV && g.nf[0] <= 256 && !wide194(g.nf[0] - 2) ? 3 : 2;
     }
     // D2Q9 H-RR tiles by the size of the level: 32 x 8 lanes below 100 MB, 64 x 8
     // above (more work groups against fewer halo nodes).  Both levels with

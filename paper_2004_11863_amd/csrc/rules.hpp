@@ -21,4 +21,35 @@ inline int fine3_zcap(const Geo& g) {
   return std::max(0, (int)std::floor(room / plane) - 4);
 }
 
+// Default of the fine role of a D3Q19 BGK / RR level of `bytes` (two buffers):
+// whether its substeps run as one marching kernel (k_fine3s) or as two
+// launches.  One work group a CU needs some planes of tiles to fill the
+// device: from 100 MB, in double (where small levels also share launches with
+// the interface, Grid::kTail) from 500 MB.  us a step in two launches / in one:
+// FP32 65^3 55 / 75, 97^3 119 / 111, 129^3 235 / 225; FP64 81^3 115 / 129, 97^3
+// 182 / 194, 113^3 285 / 287, 129^3 399 / 379.
+// Thin levels keep the two launches, which waste less on them: short rows
+// leave columns of a tile idle, few rows or planes give short runs and idle
+// CUs, and a level of 250 to 600 MB, which the memory-side cache half holds,
+// loses least by its second pass.  Nodes of the level, us in two / in one:
+// FP32 to 250 MB, sides of 48: 201 x 33 x 201 124 / 137, 399 x 9 x 399 154 / 196,
+// 121 x 61 x 121 92 / 85, 181 x 181 x 49 137 / 131.  To 600 MB, 72: 221 x 221 x 57 223 /
+// 255, 221 x 73 x 221 283 / 293, 67 x 201 x 201 294 / 313, 81 x 201 x 201 334 / 320.
+// Beyond, rows of 48 -- 17 x 301 x 301 277 / 384, 45 x 301 x 301 558 / 590, 53 x 301 x
+// 301 606 / 597 -- and sides of 56 to 1 GB, of 20 above: 401 x 25 x 401 314 / 351,
+// 301 x 301 x 49 355 / 366, 601 x 61 x 121 and 601 x 601 x 33 10 % less in one, 601 x
+// 601 x 21 591 / 591.  FP64, rows of 36 and sides of 20: 33 x 301 x 301 606 / 618, 49 x
+// 301 x 301 984 / 887; 301 x 301 x 19 270 / 282, x 23 314 / 303.
+// So do planes so large that a run is cut below 8 (fine3_zcap; FP32, 33 planes:
+// runs of 12 3908 / 3642, of 8 5225 / 5121; 17 planes: of 5 3933 / 4158, of 3 5043 /
+// 5792, of 1 6099 / 9684).
+template <typename S>
+inline bool fine3_by_default(const Geo& g, double bytes) {
+  const bool single = sizeof(S) == 4;
+  if (bytes < (single ? 1e8 : 5e8) || fine3_zcap<S>(g) < 8) return false;
+  const int row = single ? (bytes >= 2.5e8 && bytes < 6e8 ? 72 : 48) : 36;
+  const int side = !single || bytes >= 1e9 ? 20 : (bytes >= 6e8 ? 56 : (bytes >= 2.5e8 ? 72 : 48));
+  return g.nf[0] - 2 >= row && std::min(g.nf[1], g.nf[2]) - 2 >= side;
+}
+
 }  // namespace lbm

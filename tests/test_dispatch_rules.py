@@ -38,6 +38,11 @@ int main(int argc, char** argv) {
     const Geo g = geo(arg(1), arg(2), arg(3), arg(0));
     printf("%d\n", arg(0) == 4 ? fine3_zcap<float>(g) : fine3_zcap<double>(g));
   }
+  if (!strcmp(what, "fine3")) {
+    const Geo g = geo(arg(1), arg(2), arg(3), arg(0));
+    const double bytes = 2.0 * 19 * arg(0) * (double)g.Nfp;
+    printf("%d\n", arg(0) == 4 ? fine3_by_default<float>(g, bytes) : fine3_by_default<double>(g, bytes));
+  }
   return 0;
 }
 """
@@ -82,3 +87,23 @@ def test_marching_fine_kernel_limits(ask, cells, nbytes, fits):
     zcap = ask("zcap", nbytes, *cells)
     assert zcap == longest_run(cells, nbytes)
     assert (zcap > 0) == fits
+
+
+@pytest.mark.parametrize("cells,nbytes,march", [
+    ((42, 42, 42), 4, False), ((48, 48, 48), 4, True), ((64, 64, 64), 4, True), ((192, 192, 192), 4, True),
+    # thin in y or z
+    ((100, 16, 100), 4, False), ((60, 30, 60), 4, True), ((60, 60, 30), 4, True),
+    ((110, 110, 28), 4, False), ((110, 36, 110), 4, False), ((110, 40, 110), 4, True),
+    ((150, 150, 24), 4, False), ((200, 12, 200), 4, False), ((300, 30, 60), 4, True),
+    ((300, 300, 8), 4, False), ((300, 300, 16), 4, True),
+    # short rows
+    ((4, 200, 200), 4, False), ((16, 150, 150), 4, False), ((26, 150, 150), 4, True),
+    ((33, 100, 100), 4, False), ((40, 100, 100), 4, True),
+    # short runs
+    ((880, 880, 16), 4, False), ((765, 765, 16), 4, True),
+    # double
+    ((56, 56, 56), 8, False), ((64, 64, 64), 8, True), ((4, 200, 200), 8, False), ((24, 150, 150), 8, True),
+    ((300, 300, 8), 8, False), ((150, 150, 12), 8, True),
+])
+def test_marching_fine_kernel_by_default(ask, cells, nbytes, march):
+    assert ask("fine3", nbytes, *cells) == int(march)
