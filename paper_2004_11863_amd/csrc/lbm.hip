@@ -332,11 +332,9 @@ struct Grid final : GridBase {
   void init() override {
     fused = desc.collision != LBM_HRR && g.has_fine && !child;
     HIPCHK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
-    // D3Q19: the one-pass kernels by default in large levels, us a step in two
-    // passes / in one.  Fine H-RR, from 100 MB a level pair: FP32 65^3 107 / 124,
-    // 97^3 211 / 182, 129^3 406 / 390.  Coarse H-RR, from 2 GB: 200^3 FP32 1406 us
-    // a step in two passes, 1428 in one; 256^3 2389 and 2320; 384^3 7634 and
-    // 7320.  lbm_tune times them all.
+    // D3Q19: the one-pass kernels by default in large levels (rules.hpp).  Coarse
+    // H-RR, from 2 GB: 200^3 FP32 1406 us a step in two passes, 1428 in one;
+    // 256^3 2389 and 2320; 384^3 7634 and 7320.  lbm_tune times them all.
     if (fused) {
       var[1] = 0;
       // (one pass, FP32: wide tiles from 257 nodes a row or where they fit well)
@@ -353,7 +351,7 @@ struct Grid final : GridBase {
       for (int l = 0; l < 2; ++l) var[2 + l] = level_bytes(l) < 1e8 ? 1 : 0;
     if (D == 3 && desc.collision == LBM_HRR) {
       var[2] = level_bytes(0) < 2e9 ? 0 : 2;
-      var[3] = level_bytes(1) < 1e8 ? 0 : 2;
+      var[3] = hrr3_fine_by_default<S>(g, level_bytes(1)) ? 2 : 0;
     }
     timed_factor = fused_now() ? 2 : 1;
     // every state buffer starts at zero: the state is zero until

@@ -52,4 +52,18 @@ inline bool fine3_by_default(const Geo& g, double bytes) {
   return g.nf[0] - 2 >= row && std::min(g.nf[1], g.nf[2]) - 2 >= side;
 }
 
+// Default of the fine role of a D3Q19 H-RR level of `bytes` (two buffers):
+// whether a substep runs in one marching pass (k_hrr3s) or as the velocity
+// pass and the collision.  From 100 MB: us a step in two passes / in one,
+// FP32 65^3 107 / 124, 97^3 211 / 182, 129^3 406 / 390.  Rows that use less than
+// some third of a tile's columns (128, in double 64) keep the two passes: FP32
+// 9 x 401 x 401 nodes 497 / 890, 17 x 301 x 301 406 / 588, 33 x 301 x 301 708 / 764,
+// 37 x 301 x 301 757 / 776, 41 x 301 x 301 794 / 793, 45 x 301 x 301 850 / 819; FP64 9 x
+// 401 x 401 984 / 1259, 17 x 301 x 301 816 / 873, 21 x 301 x 301 904 / 885 (x 181 x 181 286 / 306), 25 x 301 x
+// 301 1004 / 944, 33 x 301 x 301 1159 / 1034.
+template <typename S>
+inline bool hrr3_fine_by_default(const Geo& g, double bytes) {
+  return bytes >= 1e8 && g.nf[0] - 2 >= (sizeof(S) == 4 ? 40 : 22);
+}
+
 }  // namespace lbm

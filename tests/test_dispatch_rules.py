@@ -43,6 +43,11 @@ int main(int argc, char** argv) {
     const double bytes = 2.0 * 19 * arg(0) * (double)g.Nfp;
     printf("%d\n", arg(0) == 4 ? fine3_by_default<float>(g, bytes) : fine3_by_default<double>(g, bytes));
   }
+  if (!strcmp(what, "hrr3")) {
+    const Geo g = geo(arg(1), arg(2), arg(3), arg(0));
+    const double bytes = 2.0 * 19 * arg(0) * (double)g.Nfp;
+    printf("%d\n", arg(0) == 4 ? hrr3_fine_by_default<float>(g, bytes) : hrr3_fine_by_default<double>(g, bytes));
+  }
   return 0;
 }
 """
@@ -107,3 +112,13 @@ def test_marching_fine_kernel_limits(ask, cells, nbytes, fits):
 ])
 def test_marching_fine_kernel_by_default(ask, cells, nbytes, march):
     assert ask("fine3", nbytes, *cells) == int(march)
+
+
+@pytest.mark.parametrize("cells,nbytes,one_pass", [
+    ((40, 40, 40), 4, False), ((44, 44, 44), 4, True), ((128, 128, 128), 4, True),
+    ((4, 200, 200), 4, False), ((18, 150, 150), 4, False), ((22, 150, 150), 4, True),
+    ((150, 150, 8), 4, True), ((200, 4, 200), 4, True),
+    ((4, 200, 200), 8, False), ((10, 150, 150), 8, False), ((12, 150, 150), 8, True), ((64, 64, 64), 8, True),
+])
+def test_one_pass_hrr_fine_by_default(ask, cells, nbytes, one_pass):
+    assert ask("hrr3", nbytes, *cells) == int(one_pass)
