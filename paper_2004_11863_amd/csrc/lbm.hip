@@ -332,9 +332,8 @@ struct Grid final : GridBase {
   void init() override {
     fused = desc.collision != LBM_HRR && g.has_fine && !child;
     HIPCHK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device));
-    // D3Q19: the one-pass kernels by default in large levels (rules.hpp).  Coarse
-    // H-RR, from 2 GB: 200^3 FP32 1406 us a step in two passes, 1428 in one;
-    // 256^3 2389 and 2320; 384^3 7634 and 7320.  lbm_tune times them all.
+    // D3Q19: the one-pass kernels by default in large levels (rules.hpp; lbm_tune
+    // times them all)
     if (fused) {
       var[1] = 0;
       // (one pass, FP32: wide tiles from 257 nodes a row or where they fit well)
@@ -350,7 +349,7 @@ struct Grid final : GridBase {
     if (D == 2 && desc.collision == LBM_HRR)
       for (int l = 0; l < 2; ++l) var[2 + l] = level_bytes(l) < 1e8 ? 1 : 0;
     if (D == 3 && desc.collision == LBM_HRR) {
-      var[2] = level_bytes(0) < 2e9 ? 0 : 2;
+      var[2] = hrr3_coarse_by_default<S>(g.n, level_bytes(0)) ? 2 : 0;
       var[3] = hrr3_fine_by_default<S>(g, level_bytes(1)) ? 2 : 0;
     }
     timed_factor = fused_now() ? 2 : 1;
@@ -693,12 +692,6 @@ struct Grid final : GridBase {
   // Both fine substeps in one marching kernel with one node per lane
   // (k_fine3s): tiles of (TXH - 2) x (TYH - 2) middle nodes.  The tile
   // counts come from nodes, not vectors; runs hold at most fine3_zcap planes.
-  // FP32 wide tiles (variant 2): 130 x 7 lanes, or 194 x 5 where they leave
-  // fewer idle columns in rows of n nodes (129 to 192).  Fine kernel with
-  // 130 x 7 / 194 x 5 / 66 x 15 lanes, us: RR 139^3 212 / 169 / 192, 159^3 277 /
-  // 229 / 246, 179^3 361 / 290 / 308, 199^3 (256 or 384 columns) 471 / 617 / 447;
-  // H-RR 139^3 169 / 123 / 153, 179^3 317 / 226 / 272, 199^3 407 / 532 / 381.
-  static bool wide194(int n) { return (n + 191) / 192 * 192 < (n + 127) / 128 * 128; }
   template <int MODEL, int TXH, int TYH>
   void go_fine3s(const S* src, S* dst, S* half, hipStream_t s, int v) {
     if constexpr (D == 3 && MODEL != M_HRR) {

@@ -8,6 +8,13 @@
 
 namespace lbm {
 
+// FP32 wide tiles of the marching D3Q19 kernels (variant 2): 130 x 7 lanes, or
+// 194 x 5 where they leave fewer idle columns in rows of n nodes (129 to 192).
+// Fine kernel with 130 x 7 / 194 x 5 / 66 x 15 lanes, us: RR 139^3 212 / 169 / 192,
+// 159^3 277 / 229 / 246, 179^3 361 / 290 / 308, 199^3 (256 or 384 columns) 471 /
+// 617 / 447; H-RR 139^3 169 / 123 / 153, 179^3 317 / 226 / 272, 199^3 407 / 532 / 381.
+inline bool wide194(int n) { return (n + 191) / 192 * 192 < (n + 127) / 128 * 128; }
+
 // k_fine3s (both D3Q19 BGK / RR fine substeps in one marching pass) addresses
 // the storage window of its run (zlen + 4 planes and one storage block) and
 // the compact x-band copy with 32-bit byte offsets, both below 2^31.  Longest
@@ -57,13 +64,29 @@ inline bool fine3_by_default(const Geo& g, double bytes) {
 // pass and the collision.  From 100 MB: us a step in two passes / in one,
 // FP32 65^3 107 / 124, 97^3 211 / 182, 129^3 406 / 390.  Rows that use less than
 // some third of a tile's columns (128, in double 64) keep the two passes: FP32
-// 9 x 401 x 401 nodes 497 / 890, 17 x 301 x 301 406 / 588, 33 x 301 x 301 708 / 764,
-// 37 x 301 x 301 757 / 776, 41 x 301 x 301 794 / 793, 45 x 301 x 301 850 / 819; FP64 9 x
-// 401 x 401 984 / 1259, 17 x 301 x 301 816 / 873, 21 x 301 x 301 904 / 885 (x 181 x 181 286 / 306), 25 x 301 x
-// 301 1004 / 944, 33 x 301 x 301 1159 / 1034.
+// 9 x 401 x 401 nodes 497 / 890, 17 x 301 x 301 406 / 588, 33 x 301 x 301 708 /
+// 764, 37 x 301 x 301 757 / 776, 41 x 301 x 301 794 / 793, 45 x 301 x 301 850 / 819;
+// FP64 9 x 401 x 401 984 / 1259, 17 x 301 x 301 816 / 873, 21 x 301 x 301 904 /
+// 885, 21 x 181 x 181 286 / 306, 25 x 301 x 301 1004 / 944, 33 x 301 x 301 1159 /
+// 1034.
 template <typename S>
 inline bool hrr3_fine_by_default(const Geo& g, double bytes) {
   return bytes >= 1e8 && g.nf[0] - 2 >= (sizeof(S) == 4 ? 40 : 22);
+}
+
+// The same for a D3Q19 H-RR coarse level (n[3] nodes): from 2 GB.  us a step in
+// two passes / in one: FP32 256^3 844 / 736, 384 x 256 x 256 1210 / 1032, 1000 x 128 x
+// 128 819 / 739; FP64 200^3 799 / 695, 96 x 280 x 280 762 / 669, 66 x 320 x 320 771 / 760.
+// In FP32 rows that use less than four fifths of their tiles' columns (128, or
+// 192 in rows of 129 to 192) keep the two passes: 130 x 350 x 350 828 / 831, 194 x
+// 280 x 280 790 / 857, 200 x 300 x 300 911 / 976, 260 x 256 x 256 863 / 929, 300 x 256 x
+// 256 976 / 993; above, 160 x 320 x 320 829 / 715, 220 x 260 x 260 779 / 776, 320 x
+// 256 x 256 1026 / 932.
+template <typename S>
+inline bool hrr3_coarse_by_default(const int* n, double bytes) {
+  if (bytes < 2e9) return false;
+  const int tile = wide194(n[0]) ? 192 : 128, columns = (n[0] + tile - 1) / tile * tile;
+  return sizeof(S) == 8 || 5 * n[0] >= 4 * columns;
 }
 
 }  // namespace lbm

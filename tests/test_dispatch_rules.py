@@ -48,6 +48,11 @@ int main(int argc, char** argv) {
     const double bytes = 2.0 * 19 * arg(0) * (double)g.Nfp;
     printf("%d\n", arg(0) == 4 ? hrr3_fine_by_default<float>(g, bytes) : hrr3_fine_by_default<double>(g, bytes));
   }
+  if (!strcmp(what, "hrr3c")) {
+    const int n[3] = {arg(1), arg(2), arg(3)};
+    const double bytes = 2.0 * 19 * arg(0) * n[0] * n[1] * n[2];
+    printf("%d\n", arg(0) == 4 ? hrr3_coarse_by_default<float>(n, bytes) : hrr3_coarse_by_default<double>(n, bytes));
+  }
   return 0;
 }
 """
@@ -122,3 +127,14 @@ def test_marching_fine_kernel_by_default(ask, cells, nbytes, march):
 ])
 def test_one_pass_hrr_fine_by_default(ask, cells, nbytes, one_pass):
     assert ask("hrr3", nbytes, *cells) == int(one_pass)
+
+
+@pytest.mark.parametrize("n,nbytes,one_pass", [
+    ((200, 200, 200), 4, False), ((256, 256, 256), 4, True), ((384, 384, 384), 4, True),
+    ((130, 350, 350), 4, False), ((153, 350, 350), 4, False), ((154, 350, 350), 4, True), ((192, 300, 300), 4, True),
+    ((194, 280, 280), 4, False), ((204, 300, 300), 4, False), ((205, 300, 300), 4, True),
+    ((257, 300, 300), 4, False), ((307, 300, 300), 4, False), ((308, 300, 300), 4, True),
+    ((180, 180, 180), 8, False), ((200, 200, 200), 8, True), ((66, 320, 320), 8, True),
+])
+def test_one_pass_hrr_coarse_by_default(ask, n, nbytes, one_pass):
+    assert ask("hrr3c", nbytes, *n) == int(one_pass)
