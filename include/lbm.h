@@ -268,8 +268,9 @@ int lbm_kernel_time(lbm_handle h, int64_t* launches, double* mean_ms, int64_t* n
  * leave most of the chip idle), 64 x 16, 32 x 16 and 32 x 8.  For the fine role of a D3Q19 BGK / RR grid, variants 0 and 1
  * run the two substeps as two launches (capped at 2 and 3 resident work
  * groups per CU), 2 and 3 as one kernel walking tiles of columns along z
- * (lanes, halo included: 130 x 7 -- 194 x 5 in rows of 129 to 192 nodes, which
- * fill it better -- and 66 x 15 in FP32, 34 x 15 and 66 x 7 in FP64), or as
+ * (lanes, halo included: 130 x 7 -- 194 x 5 in rows whose nodes fill tiles of
+ * 192 better than of 128: 129 to 192, 513 to 576 and so on -- and 66 x 15 in
+ * FP32, 34 x 15 and 66 x 7 in FP64), or as
  * two launches in a level whose planes or x-bands are past that kernel's
  * 32-bit addressing.  For the H-RR roles of a D2Q9 grid, whose kernels run a coarse
  * step or a fine substep in one pass (velocities of the tile in LDS), the

@@ -9,10 +9,13 @@
 namespace lbm {
 
 // FP32 wide tiles of the marching D3Q19 kernels (variant 2): 130 x 7 lanes, or
-// 194 x 5 where they leave fewer idle columns in rows of n nodes (129 to 192).
-// Fine kernel with 130 x 7 / 194 x 5 / 66 x 15 lanes, us: RR 139^3 212 / 169 / 192,
-// 159^3 277 / 229 / 246, 179^3 361 / 290 / 308, 199^3 (256 or 384 columns) 471 /
-// 617 / 447; H-RR 139^3 169 / 123 / 153, 179^3 317 / 226 / 272, 199^3 407 / 532 / 381.
+// 194 x 5 where 192 columns a tile leave fewer idle than 128 in rows of n nodes
+// (129 to 192, 513 to 576, 897 to 960 and so on).  Fine kernel with 130 x 7 / 194 x 5 /
+// 66 x 15 lanes, us: RR 139^3 212 / 169 / 192, 159^3 277 / 229 / 246, 179^3 361 / 290 /
+// 308, 199^3 (256 or 384 columns) 471 / 617 / 447; H-RR 139^3 169 / 123 / 153, 179^3
+// 317 / 226 / 272, 199^3 407 / 532 / 381.  Step, us: 577 x 201 x 201 RR 1244 / 1198 /
+// 1221, H-RR 2337 / 2225 / 2239; 521 x 161 x 161 RR 820 / 810 / 804, H-RR 1513 / 1471 /
+// 1451; coarse H-RR 550 x 180 x 180 852 / 825 / 779, 576 x 180 x 180 804 / 817 / 721.
 inline bool wide194(int n) { return (n + 191) / 192 * 192 < (n + 127) / 128 * 128; }
 
 // k_fine3s (both D3Q19 BGK / RR fine substeps in one marching pass) addresses
@@ -78,7 +81,7 @@ inline bool hrr3_fine_by_default(const Geo& g, double bytes) {
 // two passes / in one: FP32 256^3 844 / 736, 384 x 256 x 256 1210 / 1032, 1000 x 128 x
 // 128 819 / 739; FP64 200^3 799 / 695, 96 x 280 x 280 762 / 669, 66 x 320 x 320 771 / 760.
 // In FP32 rows that use less than four fifths of their tiles' columns (128, or
-// 192 in rows of 129 to 192) keep the two passes: 130 x 350 x 350 828 / 831, 194 x
+// 192 by wide194) keep the two passes: 130 x 350 x 350 828 / 831, 194 x
 // 280 x 280 790 / 857, 200 x 300 x 300 911 / 976, 260 x 256 x 256 863 / 929, 300 x 256 x
 // 256 976 / 993; above, 160 x 320 x 320 829 / 715, 220 x 260 x 260 779 / 776, 320 x
 // 256 x 256 1026 / 932.

@@ -53,6 +53,7 @@ int main(int argc, char** argv) {
     const double bytes = 2.0 * 19 * arg(0) * n[0] * n[1] * n[2];
     printf("%d\n", arg(0) == 4 ? hrr3_coarse_by_default<float>(n, bytes) : hrr3_coarse_by_default<double>(n, bytes));
   }
+  if (!strcmp(what, "wide194")) printf("%d\n", (int)wide194(arg(0)));
   return 0;
 }
 """
@@ -138,3 +139,10 @@ def test_one_pass_hrr_fine_by_default(ask, cells, nbytes, one_pass):
 ])
 def test_one_pass_hrr_coarse_by_default(ask, n, nbytes, one_pass):
     assert ask("hrr3c", nbytes, *n) == int(one_pass)
+
+
+@pytest.mark.parametrize("row,wide", [(64, 0), (128, 0), (129, 1), (160, 1), (192, 1), (193, 0), (256, 0), (300, 0),
+                                      (383, 0), (384, 0), (512, 0), (513, 1), (576, 1), (577, 0), (896, 0), (897, 1), (960, 1),
+                                      (961, 0)])
+def test_wide_tiles_of_192_columns(ask, row, wide):
+    assert ask("wide194", row) == wide
