@@ -336,9 +336,7 @@ struct Grid final : GridBase {
     // times them all)
     if (fused) {
       var[1] = 0;
-      // (one pass, FP32: wide tiles from 257 nodes a row or where they fit well)
-      if (D == 3 && fine3_by_default<S>(g, level_bytes(1)))
-        var[1] = DEV && g.nf[0] <= 256 && !wide194(g.nf[0] - 2) ? 3 : 2;
+      if (D == 3 && fine3_by_default<S>(g, level_bytes(1))) var[1] = DEV && tall66(g.nf[0] - 2, false) ? 3 : 2;
     }
     // D2Q9 H-RR tiles by the size of the level: 32 x 8 lanes below 100 MB, 64 x 8
     // above (more work groups against fewer halo nodes).  Both levels with
@@ -350,7 +348,7 @@ struct Grid final : GridBase {
       for (int l = 0; l < 2; ++l) var[2 + l] = level_bytes(l) < 1e8 ? 1 : 0;
     if (D == 3 && desc.collision == LBM_HRR) {
       var[2] = hrr3_coarse_by_default<S>(g.n, level_bytes(0)) ? 2 : 0;
-      var[3] = hrr3_fine_by_default<S>(g, level_bytes(1)) ? 2 : 0;
+      var[3] = hrr3_fine_by_default<S>(g, level_bytes(1)) ? (DEV && tall66(g.nf[0] - 2, true) ? 3 : 2) : 0;
     }
     timed_factor = fused_now() ? 2 : 1;
     // every state buffer starts at zero: the state is zero until

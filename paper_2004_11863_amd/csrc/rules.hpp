@@ -18,6 +18,15 @@ namespace lbm {
 // 1451; coarse H-RR 550 x 180 x 180 852 / 825 / 779, 576 x 180 x 180 804 / 817 / 721.
 inline bool wide194(int n) { return (n + 191) / 192 * 192 < (n + 127) / 128 * 128; }
 
+// FP32 fine levels whose middle rows of n nodes take 66 x 15 tiles (variant 3) by
+// default.  Between 193 and 256 nodes 130 x 7 and 66 x 15 tiles leave the same
+// columns idle; the shorter halo wins while these are many, us a step with
+// 130 x 7 / 66 x 15: 193^3 H-RR 1039 / 980, 207^3 RR 625 / 601, H-RR 1203 / 1174;
+// 223^3 RR 771 / 822, H-RR 1419 / 1483, 239^3 RR 884 / 947, H-RR 1623 / 1720.  Up to
+// 128 nodes BGK / RR takes 66 x 15 (127^3 188 / 174; in rows of 95 to 119 nodes the
+// other is up to 6 % ahead).
+inline bool tall66(int n, bool hrr) { return (n > 192 && n < 216) || (n <= 128 && !hrr); }
+
 // k_fine3s (both D3Q19 BGK / RR fine substeps in one marching pass) addresses
 // the storage window of its run (zlen + 4 planes and one storage block) and
 // the compact x-band copy with 32-bit byte offsets, both below 2^31.  Longest

@@ -54,6 +54,7 @@ int main(int argc, char** argv) {
     printf("%d\n", arg(0) == 4 ? hrr3_coarse_by_default<float>(n, bytes) : hrr3_coarse_by_default<double>(n, bytes));
   }
   if (!strcmp(what, "wide194")) printf("%d\n", (int)wide194(arg(0)));
+  if (!strcmp(what, "tall66")) printf("%d\n", (int)tall66(arg(0), arg(1) != 0));
   return 0;
 }
 """
@@ -146,3 +147,9 @@ def test_one_pass_hrr_coarse_by_default(ask, n, nbytes, one_pass):
                                       (961, 0)])
 def test_wide_tiles_of_192_columns(ask, row, wide):
     assert ask("wide194", row) == wide
+
+
+@pytest.mark.parametrize("row,rr,hrr", [(95, 1, 0), (128, 1, 0), (129, 0, 0), (192, 0, 0), (193, 1, 1), (207, 1, 1),
+                                        (215, 1, 1), (216, 0, 0), (239, 0, 0), (255, 0, 0), (257, 0, 0), (383, 0, 0)])
+def test_tall_tiles_by_default(ask, row, rr, hrr):
+    assert (ask("tall66", row, 0), ask("tall66", row, 1)) == (rr, hrr)
