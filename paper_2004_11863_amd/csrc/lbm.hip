@@ -722,7 +722,6 @@ struct Grid final : GridBase {
   bool hrr_one_pass3() const {
     return D == 3 && desc.collision == LBM_HRR && var[3] >= 2 && !dyn_on && hrr3_fits(1);
   }
-  int hrr_lds_var(int v) const { return (D == 3 && desc.collision == LBM_HRR) ? (v == 0 ? 2 : 1) : v; }
   template <int LEVEL, int TXH, int TYH>
   void go_hrr3s(const S* src, S* dst, const S* mac, hipStream_t s, int v, S* out) {
     if constexpr (D == 3) {
@@ -756,7 +755,7 @@ struct Grid final : GridBase {
   void launch_coarse_hrr(const S* src, S* dst, const S* mac, hipStream_t s) {
     if (coarse_one_pass2()) launch_hrr2c(src, dst, mac, s, -1, true);
     else if (coarse_one_pass()) launch_hrr3<0>(src, dst, mac, s, -1, g.has_fine ? const_cast<S*>(mac) : nullptr);
-    else launch_collide_hrr<0>(src, dst, mac, tau_c, s, hrr_lds_var(var[2]), true);
+    else launch_collide_hrr<0>(src, dst, mac, tau_c, s, hrr_cap(D, var[2]), true);
   }
   template <int MODEL>
   void launch_fused(const S* src, S* dst, S* half, S* cdst, hipStream_t s, int v = -1, double* su = nullptr,
@@ -855,7 +854,7 @@ struct Grid final : GridBase {
     } else if (role == 2) {
       // (D3Q19: the two passes the one-pass variants replace)
       if (D == 3) launch_stream<M_HRR, 0>(c_cur, c_oth, mac_c.as<S>(), tau_c, s);
-      launch_collide_hrr<0>(c_cur, c_oth, mac_c.as<S>(), tau_c, s, hrr_lds_var(v));
+      launch_collide_hrr<0>(c_cur, c_oth, mac_c.as<S>(), tau_c, s, hrr_cap(D, v));
     } else if (D == 2) {
       launch_hrr2(fineA(), fineB(), mac_f.as<S>(), s, v);
     } else if (v >= 2) {
@@ -864,7 +863,7 @@ struct Grid final : GridBase {
     } else {
       // the two passes the one-pass variants replace
       launch_stream<M_HRR, 1>(fineA(), fineB(), mac_f.as<S>(), tau_f, s);
-      launch_collide_hrr<1>(fineA(), fineB(), mac_f.as<S>(), tau_f, s, hrr_lds_var(v));
+      launch_collide_hrr<1>(fineA(), fineB(), mac_f.as<S>(), tau_f, s, hrr_cap(D, v));
     }
   }
 
@@ -1034,7 +1033,7 @@ struct Grid final : GridBase {
       } else {
         launch_stream<M_HRR, 1>(fA, fB, mf, tau_f, s);
         hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, s, Hm, H0, Hp, c0, c1, c2, mf, g, itf);
-        timed(s, [&] { launch_collide_hrr<1>(fA, fB, mf, tau_f, s, hrr_lds_var(var[3]), true); });
+        timed(s, [&] { launch_collide_hrr<1>(fA, fB, mf, tau_f, s, hrr_cap(D, var[3]), true); });
       }
       hipLaunchKernelGGL((k_fict<LAT, DEV, S, S>), dim3(bt), dim3(IB), 0, s, fB, mc, g, itf);
       // the coarse velocities at the history nodes' neighbours: from the
@@ -1059,7 +1058,7 @@ struct Grid final : GridBase {
       } else {
         launch_stream<M_HRR, 1>(fB, fA, mf, tau_f, s);
         hipLaunchKernelGGL((k_ring_macro<LAT, S>), dim3(br), dim3(RB), 0, s, Hm, H0, Hp, 0.0, 0.0, 1.0, mf, g, itf);
-        timed(s, [&] { launch_collide_hrr<1>(fB, fA, mf, tau_f, s, hrr_lds_var(var[3]), true); });
+        timed(s, [&] { launch_collide_hrr<1>(fB, fA, mf, tau_f, s, hrr_cap(D, var[3]), true); });
       }
       // coarse collision before the TN transfer: the vector kernel also
       // passes over TN nodes, which the transfer then overwrites; the t+1

@@ -101,4 +101,14 @@ inline bool hrr3_coarse_by_default(const int* n, double bytes) {
   return sizeof(S) == 8 || 5 * n[0] >= 4 * columns;
 }
 
+// LDS variant (residency cap, kVarLds) of the H-RR collision in the two-pass
+// form.  D3Q19: two work groups a CU, or three where variant 1 of an H-RR role
+// asks for them; the other variants name tiles of the one-pass kernels and
+// choose no cap where a level cannot take these (dynamic sigma, the coarse level
+// of a nested grid's inner pair, planes past their addressing).  D2Q9, where only
+// that coarse level has two passes: no cap (nested grid of 2048^2 / 2049^2 /
+// 2049^2 nodes, us a step capped at two / not capped: FP32 595 / 576, FP64 1037 /
+// 1027; 1024^2 FP64 355 / 352).
+inline int hrr_cap(int D, int variant) { return D == 2 ? 0 : (variant == 1 ? 1 : 2); }
+
 }  // namespace lbm

@@ -55,6 +55,7 @@ int main(int argc, char** argv) {
   }
   if (!strcmp(what, "wide194")) printf("%d\n", (int)wide194(arg(0)));
   if (!strcmp(what, "tall66")) printf("%d\n", (int)tall66(arg(0), arg(1) != 0));
+  if (!strcmp(what, "cap")) printf("%d\n", hrr_cap(arg(0), arg(1)));
   return 0;
 }
 """
@@ -153,3 +154,10 @@ def test_wide_tiles_of_192_columns(ask, row, wide):
                                         (215, 1, 1), (216, 0, 0), (239, 0, 0), (255, 0, 0), (257, 0, 0), (383, 0, 0)])
 def test_tall_tiles_by_default(ask, row, rr, hrr):
     assert (ask("tall66", row, 0), ask("tall66", row, 1)) == (rr, hrr)
+
+
+def test_two_pass_hrr_collision_residency(ask):
+    """D2Q9 not capped; D3Q19 two work groups a CU (LDS variant 2), three for variant 1: an index that names a
+    one-pass tile does not choose a cap."""
+    assert [ask("cap", 2, v) for v in range(4)] == [0, 0, 0, 0]
+    assert [ask("cap", 3, v) for v in range(4)] == [2, 1, 2, 2]
