@@ -574,8 +574,9 @@ struct Iface {
   const int64_t* hnode;  // [NH] coarse node (logical index) of each history entry
   int64_t NR;
   const int64_t* rnode;  // [NR] fine node (logical index) of each ring entry
-  const int32_t* rnp;    // [NR] stencil points (1, 4, 16)
-  const int32_t* rpt;    // [NR][16] history entries
+  const int32_t* rnp;    // [NR] stencil points (1, 4)
+  const int32_t* rpt;    // [NR][16] history entries (these three D2Q9 only: D3Q19
+                         // rings work by tiles, ring3_tile)
   int64_t NT;
   const int64_t* tnf;    // [NT] fine TN nodes (logical)
   const int64_t* tnc;    // [NT] coarse TN nodes (logical)
@@ -753,6 +754,7 @@ __device__ __forceinline__ void ring_macro_body(const double* __restrict__ Hm, c
                                        const double* __restrict__ Hp, double c0, double c1, double c2,
                                        T* __restrict__ mac_f, const Geo& g, const Iface& itf, int64_t r) {
   using L = Lattice<LAT>;
+  static_assert(L::D == 2, "D3Q19: ring3_macro_body");
   if (r >= itf.NR) return;
   const int np = itf.rnp[r];
   const int32_t* pt = itf.rpt + 16 * r;

@@ -386,9 +386,11 @@ struct Grid final : GridBase {
         if (bytes) HIPCHK(hipMemcpy(b.p, src, bytes, hipMemcpyHostToDevice));
       };
       up(d_hnode, tabs.hnode.data(), sizeof(int64_t) * tabs.hnode.size());
-      up(d_rnode, tabs.rnode.data(), sizeof(int64_t) * tabs.rnode.size());
-      up(d_rnp, tabs.rnp.data(), sizeof(int32_t) * tabs.rnp.size());
-      up(d_rpt, tabs.rpt.data(), sizeof(int32_t) * tabs.rpt.size());
+      if (D == 2) {  // (D3Q19 rings work by tiles, ring3_tile)
+        up(d_rnode, tabs.rnode.data(), sizeof(int64_t) * tabs.rnode.size());
+        up(d_rnp, tabs.rnp.data(), sizeof(int32_t) * tabs.rnp.size());
+        up(d_rpt, tabs.rpt.data(), sizeof(int32_t) * tabs.rpt.size());
+      }
       up(d_tnf, tabs.tnf.data(), sizeof(int64_t) * tabs.tnf.size());
       up(d_tnc, tabs.tnc.data(), sizeof(int64_t) * tabs.tnc.size());
       itf.NH = (int64_t)tabs.hnode.size();
@@ -1645,7 +1647,7 @@ static int64_t grid_footprint(const lbm_grid_desc& d, const Geo& g) {
     }
     const int64_t nr = ring_out - ring_in, nt = tn_out - tn_in;
     const int64_t hn = 1 + D + Q + (D == 2 ? 3 : 6);
-    bytes += 4 * 8 * hn * nh + nh * 8 + nr * (8 + 4 + 64) + nt * 16;
+    bytes += 4 * 8 * hn * nh + nh * 8 + (D == 2 ? nr * (8 + 4 + 64) : 0) + nt * 16;
   }
   return bytes;
 }
@@ -1844,9 +1846,11 @@ struct Batch final : BatchBase {
       };
       const HostTables& t = in->tabs;
       up(in->d_hnode, t.hnode.data(), sizeof(int64_t) * t.hnode.size());
-      up(in->d_rnode, t.rnode.data(), sizeof(int64_t) * t.rnode.size());
-      up(in->d_rnp, t.rnp.data(), sizeof(int32_t) * t.rnp.size());
-      up(in->d_rpt, t.rpt.data(), sizeof(int32_t) * t.rpt.size());
+      if (D == 2) {  // (D3Q19 rings work by tiles, ring3_tile)
+        up(in->d_rnode, t.rnode.data(), sizeof(int64_t) * t.rnode.size());
+        up(in->d_rnp, t.rnp.data(), sizeof(int32_t) * t.rnp.size());
+        up(in->d_rpt, t.rpt.data(), sizeof(int32_t) * t.rpt.size());
+      }
       up(in->d_tnf, t.tnf.data(), sizeof(int64_t) * t.tnf.size());
       up(in->d_tnc, t.tnc.data(), sizeof(int64_t) * t.tnc.size());
       in->itf = Iface{(int64_t)t.hnode.size(), in->d_hnode.template as<int64_t>(), (int64_t)t.rnode.size(),
