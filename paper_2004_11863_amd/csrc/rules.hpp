@@ -51,14 +51,16 @@ inline int fine3_zcap(const Geo& g) {
 // leave columns of a tile idle, few rows or planes give short runs and idle
 // CUs, and a level of 250 to 600 MB, which the memory-side cache half holds,
 // loses least by its second pass.  Nodes of the level, us in two / in one:
-// FP32 to 250 MB, sides of 48: 201 x 33 x 201 124 / 137, 399 x 9 x 399 154 / 196,
-// 121 x 61 x 121 92 / 85, 181 x 181 x 49 137 / 131.  To 600 MB, 72: 221 x 221 x 57 223 /
-// 255, 221 x 73 x 221 283 / 293, 67 x 201 x 201 294 / 313, 81 x 201 x 201 334 / 320.
-// Beyond, rows of 48 -- 17 x 301 x 301 277 / 384, 45 x 301 x 301 558 / 590, 53 x 301 x
-// 301 606 / 597 -- and sides of 56 to 1 GB, of 20 above: 401 x 25 x 401 314 / 351,
-// 301 x 301 x 49 355 / 366, 601 x 61 x 121 and 601 x 601 x 33 10 % less in one, 601 x
-// 601 x 21 591 / 591.  FP64, rows of 36 and sides of 20: 33 x 301 x 301 606 / 618, 49 x
-// 301 x 301 984 / 887; 301 x 301 x 19 270 / 282, x 23 314 / 303.
+// FP32 to 600 MB, rows of 72 -- 61 x 121 x 121 98 / 118, 67 x 201 x 201 291 / 313, 81 x
+// 201 x 201 334 / 320 -- and to 250 MB sides of 48: 201 x 33 x 201 124 / 137, 399 x 9 x
+// 399 154 / 196, 121 x 61 x 121 92 / 85; to 600 MB of 72: 221 x 221 x 57 223 / 255, 221 x
+// 73 x 221 283 / 293; but of 36 where the row fills 194 x 5 tiles: 181 x 181 x 41 124 /
+// 115, x 57 158 / 150, x 73 196 / 186.  Beyond, rows of 48 -- 17 x 301 x 301 277 / 384,
+// 45 x 301 x 301 558 / 590, 53 x 301 x 301 606 / 597 -- and sides of 56 to 1 GB, of 19
+// above: 401 x 25 x 401 314 / 351, 301 x 301 x 49 355 / 366, 601 x 61 x 121 and 601 x
+// 601 x 33 10 % less in one, 601 x 601 x 21 603 / 590.  FP64, rows of 36 and sides of
+// 20: 33 x 301 x 301 606 / 618, 49 x 301 x 301 984 / 887; 301 x 301 x 19 270 / 282, x 23
+// 314 / 303.
 // So do planes so large that a run is cut below 8 (fine3_zcap; FP32, 33 planes:
 // runs of 12 3908 / 3642, of 8 5225 / 5121; 17 planes: of 5 3933 / 4158, of 3 5043 /
 // 5792, of 1 6099 / 9684).
@@ -66,16 +68,17 @@ template <typename S>
 inline bool fine3_by_default(const Geo& g, double bytes) {
   const bool single = sizeof(S) == 4;
   if (bytes < (single ? 1e8 : 5e8) || fine3_zcap<S>(g) < 8) return false;
-  const int row = single ? (bytes >= 2.5e8 && bytes < 6e8 ? 72 : 48) : 36;
-  const int side = !single || bytes >= 1e9 ? 20 : (bytes >= 6e8 ? 56 : (bytes >= 2.5e8 ? 72 : 48));
-  return g.nf[0] - 2 >= row && std::min(g.nf[1], g.nf[2]) - 2 >= side;
+  const int n = g.nf[0] - 2, row = single ? (bytes < 6e8 ? 72 : 48) : 36;
+  int side = single ? 19 : 20;
+  if (single && bytes < 1e9) side = bytes >= 6e8 ? 56 : (n >= 154 && n <= 192 ? 36 : (bytes >= 2.5e8 ? 72 : 48));
+  return n >= row && std::min(g.nf[1], g.nf[2]) - 2 >= side;
 }
 
 // Default of the fine role of a D3Q19 H-RR level of `bytes` (two buffers):
 // whether a substep runs in one marching pass (k_hrr3s) or as the velocity
 // pass and the collision.  From 100 MB: us a step in two passes / in one,
 // FP32 65^3 107 / 124, 97^3 211 / 182, 129^3 406 / 390.  Rows that use less than
-// some third of a tile's columns (128, in double 64) keep the two passes: FP32
+// about 0.3 of a tile's columns (128, in double 64) keep the two passes: FP32
 // 9 x 401 x 401 nodes 497 / 890, 17 x 301 x 301 406 / 588, 33 x 301 x 301 708 /
 // 764, 37 x 301 x 301 757 / 776, 41 x 301 x 301 794 / 793, 45 x 301 x 301 850 / 819;
 // FP64 9 x 401 x 401 984 / 1259, 17 x 301 x 301 816 / 873, 21 x 301 x 301 904 /
@@ -83,22 +86,21 @@ inline bool fine3_by_default(const Geo& g, double bytes) {
 // 1034.
 template <typename S>
 inline bool hrr3_fine_by_default(const Geo& g, double bytes) {
-  return bytes >= 1e8 && g.nf[0] - 2 >= (sizeof(S) == 4 ? 40 : 22);
+  return bytes >= 1e8 && g.nf[0] - 2 >= (sizeof(S) == 4 ? 40 : 18);
 }
 
 // The same for a D3Q19 H-RR coarse level (n[3] nodes): from 2 GB.  us a step in
 // two passes / in one: FP32 256^3 844 / 736, 384 x 256 x 256 1210 / 1032, 1000 x 128 x
 // 128 819 / 739; FP64 200^3 799 / 695, 96 x 280 x 280 762 / 669, 66 x 320 x 320 771 / 760.
-// In FP32 rows that use less than four fifths of their tiles' columns (128, or
-// 192 by wide194) keep the two passes: 130 x 350 x 350 828 / 831, 194 x
-// 280 x 280 790 / 857, 200 x 300 x 300 911 / 976, 260 x 256 x 256 863 / 929, 300 x 256 x
-// 256 976 / 993; above, 160 x 320 x 320 829 / 715, 220 x 260 x 260 779 / 776, 320 x
-// 256 x 256 1026 / 932.
+// In FP32 rows that leave more than a fifth of the columns of two or three
+// tiles of 128 idle keep the two passes: 194 x 280 x 280 822 / 857, 200 x 300 x 300 945 /
+// 976, 260 x 256 x 256 893 / 930, 290 x 256 x 256 985 / 995.  Elsewhere one pass is level
+// or ahead: 130 x 350 x 350 860 / 832, 160 x 320 x 320 829 / 715, 300 x 256 x 256 988 /
+// 993, 300 x 1600 x 30 809 / 770, 390 x 240 x 240 1156 / 1121.
 template <typename S>
 inline bool hrr3_coarse_by_default(const int* n, double bytes) {
   if (bytes < 2e9) return false;
-  const int tile = wide194(n[0]) ? 192 : 128, columns = (n[0] + tile - 1) / tile * tile;
-  return sizeof(S) == 8 || 5 * n[0] >= 4 * columns;
+  return sizeof(S) == 8 || !((n[0] > 192 && n[0] < 205) || (n[0] > 256 && n[0] < 298));
 }
 
 // LDS variant (residency cap, kVarLds) of the H-RR collision in the two-pass

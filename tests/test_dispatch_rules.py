@@ -111,7 +111,9 @@ def test_marching_fine_kernel_limits(ask, cells, nbytes, fits):
     ((300, 300, 8), 4, False), ((300, 300, 16), 4, True),
     # short rows
     ((4, 200, 200), 4, False), ((16, 150, 150), 4, False), ((26, 150, 150), 4, True),
-    ((33, 100, 100), 4, False), ((40, 100, 100), 4, True),
+    ((33, 100, 100), 4, False), ((40, 100, 100), 4, True), ((30, 60, 60), 4, False),
+    # rows that fill tiles of 192 nodes
+    ((90, 90, 24), 4, True), ((90, 28, 90), 4, True), ((90, 90, 20), 4, True), ((90, 90, 18), 4, False),
     # short runs
     ((880, 880, 16), 4, False), ((765, 765, 16), 4, True),
     # double
@@ -126,7 +128,7 @@ def test_marching_fine_kernel_by_default(ask, cells, nbytes, march):
     ((40, 40, 40), 4, False), ((44, 44, 44), 4, True), ((128, 128, 128), 4, True),
     ((4, 200, 200), 4, False), ((18, 150, 150), 4, False), ((22, 150, 150), 4, True),
     ((150, 150, 8), 4, True), ((200, 4, 200), 4, True),
-    ((4, 200, 200), 8, False), ((10, 150, 150), 8, False), ((12, 150, 150), 8, True), ((64, 64, 64), 8, True),
+    ((4, 200, 200), 8, False), ((8, 150, 150), 8, False), ((10, 150, 150), 8, True), ((64, 64, 64), 8, True),
 ])
 def test_one_pass_hrr_fine_by_default(ask, cells, nbytes, one_pass):
     assert ask("hrr3", nbytes, *cells) == int(one_pass)
@@ -134,9 +136,9 @@ def test_one_pass_hrr_fine_by_default(ask, cells, nbytes, one_pass):
 
 @pytest.mark.parametrize("n,nbytes,one_pass", [
     ((200, 200, 200), 4, False), ((256, 256, 256), 4, True), ((384, 384, 384), 4, True),
-    ((130, 350, 350), 4, False), ((153, 350, 350), 4, False), ((154, 350, 350), 4, True), ((192, 300, 300), 4, True),
-    ((194, 280, 280), 4, False), ((204, 300, 300), 4, False), ((205, 300, 300), 4, True),
-    ((257, 300, 300), 4, False), ((307, 300, 300), 4, False), ((308, 300, 300), 4, True),
+    ((130, 350, 350), 4, True), ((160, 350, 350), 4, True), ((192, 300, 300), 4, True),
+    ((193, 300, 300), 4, False), ((204, 300, 300), 4, False), ((205, 300, 300), 4, True),
+    ((257, 300, 300), 4, False), ((297, 300, 300), 4, False), ((298, 300, 300), 4, True),
     ((180, 180, 180), 8, False), ((200, 200, 200), 8, True), ((66, 320, 320), 8, True),
 ])
 def test_one_pass_hrr_coarse_by_default(ask, n, nbytes, one_pass):
