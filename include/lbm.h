@@ -99,7 +99,8 @@ typedef struct {
  * history, stencil tables) and a non-blocking stream.  The state is
  * zero until lbm_set_state.  LBM_EINVAL for a bad descriptor, including a
  * level of 2^31 or more padded node positions (rows padded to a multiple of
- * 4 nodes). */
+ * 4 nodes; in D3Q19 fine levels of 512 MB to 64 GB, two buffers, to whole
+ * 128-byte lines where that takes at most 12 % more). */
 int lbm_create_grid(const lbm_grid_desc* d, lbm_handle* out);
 int lbm_destroy(lbm_handle h);
 
@@ -353,8 +354,8 @@ int lbm_batch_slot_steps(lbm_batch_handle b, int slot, int64_t* steps);
 /* Device bytes a grid of this descriptor occupies in a batch slot
  * (populations, macro planes, history, interface tables), for admission by
  * memory footprint.  Fine levels hold three population buffers for D2Q9
- * BGK / RR (the third keeps the half-step ring and band of the fused fine
- * kernel), two otherwise; a single D3Q19 BGK / RR grid (lbm_create_grid)
+ * BGK / RR (the third keeps the half-step ring of the fused fine kernel),
+ * two otherwise; a single D3Q19 BGK / RR grid (lbm_create_grid)
  * also holds a third.  D3Q19 BGK / RR fine levels add the compact copy of
  * the fine x-bands (2 * 19 * 5 values per fine (y, z) row). */
 int lbm_footprint(const lbm_grid_desc* d, int64_t* bytes);

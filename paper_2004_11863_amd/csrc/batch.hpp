@@ -27,7 +27,7 @@ struct InstDev {
   Flat fc, ff;  // flat numbering of the coarse / fine bulk vectors
   void* cbuf[2];
   void* fbuf[2];  // fbuf[fpar] holds the fine state at integer times
-  void* fh;       // fused: the t+1/2 ring and band (fine-to-coarse source)
+  void* fh;       // fused: the t+1/2 ring
   void* xb;       // D3Q19 BGK / RR: compact copy of the fine x-bands at t+1/2 (xband_at)
   void* mac_c;
   void* mac_f;
@@ -543,8 +543,9 @@ __global__ __launch_bounds__(256) void kb_stream_tail(const InstDev* __restrict_
   }
 }
 
-// Uniform (single-level) instances: stream (+ collide) of the coarse level.
-// Handled by kb_stream LEVEL 0; nothing else runs for them.
+// Uniform (single-level) instances have work in the coarse parts only: of
+// kb_stream_ring (BGK, RR), kb_hrr2c (D2Q9 H-RR), or kb_stream and kb_collide
+// LEVEL 0 (D3Q19 H-RR).
 
 // End of a coarse step outside a run of kPhases: the n descriptors move on.
 __global__ void kb_advance(InstDev* __restrict__ inst, int n) {

@@ -1583,9 +1583,9 @@ __global__ __launch_bounds__(256) void k_stream_ring(const S* __restrict__ src, 
 // Ring reconstruction at t+1 (Hp -> the fine buffer of integer times,
 // populations that stream inward) and the fine-to-coarse transfer (fine
 // state at t+1/2 -> coarse TN) in one launch: they write disjoint buffers and
-// read none of each other's outputs.  Blocks [0, nrb) take 256 ring nodes
-// each, the rest PER TN nodes each; both parts are XCD-contiguous (nrb is a
-// multiple of 8).  su: the transfer records the NH sensors' velocities of the
+// read none of each other's outputs.  Blocks [0, nrb) take 256 ring nodes each
+// (D3Q19: a tile of a face, ring3_tile), the rest a work group of TN nodes
+// (coalesce_body); both parts are XCD-contiguous (nrb is a multiple of 8).  su: the transfer records the NH sensors' velocities of the
 // TN nodes there (or null).
 template <int LAT, bool DEV, typename S, int MODEL>
 __global__ __launch_bounds__(256) void k_ring_coalesce(const double* __restrict__ Hp, S* __restrict__ fdst,

@@ -76,8 +76,9 @@ struct DevBuf {
 // device memory of that device, aligned for doubles, all of them inside one
 // allocation.  Anything else goes through a buffer of the library, by the
 // runtime's copies: these take another device's memory and mapped host memory
-// and refuse an array that ends before n values.  In place the fields move once instead of
-// three times: 4096^2 + 4097 x 2049 nodes, set and read back 1110 -> 560 us.
+// and refuse an array that ends before n values.  In place the fields move
+// once instead of three times: 4096^2 + 4097 x 2049 nodes, set and read back
+// 1110 -> 560 us.
 static bool in_place(const double* p, size_t n, int device) {
   if ((uintptr_t)p % sizeof(double)) return false;
   hipPointerAttribute_t a;
@@ -279,8 +280,9 @@ struct Grid final : GridBase {
   // Fine buffers: fbuf[fpar] holds the state at integer times.  A fused step
   // (BGK / RR: always in 2D, k_fine2; in 3D when the fine-role variant picks
   // k_fine3s) runs both fine substeps in one kernel from fbuf[fpar] into the
-  // other buffer, which then becomes current; fbuf[2] receives the t+1/2
-  // ring and the t+1/2 band the fine-to-coarse transfer pulls from.
+  // other buffer, which then becomes current; fbuf[2] receives the t+1/2 ring
+  // and, D3Q19, the t+1/2 y- and z-bands the fine-to-coarse transfer pulls from
+  // (D2Q9 with sensors on: the whole t+1/2 state).
   // Otherwise the substeps go fbuf[fpar] -> other -> fbuf[fpar].
   int fpar = 0;
   bool fused = false;
@@ -1621,7 +1623,7 @@ struct BatchBase {
 // Device bytes one grid of this descriptor needs in a batch slot
 // (populations, macro planes, history, interface tables), without any
 // scratch.  D2Q9 BGK / RR keep a third fine population buffer (the fused
-// fine phase's t+1/2 ring and band), D3Q19 BGK / RR the compact copy of the
+// fine phase's t+1/2 ring), D3Q19 BGK / RR the compact copy of the
 // fine x-bands.
 static int64_t grid_footprint(const lbm_grid_desc& d, const Geo& g) {
   const int Q = d.lattice == LBM_D2Q9 ? 9 : 19;
