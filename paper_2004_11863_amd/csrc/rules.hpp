@@ -51,13 +51,15 @@ inline int fine3_zcap(const Geo& g) {
 // leave columns of a tile idle, few rows or planes give short runs and idle
 // CUs, and a level of 250 to 600 MB, which the memory-side cache half holds,
 // loses least by its second pass.  Nodes of the level, us in two / in one:
-// FP32 to 600 MB, rows of 72 -- 61 x 121 x 121 98 / 118, 67 x 201 x 201 291 / 313, 81 x
-// 201 x 201 334 / 320 -- and to 250 MB sides of 48: 201 x 33 x 201 124 / 137, 399 x 9 x
-// 399 154 / 196, 121 x 61 x 121 92 / 85; to 600 MB of 72: 221 x 221 x 57 223 / 255, 221 x
-// 73 x 221 283 / 293; but of 36 where the row fills 194 x 5 tiles: 181 x 181 x 41 124 /
-// 115, x 57 158 / 150, x 73 196 / 186.  Beyond, rows of 48 -- 17 x 301 x 301 277 / 384,
-// 45 x 301 x 301 558 / 590, 53 x 301 x 301 606 / 597 -- and sides of 56 to 1 GB, of 19
-// above: 401 x 25 x 401 314 / 351, 301 x 301 x 49 355 / 366, 601 x 61 x 121 and 601 x
+// FP32 to 600 MB, rows of 72: 61 x 121 x 121 98 / 118, 67 x 201 x 201 291 / 313, 81 x
+// 201 x 201 334 / 320.  To 170 MB, in rows of 129 on of 130 x 7 or 194 x 5 tiles, sides
+// of 15: 181 x 181 x 29 99 / 91, 401 x 41 x 61 97 / 82, 401 x 121 x 17 90 / 86, 241 x 241 x
+// 19 112 / 112, 399 x 9 x 399 154 / 196.  To 250 MB sides of 48: 201 x 33 x 201 124 / 137, 221 x
+// 221 x 23 111 / 125, 221 x 29 x 221 130 / 157, 121 x 61 x 121 92 / 85.  To 600 MB of 72: 221 x
+// 221 x 57 223 / 255, 221 x 73 x 221 283 / 293; but of 36 where the row fills 194 x 5
+// tiles: 181 x 181 x 57 158 / 150, x 73 196 / 186.  Beyond, rows of 48 -- 17 x 301 x 301
+// 277 / 384, 45 x 301 x 301 558 / 590, 53 x 301 x 301 606 / 597 -- and sides of 56 to 1 GB,
+// of 19 above: 401 x 25 x 401 314 / 351, 301 x 301 x 49 355 / 366, 601 x 61 x 121 and 601 x
 // 601 x 33 10 % less in one, 601 x 601 x 21 603 / 590.  FP64, rows of 36 and sides of
 // 20: 33 x 301 x 301 606 / 618, 49 x 301 x 301 984 / 887; 301 x 301 x 19 270 / 282, x 23
 // 314 / 303.
@@ -70,7 +72,11 @@ inline bool fine3_by_default(const Geo& g, double bytes) {
   if (bytes < (single ? 1e8 : 5e8) || fine3_zcap<S>(g) < 8) return false;
   const int n = g.nf[0] - 2, row = single ? (bytes < 6e8 ? 72 : 48) : 36;
   int side = single ? 19 : 20;
-  if (single && bytes < 1e9) side = bytes >= 6e8 ? 56 : (n >= 154 && n <= 192 ? 36 : (bytes >= 2.5e8 ? 72 : 48));
+  if (single && bytes < 1e9) {
+    if (bytes < 1.7e8 && n > 128 && !tall66(n, false)) side = 15;
+    else if (bytes < 6e8) side = n >= 154 && n <= 192 ? 36 : (bytes < 2.5e8 ? 48 : 72);
+    else side = 56;
+  }
   return n >= row && std::min(g.nf[1], g.nf[2]) - 2 >= side;
 }
 

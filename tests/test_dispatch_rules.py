@@ -113,7 +113,10 @@ def test_marching_fine_kernel_limits(ask, cells, nbytes, fits):
     ((4, 200, 200), 4, False), ((16, 150, 150), 4, False), ((26, 150, 150), 4, True),
     ((33, 100, 100), 4, False), ((40, 100, 100), 4, True), ((30, 60, 60), 4, False),
     # rows that fill tiles of 192 nodes
-    ((90, 90, 24), 4, True), ((90, 28, 90), 4, True), ((90, 90, 20), 4, True), ((90, 90, 18), 4, False),
+    ((90, 90, 24), 4, True), ((90, 28, 90), 4, True), ((90, 90, 20), 4, True), ((90, 90, 17), 4, False),
+    # rows of several tiles in levels that the memory-side cache holds
+    ((90, 90, 14), 4, True), ((200, 20, 30), 4, True), ((200, 60, 8), 4, True), ((300, 20, 7), 4, False),
+    ((60, 60, 23), 4, False), ((110, 110, 11), 4, False), ((110, 14, 110), 4, False),
     # short runs
     ((880, 880, 16), 4, False), ((765, 765, 16), 4, True),
     # double
