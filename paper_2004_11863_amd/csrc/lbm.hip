@@ -1695,7 +1695,13 @@ struct Batch final : BatchBase {
   // One step (with kb_advance), and a run of kPhases steps: a replay of a run
   // instead of six saves five gaps between graphs and six kb_advance launches
   // (60 steps: 12 planes H-RR FP32 7.69 -> 7.33 ms, 20 planes RR 9.61 -> 9.24,
-  // 8 boxes RR 12.88 -> 12.56).
+  // 8 boxes RR 12.88 -> 12.56).  Capturing a run takes as long as some four of its
+  // replays save, so it waits until kRunAfter steps have been asked for since
+  // the graphs were dropped: a first call of 6 / 12 / 20 steps of three 64^2 planes,
+  // H-RR FP64, 511 / 701 / 979 us with the run, 290 / 530 / 835 without; of two 20^3
+  // boxes, H-RR FP32, 845 / 1276 / 1884 and 631 / 1100 / 1772.
+  static constexpr int kRunAfter = 4 * kPhases;
+  int64_t graph_steps = 0;  // steps replayed since the graphs were dropped
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
   int phase = 0;  // descriptor phase the launches below read
@@ -1708,6 +1714,7 @@ struct Batch final : BatchBase {
       exec[k] = nullptr;
       graph[k] = nullptr;
     }
+    graph_steps = 0;
   }
 
   void init(int cap) {
@@ -2222,11 +2229,12 @@ struct Batch final : BatchBase {
     for (int k = 0; k < capacity; ++k) active += slots[(size_t)k] ? 1 : 0;
     if (active == 0 || n <= 0) return;
     for (int k = 0; k < n;) {
-      const bool run = n - k >= kPhases;
+      const bool run = n - k >= kPhases && (!use_graph || exec[1] || graph_steps + (n - k) >= kRunAfter);
       if (use_graph && !exec[run]) capture(run);
       if (use_graph) HIPCHK(hipGraphLaunch(exec[run], s));
       else launch_steps(run, s);
       k += run ? kPhases : 1;
+      if (use_graph) graph_steps += run ? kPhases : 1;
     }
     HIPCHK(hipGetLastError());
     HIPCHK(hipEventRecord(stepped, s));
