@@ -301,7 +301,7 @@ const char* lbm_last_error(lbm_handle h);
  * precision, each with its own geometry, tau and sigma, advanced together.
  * Each coarse step is one sequence of launches over the work of all grids
  * (bulk chunks, interface node blocks), captured once as a hipGraph (one step
- * and a run of six) and replayed; grids may join and leave between steps (continuous batching),
+ * and, from 24 steps on, a run of six) and replayed; grids may join and leave between steps (continuous batching),
  * which rewrites device work lists (the launch is captured again when a list
  * outgrows its buffer, after lbm_batch_tune or lbm_batch_set_variants, and
  * when graphs are switched off and on).  A grid in a batch computes exactly what the
